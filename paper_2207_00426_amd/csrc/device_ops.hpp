@@ -404,7 +404,6 @@ template <typename T, int NX, int NZ, class VI, class VJ, class VO>
 PSS_INL void filter_combine_v(const VI &ei, const VJ &ej, const VO &o)
 {
     constexpr int C = NZ + NX;
-    constexpr int K = cmin(2 * NX, C);
     // bi and q = eta_j - Z_j Z_j^T b_i need the inputs only; computing them
     // first keeps U_i, Z_j out of the Tria below
     T v[NX], q[NX];
@@ -436,10 +435,13 @@ PSS_INL void filter_combine_v(const VI &ei, const VJ &ej, const VO &o)
             v[i] = bi[i];
             q[i] = etj[i] - s;
         }
-        // Xi = Tria([[U_i^T Z_j, I], [Z_j, 0]])
         xi_block(Ui, Zj, M);
     }
-    lq_rows<K, NZ>(M);
+    // Xi's upper rows only: its lower right block enters through its Gram
+    // matrix alone (Z below), so the rows left there by the first NX
+    // reflections serve as they are, NX x NZ and dense, and the other NX
+    // reflections of the printed Tria need not run
+    lq_rows<NX, NZ>(M);
     // Tm = U_i Xi11^{-T}, G = I - Tm Xi21^T
     T Tm[NX][NX], G[NX][NX];
     {
@@ -507,16 +509,16 @@ PSS_INL void filter_combine_v(const VI &ei, const VJ &ej, const VO &o)
         for (int i = 0; i < NX; ++i)
             o.seta(i, aq[i] + ei.eta(i));
     }
-    // Z = Tria([A_i^T Xi22, Z_i]); Xi22 is NX x NZ lower trapezoidal
+    // Z = Tria([A_i^T Xi22, Z_i])
     {
         T AX[NX][NZ];
 #pragma unroll
         for (int a = 0; a < NX; ++a)
 #pragma unroll
             for (int c = 0; c < NZ; ++c) {
-                T s = Ai[c][a] * M[NX + c][NX + c];
+                T s = Ai[0][a] * M[NX][NX + c];
 #pragma unroll
-                for (int t = c + 1; t < NX; ++t)
+                for (int t = 1; t < NX; ++t)
                     s = pfma(Ai[t][a], M[NX + t][NX + c], s);
                 AX[a][c] = s;
             }

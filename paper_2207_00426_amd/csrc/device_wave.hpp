@@ -11,9 +11,7 @@
 // are simply absent; a lane outside the matrix carries rho = -1 and is never
 // updated.
 //
-// The reflector is the one of pss::lq_rows (pivot taken cancellation-free,
-// tau = -1 / (r v0), FP32 rows scaled by a power of two, a tail below machine
-// epsilon relative to a positive pivot left alone), so a wave sweep and a
+// The reflector is pss::reflector, as in pss::lq_rows, so a wave sweep and a
 // one-thread sweep of the same matrix differ only in where each row's
 // arithmetic runs.
 #pragma once
@@ -76,27 +74,23 @@ __device__ __forceinline__ void lq_rows(T (&a)[C], int rho)
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
             sig = pfma(x[j], x[j], sig);
-        const T al = x[i];
-        const T nr = psqrt(pfma(al, al, sig));
-        const T v0 = (al > T(0)) ? -sig * prcp(al + nr) : (al - nr);
-        const T p = nr * v0;
-        const bool skip = !(p < T(0)) || (al > T(0) && sig <= Eps<T>::v * Eps<T>::v * al * al);
-        const T tau = skip ? T(0) : -prcp(p);
+        T beta, tau, d;
+        bool neg;
+        reflector(x[i], sig, beta, tau, d, neg);
         if (rho > i) {
-            T w = a[i] * v0;
+            const T ap = pflip(a[i], neg);
+            T w = -(beta * ap);
 #pragma unroll
             for (int j = i + 1; j < jend; ++j)
                 w = pfma(a[j], x[j], w);
             const T tw = tau * w;
-            a[i] = pfma(-tw, v0, a[i]);
+            a[i] = pfma(tw, beta, ap);
 #pragma unroll
             for (int j = i + 1; j < jend; ++j)
                 a[j] = pfma(-tw, x[j], a[j]);
         }
-        if (rho == i) {
-            const T d = (skip && al > T(0)) ? al : nr;
+        if (rho == i)
             a[i] = kScale ? pldexp(d, ex) : d;
-        }
     }
 }
 
