@@ -119,20 +119,34 @@ PSS_INL float pnorm(float s)
 // x with its sign flipped where neg
 template <typename T>
 PSS_INL T pflip(T x, bool neg) { return neg ? -x : x; }
+template <>
+PSS_INL double pflip(double x, bool neg)
+{
+    union {
+        double d;
+        unsigned u[2];
+    } v = {x};
+    v.u[1] ^= neg ? 0x80000000u : 0u;
+    return v.d;
+}
 
 // beta, tau, the reduced diagonal d and the column's sign from a row's pivot
-// and the sum of squares of its tail
+// and the sum of squares of its tail.  A vanishing row is masked out by a
+// factor, not by a branch around the root and the reciprocal (the compiler
+// makes one of a select there): beta = d = tau = 0.
 template <typename T>
 PSS_INL void reflector(T al, T sig, T &beta, T &tau, T &d, bool &neg)
 {
+    constexpr double tiny = sizeof(T) == 4 ? 1e-30 : 1e-290;
     const T s = pfma(al, al, sig);
-    const T nr = pnorm(s);
-    const bool go = s > T(sizeof(T) == 4 ? 1e-30 : 1e-290);
-    beta = go ? pabs(al) + nr : T(0);
-    tau = go ? prcp(nr * beta) : T(0);
-    neg = go && al > T(0);
-    // s as it is: zero for a zero row, NaN for a NaN row
-    d = go ? nr : (s > T(0) ? pabs(al) : s);
+    const T on = s > T(tiny) ? T(1) : T(0);
+    const T nr = pnorm(pmax(s, T(tiny)));
+    const T aa = pabs(al);
+    tau = prcp(nr * (aa + nr)) * on;
+    // s - s: NaN where the row's norm is not finite
+    d = pfma(nr, on, s - s);
+    beta = pfma(aa, on, d);
+    neg = al > T(0);
 }
 
 template <int K, int Z0, typename T, int R, int C>

@@ -8,6 +8,7 @@
 #include "adjoint.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
+#include "scan_group.hpp"
 
 namespace pss {
 
@@ -185,6 +186,24 @@ struct Core {
         int rc = launch_plan(c, sh, extra, w.tile_off, w.elem_off);
         if (rc)
             return rc;
+        // levels above the finest: one element per 16-lane group where the
+        // scan has group operators (their elements and prefixes stored whole),
+        // else one per lane
+        constexpr bool Grp = GroupOp<Op>::value;
+        auto agg_of = [&](int l) {
+            if constexpr (Grp)
+                return typename GroupOp<Op>::Ref{w.agg[l]};
+            else
+                return agg_ref(w.agg[l], sh.nelem[l]);
+        };
+        auto pre_of = [&](int l) {
+            if constexpr (Grp)
+                return MargAos<T, NX>{w.pre[l]};
+            else
+                return marg_ref(w.pre[l], sh.nelem[l]);
+        };
+        using Agg = decltype(agg_of(1));
+        using Pre = decltype(pre_of(1));
         using LvSrc = RefSrc<Op, AggRef>;
         using LvSrcI = RefSrc<Op, AggRef, true>;
         using LvDst = PreDst<Op, MargRef<T, NX>>;
@@ -199,6 +218,9 @@ struct Core {
             g.E = sh.E[l];
             g.stage = scan_stage(Op::NE, Op::NP, sh.T[l], sh.E[l], sizeof(T));
             return g;
+        };
+        auto ggeom = [&](int l) {
+            return GroupGeom{w.elem_off[l], w.tile_off[l], c.B, sh.T[l] * sh.E[l]};
         };
         // calls launch(src) with the element source of level l >= 1
         auto with_src = [&](int l, auto &&launch) -> int {
@@ -216,34 +238,41 @@ struct Core {
                 continue;
             const LevelGeom g = geom(l);
             const int64_t tree_ld = sh.ntiles[l] * sh.T[l];
-            AggRef agg = agg_ref(w.agg[l + 1], sh.nelem[l + 1]);
             const size_t lb = lds_bytes<Op>(sh.T[l], sh.E[l], g.stage);
+            const dim3 grid((unsigned)sh.ntiles[l]);
             KTime kt(c.s, Op::name, "up", l);
             if (l == 0) {
+                const Agg agg = agg_of(1);
                 bool flat = false;
                 if constexpr (Flat) {
                     if ((flat = sh.flat[0])) {
-                        auto k = k_scan_up_flat<Op, Src0, AggRef>;
+                        auto k = k_scan_up_flat<Op, Src0, Agg>;
                         if ((rc = prep_lds(k, lb)))
                             return rc;
-                        hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb,
-                                           c.s, g, src0, agg, w.elem_off[1], sh.T[1], sh.E[1]);
+                        // nE = 1: whole elements need no interleaving
+                        hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, agg,
+                                           w.elem_off[1], sh.T[1], Grp ? 1 : sh.E[1]);
                     }
                 }
                 if (!flat) {
-                    auto k = k_scan_up<Op, Src0, AggRef>;
+                    auto k = k_scan_up<Op, Src0, Agg>;
                     if ((rc = prep_lds(k, lb)))
                         return rc;
-                    hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb, c.s,
-                                       g, src0, agg, w.tree[l], tree_ld);
+                    hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, agg, w.tree[l],
+                                       tree_ld);
                 }
+            } else if constexpr (Grp) {
+                static_assert(kGroups <= 64, "the saved prefixes use the tree's space");
+                hipLaunchKernelGGL((k_group_up<Op>), grid, dim3(kGroupThreads), 0, c.s, ggeom(l),
+                                   w.agg[l], w.agg[l + 1], w.tree[l]);
             } else {
                 rc = with_src(l, [&](auto s) -> int {
                     auto k = k_scan_up<Op, decltype(s), AggRef>;
                     if (int r = prep_lds(k, lb))
                         return r;
-                    hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb, c.s,
-                                       g, s, agg, w.tree[l], tree_ld);
+                    hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, s,
+                                       agg_ref(w.agg[l + 1], sh.nelem[l + 1]), w.tree[l],
+                                       tree_ld);
                     return 0;
                 });
                 if (rc)
@@ -257,21 +286,23 @@ struct Core {
             const int l = sh.L - 1;
             const LevelGeom g = geom(l);
             const size_t lb = lds_bytes<Op>(sh.T[l], sh.E[l], g.stage);
+            const dim3 grid((unsigned)sh.ntiles[l]);
             KTime kt(c.s, Op::name, "top", l);
             if (l == 0) {
                 auto k = k_scan_top<Op, Src0, Dst0, Start>;
                 if ((rc = prep_lds(k, lb)))
                     return rc;
-                hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb, c.s, g,
-                                   src0, dst0, start);
+                hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, dst0, start);
+            } else if constexpr (Grp) {
+                hipLaunchKernelGGL((k_group_top<Op, Start>), grid, dim3(kGroupThreads), 0, c.s,
+                                   ggeom(l), w.agg[l], w.pre[l], start);
             } else {
                 LvDst d{marg_ref(w.pre[l], sh.nelem[l])};
                 rc = with_src(l, [&](auto s) -> int {
                     auto k = k_scan_top<Op, decltype(s), LvDst, Start>;
                     if (int r = prep_lds(k, lb))
                         return r;
-                    hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb, c.s,
-                                       g, s, d, start);
+                    hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, s, d, start);
                     return 0;
                 });
                 if (rc)
@@ -285,34 +316,39 @@ struct Core {
             const LevelGeom g = geom(l);
             const int64_t tree_ld = sh.ntiles[l] * sh.T[l];
             const size_t lb = lds_bytes<Op>(sh.T[l], sh.E[l], g.stage);
-            MargRef<T, NX> pin = marg_ref(w.pre[l + 1], sh.nelem[l + 1]);
+            const dim3 grid((unsigned)sh.ntiles[l]);
             KTime kt(c.s, Op::name, "down", l);
             if (l == 0) {
+                const Pre pin = pre_of(1);
                 bool flat = false;
                 if constexpr (Flat) {
                     if ((flat = sh.flat[0])) {
-                        auto k = k_scan_down_flat<Op, Src0, Dst0, MargRef<T, NX>>;
+                        auto k = k_scan_down_flat<Op, Src0, Dst0, Pre>;
                         if ((rc = prep_lds(k, lb)))
                             return rc;
-                        hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb,
-                                           c.s, g, src0, dst0, w.elem_off[1], pin);
+                        hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, dst0,
+                                           w.elem_off[1], pin);
                     }
                 }
                 if (!flat) {
-                    auto k = k_scan_down<Op, Src0, Dst0, MargRef<T, NX>>;
+                    auto k = k_scan_down<Op, Src0, Dst0, Pre>;
                     if ((rc = prep_lds(k, lb)))
                         return rc;
-                    hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb, c.s,
-                                       g, src0, dst0, w.tree[l], tree_ld, pin);
+                    hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, dst0, w.tree[l],
+                                       tree_ld, pin);
                 }
+            } else if constexpr (Grp) {
+                hipLaunchKernelGGL((k_group_down<Op>), grid, dim3(kGroupThreads), 0, c.s,
+                                   ggeom(l), w.agg[l], w.tree[l], w.pre[l + 1], w.pre[l]);
             } else {
                 LvDst d{marg_ref(w.pre[l], sh.nelem[l])};
+                MargRef<T, NX> pin = marg_ref(w.pre[l + 1], sh.nelem[l + 1]);
                 rc = with_src(l, [&](auto s) -> int {
                     auto k = k_scan_down<Op, decltype(s), LvDst, MargRef<T, NX>>;
                     if (int r = prep_lds(k, lb))
                         return r;
-                    hipLaunchKernelGGL(k, dim3((unsigned)sh.ntiles[l]), dim3(sh.T[l]), lb, c.s,
-                                       g, s, d, w.tree[l], tree_ld, pin);
+                    hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, s, d, w.tree[l],
+                                       tree_ld, pin);
                     return 0;
                 });
                 if (rc)
