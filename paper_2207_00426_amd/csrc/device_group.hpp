@@ -123,15 +123,16 @@ __device__ __forceinline__ void lq(T (&row)[C], int rho, T (&inv)[K])
         bool neg;
         reflector(x[i], sig, beta, tau, d, neg);
         inv[i] = kScale ? pldexp(tau * beta, -ex) : tau * beta;
-        const bool live = rho > i;
+        // every row takes the reflection: on a row that is already reduced it
+        // reaches only columns right of that row's diagonal, which are stale
         const T ap = pflip(row[i], neg);
         T w = -(beta * ap);
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
             w = pfma(row[j], x[j], w);
-        const T tw = live ? tau * w : T(0);
+        const T tw = tau * w;
         const T nw = pfma(tw, beta, ap);
-        row[i] = live ? nw : (rho == i ? (kScale ? pldexp(d, ex) : d) : row[i]);
+        row[i] = rho == i ? (kScale ? pldexp(d, ex) : d) : nw;
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
             row[j] = pfma(-tw, x[j], row[j]);
