@@ -9,6 +9,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "scan_group.hpp"
+#include "steps.hpp"
 
 namespace pss {
 
@@ -32,6 +33,7 @@ struct Defaults {
     static constexpr int T0 = 64;
     static constexpr int E0_filter = 4;
     static constexpr int E0_smoother = 2;
+    static constexpr int E0_step = 8;
     static constexpr int Tup = 64;
     static constexpr int E1_filter = 4;
     static constexpr int E1_smoother = 2;
@@ -40,6 +42,10 @@ struct Defaults {
     static constexpr bool flat_filter = true;
     static constexpr bool flat_smoother = false;
 };
+
+// marginals of a call up to this size are written in the caller's layout by
+// the last smoothing pass itself
+constexpr size_t kDirectBytes = size_t(16) << 20;
 
 template <typename T, int NX, int NY>
 struct Core {
@@ -170,55 +176,67 @@ struct Core {
                          "hipFuncSetAttribute");
     }
 
-    // generic multi-level scan driver; Flat: level 0 may be flat (then it
-    // is, see plan_scan, and level 1 is stored tile-interleaved)
+    // references to a level's elements and prefixes: one element per 16-lane
+    // group above the finest level where the scan has group operators (stored
+    // whole), else one per lane
+    template <class Op, class AggRef>
+    static auto agg_of(const ScanShape &sh, const ScanWs<Op> &w, int l,
+                       AggRef (*agg_ref)(T *, int64_t))
+    {
+        if constexpr (GroupOp<Op>::value)
+            return typename GroupOp<Op>::Ref{w.agg[l]};
+        else
+            return agg_ref(w.agg[l], sh.nelem[l]);
+    }
+    template <class Op>
+    static auto pre_of(const ScanShape &sh, const ScanWs<Op> &w, int l)
+    {
+        if constexpr (GroupOp<Op>::value)
+            return MargAos<T, NX>{w.pre[l]};
+        else
+            return marg_ref(w.pre[l], sh.nelem[l]);
+    }
+    // elements per thread that the finest level's aggregates are interleaved
+    // for (whole elements need no interleaving)
+    template <class Op>
+    static int agg_ilv(const ScanShape &sh) { return GroupOp<Op>::value ? 1 : sh.E[1]; }
+
+    template <class Op>
+    static LevelGeom level_geom(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int l,
+                                int extra)
+    {
+        LevelGeom g;
+        g.y_off = c.p->y_off;
+        g.elem_off = l > 0 ? w.elem_off[l] : nullptr;
+        g.tile_off = w.tile_off[l];
+        g.level = l;
+        g.extra = extra;
+        g.B = c.B;
+        g.E = sh.E[l];
+        g.stage = scan_stage(Op::NE, Op::NP, sh.T[l], sh.E[l], sizeof(T));
+        return g;
+    }
+
+    // multi-level scan driver: the finest level's kernels come from the caller
+    // (up0 writes the elements of level 1, down0 reads their prefixes, top0 is
+    // the whole scan where level 0 is the top), the levels above run here.
+    // Flat: level 0 may be flat (then it is, see plan_scan).
     // stop > 0 (and < sh.L): run only the levels below `stop`, whose
     // exclusive prefixes w.pre[stop] the caller provides (a checkpoint):
     // the up-sweeps that rebuild those levels' trees and elements, then their
     // down-sweeps; the levels from `stop` up are not run.
-    template <class Op, bool Flat, class Src0, class Dst0, class AggRef, class Start>
-    static int run_scan(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int extra,
-                        const Src0 &src0, const Dst0 &dst0, const Start &start,
-                        AggRef (*agg_ref)(T *, int64_t), int stop = 0)
+    template <class Op, bool Flat, class AggRef, class Start, class Up0, class Top0, class Down0>
+    static int run_levels(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int extra,
+                          const Start &start, AggRef (*agg_ref)(T *, int64_t), int stop,
+                          const Up0 &up0, const Top0 &top0, const Down0 &down0)
     {
         const int top = (stop > 0 && stop < sh.L) ? stop : sh.L;
         const bool partial = top < sh.L;
-        int rc = launch_plan(c, sh, extra, w.tile_off, w.elem_off);
-        if (rc)
-            return rc;
-        // levels above the finest: one element per 16-lane group where the
-        // scan has group operators (their elements and prefixes stored whole),
-        // else one per lane
+        int rc = PSS_OK;
         constexpr bool Grp = GroupOp<Op>::value;
-        auto agg_of = [&](int l) {
-            if constexpr (Grp)
-                return typename GroupOp<Op>::Ref{w.agg[l]};
-            else
-                return agg_ref(w.agg[l], sh.nelem[l]);
-        };
-        auto pre_of = [&](int l) {
-            if constexpr (Grp)
-                return MargAos<T, NX>{w.pre[l]};
-            else
-                return marg_ref(w.pre[l], sh.nelem[l]);
-        };
-        using Agg = decltype(agg_of(1));
-        using Pre = decltype(pre_of(1));
         using LvSrc = RefSrc<Op, AggRef>;
         using LvSrcI = RefSrc<Op, AggRef, true>;
         using LvDst = PreDst<Op, MargRef<T, NX>>;
-        auto geom = [&](int l) {
-            LevelGeom g;
-            g.y_off = c.p->y_off;
-            g.elem_off = l > 0 ? w.elem_off[l] : nullptr;
-            g.tile_off = w.tile_off[l];
-            g.level = l;
-            g.extra = extra;
-            g.B = c.B;
-            g.E = sh.E[l];
-            g.stage = scan_stage(Op::NE, Op::NP, sh.T[l], sh.E[l], sizeof(T));
-            return g;
-        };
         auto ggeom = [&](int l) {
             return GroupGeom{w.elem_off[l], w.tile_off[l], c.B, sh.T[l] * sh.E[l]};
         };
@@ -236,32 +254,17 @@ struct Core {
         for (int l = 0; l + 1 < sh.L && l < top; ++l) {
             if (partial && l == top - 1 && sh.flat[l])
                 continue;
-            const LevelGeom g = geom(l);
+            if (l == 0) {
+                if ((rc = up0()))
+                    return rc;
+                continue;
+            }
+            const LevelGeom g = level_geom(c, sh, w, l, extra);
             const int64_t tree_ld = sh.ntiles[l] * sh.T[l];
             const size_t lb = lds_bytes<Op>(sh.T[l], sh.E[l], g.stage);
             const dim3 grid((unsigned)sh.ntiles[l]);
             KTime kt(c.s, Op::name, "up", l);
-            if (l == 0) {
-                const Agg agg = agg_of(1);
-                bool flat = false;
-                if constexpr (Flat) {
-                    if ((flat = sh.flat[0])) {
-                        auto k = k_scan_up_flat<Op, Src0, Agg>;
-                        if ((rc = prep_lds(k, lb)))
-                            return rc;
-                        // nE = 1: whole elements need no interleaving
-                        hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, agg,
-                                           w.elem_off[1], sh.T[1], Grp ? 1 : sh.E[1]);
-                    }
-                }
-                if (!flat) {
-                    auto k = k_scan_up<Op, Src0, Agg>;
-                    if ((rc = prep_lds(k, lb)))
-                        return rc;
-                    hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, agg, w.tree[l],
-                                       tree_ld);
-                }
-            } else if constexpr (Grp) {
+            if constexpr (Grp) {
                 static_assert(kGroups <= 64, "the saved prefixes use the tree's space");
                 hipLaunchKernelGGL((k_group_up<Op>), grid, dim3(kGroupThreads), 0, c.s, ggeom(l),
                                    w.agg[l], w.agg[l + 1], w.tree[l]);
@@ -282,18 +285,16 @@ struct Core {
                 return rc;
         }
         // top level
-        if (!partial) {
+        if (!partial && sh.L == 1) {
+            if ((rc = top0()))
+                return rc;
+        } else if (!partial) {
             const int l = sh.L - 1;
-            const LevelGeom g = geom(l);
+            const LevelGeom g = level_geom(c, sh, w, l, extra);
             const size_t lb = lds_bytes<Op>(sh.T[l], sh.E[l], g.stage);
             const dim3 grid((unsigned)sh.ntiles[l]);
             KTime kt(c.s, Op::name, "top", l);
-            if (l == 0) {
-                auto k = k_scan_top<Op, Src0, Dst0, Start>;
-                if ((rc = prep_lds(k, lb)))
-                    return rc;
-                hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, dst0, start);
-            } else if constexpr (Grp) {
+            if constexpr (Grp) {
                 hipLaunchKernelGGL((k_group_top<Op, Start>), grid, dim3(kGroupThreads), 0, c.s,
                                    ggeom(l), w.agg[l], w.pre[l], start);
             } else {
@@ -313,31 +314,17 @@ struct Core {
         }
         // down-sweeps of the lower levels
         for (int l = top - (partial ? 1 : 2); l >= 0; --l) {
-            const LevelGeom g = geom(l);
+            if (l == 0) {
+                if ((rc = down0()))
+                    return rc;
+                continue;
+            }
+            const LevelGeom g = level_geom(c, sh, w, l, extra);
             const int64_t tree_ld = sh.ntiles[l] * sh.T[l];
             const size_t lb = lds_bytes<Op>(sh.T[l], sh.E[l], g.stage);
             const dim3 grid((unsigned)sh.ntiles[l]);
             KTime kt(c.s, Op::name, "down", l);
-            if (l == 0) {
-                const Pre pin = pre_of(1);
-                bool flat = false;
-                if constexpr (Flat) {
-                    if ((flat = sh.flat[0])) {
-                        auto k = k_scan_down_flat<Op, Src0, Dst0, Pre>;
-                        if ((rc = prep_lds(k, lb)))
-                            return rc;
-                        hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, dst0,
-                                           w.elem_off[1], pin);
-                    }
-                }
-                if (!flat) {
-                    auto k = k_scan_down<Op, Src0, Dst0, Pre>;
-                    if ((rc = prep_lds(k, lb)))
-                        return rc;
-                    hipLaunchKernelGGL(k, grid, dim3(sh.T[l]), lb, c.s, g, src0, dst0, w.tree[l],
-                                       tree_ld, pin);
-                }
-            } else if constexpr (Grp) {
+            if constexpr (Grp) {
                 hipLaunchKernelGGL((k_group_down<Op>), grid, dim3(kGroupThreads), 0, c.s,
                                    ggeom(l), w.agg[l], w.tree[l], w.pre[l + 1], w.pre[l]);
             } else {
@@ -358,6 +345,70 @@ struct Core {
                 return rc;
         }
         return PSS_OK;
+    }
+
+    // a scan whose finest level folds and applies given elements (Src0, Dst0)
+    template <class Op, bool Flat, class Src0, class Dst0, class AggRef, class Start>
+    static int run_scan(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int extra,
+                        const Src0 &src0, const Dst0 &dst0, const Start &start,
+                        AggRef (*agg_ref)(T *, int64_t), int stop = 0)
+    {
+        int rc = launch_plan(c, sh, extra, w.tile_off, w.elem_off);
+        if (rc)
+            return rc;
+        const LevelGeom g = level_geom(c, sh, w, 0, extra);
+        const int64_t tree_ld = sh.ntiles[0] * sh.T[0];
+        const size_t lb = lds_bytes<Op>(sh.T[0], sh.E[0], g.stage);
+        const dim3 grid((unsigned)sh.ntiles[0]), block(sh.T[0]);
+        auto up0 = [&]() -> int {
+            KTime kt(c.s, Op::name, "up", 0);
+            const auto agg = agg_of(sh, w, 1, agg_ref);
+            using Agg = std::decay_t<decltype(agg)>;
+            if constexpr (Flat) {
+                if (sh.flat[0]) {
+                    auto k = k_scan_up_flat<Op, Src0, Agg>;
+                    if (int r = prep_lds(k, lb))
+                        return r;
+                    hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, agg, w.elem_off[1],
+                                       sh.T[1], agg_ilv<Op>(sh));
+                    return hip_check(hipGetLastError(), "scan up launch");
+                }
+            }
+            auto k = k_scan_up<Op, Src0, Agg>;
+            if (int r = prep_lds(k, lb))
+                return r;
+            hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, agg, w.tree[0], tree_ld);
+            return hip_check(hipGetLastError(), "scan up launch");
+        };
+        auto top0 = [&]() -> int {
+            KTime kt(c.s, Op::name, "top", 0);
+            auto k = k_scan_top<Op, Src0, Dst0, Start>;
+            if (int r = prep_lds(k, lb))
+                return r;
+            hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, dst0, start);
+            return hip_check(hipGetLastError(), "scan top launch");
+        };
+        auto down0 = [&]() -> int {
+            KTime kt(c.s, Op::name, "down", 0);
+            const auto pin = pre_of(sh, w, 1);
+            using Pre = std::decay_t<decltype(pin)>;
+            if constexpr (Flat) {
+                if (sh.flat[0]) {
+                    auto k = k_scan_down_flat<Op, Src0, Dst0, Pre>;
+                    if (int r = prep_lds(k, lb))
+                        return r;
+                    hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, dst0, w.elem_off[1],
+                                       pin);
+                    return hip_check(hipGetLastError(), "scan down launch");
+                }
+            }
+            auto k = k_scan_down<Op, Src0, Dst0, Pre>;
+            if (int r = prep_lds(k, lb))
+                return r;
+            hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, dst0, w.tree[0], tree_ld, pin);
+            return hip_check(hipGetLastError(), "scan down launch");
+        };
+        return run_levels<Op, Flat>(c, sh, w, extra, start, agg_ref, stop, up0, top0, down0);
     }
 
     // ------------------------------------------------------------------
@@ -642,8 +693,23 @@ struct Core {
     // from it up keep nothing but the log-likelihoods)
     static int filter_levels(const Ctx &c) { return filter_shape(c).L; }
 
-    static int ipls(const Ctx &c, const pss_gamma *gin, const void *y, int n_iter, void *m_nom,
-                    void *N_nom, void *mf_out, void *Nf_out, void *ws)
+    // tiles of the finest level when it runs Kalman steps (steps.hpp)
+    static ScanShape step_shape(const Ctx &c)
+    {
+        int T0, E0, Tup, E1, Eup;
+        shapes(c, false, T0, E0, Tup, E1, Eup);
+        if (c.p->scan_elems <= 0)
+            E0 = Defaults<T, NX>::E0_step;
+        return plan_scan(c, 0, T0, E0, Tup, E1, Eup, true);
+    }
+
+    // linearisation of every step into its interleaved slot
+    static int step_lin(const Ctx &c, const NomRef<T, NX> &nom, const void *y,
+                        const pss_gamma *out, const ScanShape &sh);
+
+    // Algorithm 3 in covariance form: the scans over stored elements
+    static int ipls_cov(const Ctx &c, const pss_gamma *gin, const void *y, int n_iter,
+                        void *m_nom, void *N_nom, void *mf_out, void *Nf_out, void *ws)
     {
         Carver cv{static_cast<char *>(ws)};
         pss_gamma gw = carve_gamma(cv, c.T_y);
@@ -651,12 +717,6 @@ struct Core {
         T *mfb = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
         void *scan_ws = cv.base + cv.used;
         const pss_gamma *g = nonlinear(c) ? &gw : gin;
-        // FP32: the CT model's passes run in deviation coordinates relative
-        // to the nominal means (see Ctx), unless the caller takes the
-        // filtering marginals (those are absolute).  On the 10^6-step track
-        // this cut the late passes' mean error about 5x; FP64 loses nothing
-        // measurable in absolute coordinates and keeps them (the offsets and
-        // the smoother's read of the nominal cost 0.04 ms per pass there).
         Ctx cs = c;
         if (sizeof(T) == 4 && c.p->model == PSS_MODEL_CT_BEARINGS && !mf_out)
             cs.dev_m = m_nom;
@@ -665,10 +725,9 @@ struct Core {
         void *mf = mf_out ? mf_out : (void *)mfb;
         void *Nf = mf_out ? Nf_out : (void *)(mfb + (size_t)NX * c.T_x);
         int rc = PSS_OK;
-        const bool cov = c.p->form == PSS_FORM_COV;
         for (int it = 0; it < n_iter && rc == PSS_OK; ++it) {
             const int fused =
-                nonlinear(c) ? slr_felem(cs, m_nom, N_nom, y, &gw, &el, cov, false) : 1;
+                nonlinear(c) ? slr_felem(cs, m_nom, N_nom, y, &gw, &el, true, false) : 1;
             if (fused < 0) {
                 rc = fused;
                 break;
@@ -676,14 +735,146 @@ struct Core {
             if (fused) {
                 if (nonlinear(c) && (rc = slr(cs, m_nom, N_nom, y, &gw)))
                     break;
-                if ((rc = felem(cs, g, y, &el, true, cov)))
+                if ((rc = felem(cs, g, y, &el, true, true)))
                     break;
             }
-            if ((rc = fscan(cs, &el, mf, Nf, scan_ws, true, cov)))
+            if ((rc = fscan(cs, &el, mf, Nf, scan_ws, true, true)))
                 break;
-            rc = sscan(cs, g, mf, Nf, m_nom, N_nom, scan_ws, cov);
+            rc = sscan(cs, g, mf, Nf, m_nom, N_nom, scan_ws, true);
         }
         return rc;
+    }
+
+    // Algorithm 3 in square-root form: the finest level runs Kalman steps
+    static int ipls(const Ctx &c, const pss_gamma *gin, const void *y, int n_iter, void *m_nom,
+                    void *N_nom, void *mf_out, void *Nf_out, void *ws)
+    {
+        if (c.p->form == PSS_FORM_COV)
+            return ipls_cov(c, gin, y, n_iter, m_nom, N_nom, mf_out, Nf_out, ws);
+        const ScanShape sh = step_shape(c);
+        Carver cv{static_cast<char *>(ws)};
+        pss_gamma gw = carve_gamma(cv, c.T_y);
+        // the space of the filter elements: smoother elements, then one
+        // marginal per sequence (felem - selem = marg numbers per step)
+        T *fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
+        T *mid = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
+        const auto w = carve_scan<FS>(cv, c, sh);
+        const SElemRef<T, NX> stash = selem_ref(fel, c.T_y);
+        const MargAos<T, NX> last{fel + (size_t)Sizes<NX>::selem * c.T_y};
+        // the smoother's upper levels take over the filter's space
+        ScanWs<SS> ws_s{};
+        for (int l = 0; l < sh.L; ++l) {
+            ws_s.tile_off[l] = w.tile_off[l];
+            ws_s.elem_off[l] = w.elem_off[l];
+            ws_s.agg[l] = w.agg[l];
+            ws_s.pre[l] = w.pre[l];
+            ws_s.tree[l] = w.tree[l];
+        }
+        int rc = launch_plan(c, sh, 0, w.tile_off, w.elem_off);
+        if (rc)
+            return rc;
+        const int64_t TS = (int64_t)sh.T[0] * sh.E[0];
+        pss_gamma gl = gw;
+        if (!nonlinear(c)) {
+            if (gin->stride == 0) {
+                gl = *gin;
+            } else {
+                hipLaunchKernelGGL((k_gamma_ilv<T, NX, NY>), dim3((unsigned)((c.T_y + 255) / 256)),
+                                   dim3(256), 0, c.s, c.p->y_off, c.B, c.T_y,
+                                   gamma_ref(gin, c.T_y), gamma_ref(&gw, c.T_y), TS, sh.E[0]);
+                if ((rc = hip_check(hipGetLastError(), "linearisation layout launch")))
+                    return rc;
+            }
+        }
+        const GammaRef<T, NX, NY> gam = gamma_ref(&gl, c.T_y);
+        const NomRef<T, NX> plain{marg_ref2(m_nom, N_nom, c.T_x), c.T_y, 0};
+        const NomRef<T, NX> inner{marg_ref(mid, c.T_x), c.T_y, 1};
+        // The last pass writes the caller's layout itself while the lines it
+        // fills piecemeal stay in the caches (each thread fills E consecutive
+        // states of every component); a longer one writes interleaved and a
+        // copy follows.  10^6 FP64 states: 0.32 ms in place, 0.12 + 0.07 ms with
+        // the copy; 4 * 10^5 FP32 states 0.083 against 0.031 + 0.020 ms.
+        const bool direct = (size_t)c.T_x * Sizes<NX>::marg * sizeof(T) <= kDirectBytes;
+        // FP32: the CT model's passes run in deviation coordinates relative
+        // to the nominal means (see Ctx), unless the caller takes the
+        // filtering marginals (those are absolute).  On the 10^6-step track
+        // this cut the late passes' mean error about 5x; FP64 loses nothing
+        // measurable in absolute coordinates and keeps them.
+        const bool dev = sizeof(T) == 4 && c.p->model == PSS_MODEL_CT_BEARINGS && !mf_out;
+        const MargRef<T, NX> filt = marg_ref2(mf_out, Nf_out, c.T_x);
+        for (int it = 0; it < n_iter; ++it) {
+            const bool fin = it + 1 == n_iter;
+            const NomRef<T, NX> in = it == 0 ? plain : inner, out = fin && direct ? plain : inner;
+            Ctx cs = c;
+            cs.dev_m = dev ? in.r.m : nullptr;
+            if (nonlinear(c) && (rc = step_lin(cs, in, y, &gw, sh)))
+                return rc;
+            NomRef<T, NX> rdev = in;
+            if (!dev)
+                rdev.r.m = nullptr;
+            MargRef<T, NX> fo = filt;
+            if (!fin)
+                fo.m = nullptr;
+            if ((rc = step_pass(cs, sh, w, ws_s, gam, y, in, rdev, out, stash, last, fo)))
+                return rc;
+        }
+        if (!direct && n_iter > 0) {
+            KTime kt(c.s, "nominal_plain", "", 0);
+            hipLaunchKernelGGL((k_nominal_plain<T, NX>), dim3((unsigned)((c.T_x + 255) / 256)),
+                               dim3(256), 0, c.s, c.p->y_off, c.B, c.T_y, c.T_x, inner.r, plain.r,
+                               TS, sh.E[0]);
+            rc = hip_check(hipGetLastError(), "nominal layout launch");
+        }
+        return rc;
+    }
+
+    // one filter and smoother pass over interleaved linearisation slots
+    static int step_pass(const Ctx &c, const ScanShape &sh, const ScanWs<FS> &w,
+                         const ScanWs<SS> &ws_s, const GammaRef<T, NX, NY> &gam, const void *y,
+                         const NomRef<T, NX> &nom, const NomRef<T, NX> &dev,
+                         const NomRef<T, NX> &out, const SElemRef<T, NX> &stash,
+                         const MargAos<T, NX> &last, const MargRef<T, NX> &filt)
+    {
+        const LevelGeom g = level_geom(c, sh, w, 0, 0);
+        const dim3 grid((unsigned)sh.ntiles[0]), block(sh.T[0]);
+        const StepPrior<T, NX> prior{cptr<T>(c.p->m0), cptr<T>(c.p->N0), cptr<T>(c.dev_m),
+                                     nom.r.ld};
+        const StartPre<T, NX> st{cptr<T>(c.p->m0), cptr<T>(c.p->N0)}, none{nullptr, nullptr};
+        auto no_top = [&]() -> int { return PSS_OK; }; // a flat level 0 is never the top
+        int rc = run_levels<FS, true>(
+            c, sh, w, 0, st, &felem_ref, 0,
+            [&]() -> int {
+                KTime kt(c.s, "step_fold", "", 0);
+                const auto agg = agg_of(sh, w, 1, &felem_ref);
+                using Agg = std::decay_t<decltype(agg)>;
+                hipLaunchKernelGGL((k_step_fold<T, NX, NY, Agg>), grid, block, 0, c.s, g, gam,
+                                   cptr<T>(y), c.T_y, prior, nom, agg, w.elem_off[1], sh.T[1],
+                                   agg_ilv<FS>(sh));
+                return hip_check(hipGetLastError(), "step fold launch");
+            },
+            no_top,
+            [&]() -> int {
+                KTime kt(c.s, "step_walk", "", 0);
+                const auto pre = pre_of(sh, w, 1);
+                const auto agg = agg_of(sh, ws_s, 1, &selem_ref);
+                using Pre = std::decay_t<decltype(pre)>;
+                using Agg = std::decay_t<decltype(agg)>;
+                hipLaunchKernelGGL((k_step_walk<T, NX, NY, Agg, Pre>), grid, block, 0, c.s, g,
+                                   gam, cptr<T>(y), c.T_y, prior, nom, pre, stash, agg, last,
+                                   filt, w.elem_off[1], sh.T[1], agg_ilv<SS>(sh));
+                return hip_check(hipGetLastError(), "step walk launch");
+            });
+        if (rc)
+            return rc;
+        return run_levels<SS, true>(
+            c, sh, ws_s, 0, none, &selem_ref, 0, no_top, no_top, [&]() -> int {
+                KTime kt(c.s, "step_smooth", "", 0);
+                const auto pre = pre_of(sh, ws_s, 1);
+                using Pre = std::decay_t<decltype(pre)>;
+                hipLaunchKernelGGL((k_step_smooth<T, NX, Pre>), grid, block, 0, c.s, g, stash,
+                                   pre, last, dev, out, w.elem_off[1]);
+                return hip_check(hipGetLastError(), "step smooth launch");
+            });
     }
 
     // linearisation (nonlinear models) and level-0 filter elements
@@ -1035,6 +1226,51 @@ int Core<T, NX, NY>::slr_felem(const Ctx &c, const void *m, const void *N, const
         }
     }
     return 1;
+}
+
+template <typename T, int NX, int NY>
+int Core<T, NX, NY>::step_lin(const Ctx &c, const NomRef<T, NX> &nom, const void *y,
+                              const pss_gamma *out, const ScanShape &sh)
+{
+    const dim3 grid((unsigned)((c.T_y + 255) / 256)), block(256);
+    const int lin = c.p->linearization, dev = c.dev_m ? 1 : 0;
+    const int64_t TS = (int64_t)sh.T[0] * sh.E[0];
+    auto run = [&](const auto &l) -> int {
+        using Lin = std::decay_t<decltype(l)>;
+        KTime kt(c.s, "slr", "", 0);
+        hipLaunchKernelGGL((k_step_lin<Lin>), grid, block, 0, c.s, c.p->y_off, c.B, c.T_y, l, nom,
+                           cptr<T>(y), gamma_ref(out, c.T_y), TS, sh.E[0], dev);
+        return hip_check(hipGetLastError(), "slr launch");
+    };
+    if constexpr (NX == 5 && NY == 2) {
+        if (c.p->model == PSS_MODEL_CT_BEARINGS) {
+            const CTParams<T> P = ct_params<T>(ct_host(c.p));
+            if (lin == PSS_LIN_CUBATURE)
+                return run(LinCT<T, false>{P});
+            if (lin == PSS_LIN_TAYLOR)
+                return run(LinCT<T, true>{P});
+            LinCTRule<T> l{P, {}};
+            if (!rule_spec(c.p, NX, l.R))
+                return PSS_EINVAL;
+            return run(l);
+        }
+    }
+    if constexpr (NX == 1 && NY == 1) {
+        if (c.p->model == PSS_MODEL_RICKER_POISSON) {
+            const RickerHost h = ricker_host(c.p);
+            LinRicker<T> l{};
+            l.P.loga = (T)h.loga;
+            l.P.b = (T)h.b;
+            l.P.sqQ = (T)h.sqQ;
+            l.taylor = lin == PSS_LIN_TAYLOR ? 1 : 0;
+            if (!l.taylor && !rule_spec(c.p, NX, l.R))
+                return PSS_EINVAL;
+            return run(l);
+        }
+    }
+    (void)y;
+    set_error("no linearisation is built for this model and dimension pair");
+    return PSS_EUNSUPPORTED;
 }
 
 template <typename T, int NX, int NY>

@@ -1,0 +1,627 @@
+// Finest level of the smoothing pass, built from Kalman steps.
+//
+// A thread owns E consecutive steps of one sequence and works on them one
+// after the other, from the linearisation itself:
+//   k_step_fold    the aggregate of its steps (a filter element of level 1):
+//                  the conditional filter started from a known state, its
+//                  transfer matrix A and the information (eta, Z) its
+//                  measurements hold about that state
+//   k_step_walk    from the filtering marginal before its first step (the scan
+//                  above): filters, writes the smoother element of every state
+//                  (Table 4) and folds them into the thread's smoother aggregate
+//   k_step_smooth  from the smoothing marginal after its last step: Table 5's
+//                  apply form, back to its first state
+// so no filter element is ever stored, and the filtering marginals only on
+// request.  A step costs about half the flops of building an element and
+// combining it (Lemma 1 and Table 3 hold for any split of the steps).  Between
+// two steps the factor N of a marginal is any square root of P, NX x NX and
+// dense: the next step's Tria([F N, S_L]) depends on its Gram matrix alone, so
+// the update's own Tria stops after its NY measurement rows.  A stored factor
+// is triangular as everywhere.
+//
+// The linearisation, the stash of smoother elements and the nominal between
+// passes are tile-interleaved (ilv): a wave's accesses are whole lines.
+//
+// Measured at 10^6 FP64 coordinated-turn steps, per pass (bound by their
+// bytes; a large copy reaches 4.9 TB/s): fold 0.163 ms for 0.50 GB, walk 0.197
+// ms for 0.86 GB, smooth 0.12 ms for 0.52 GB; they replace element build
+// (0.224), filter up and down (0.202, 0.139) and smoother up and down (0.334,
+// 0.191 ms).  Holding fold and walk to 256 registers (two waves a SIMD) gained
+// nothing: 0.161 and 0.221 ms.
+#pragma once
+
+#include "kernels.hpp"
+#include "scan_group.hpp"
+
+namespace pss {
+
+// marginals of every state: plain (state k of sequence b at y_off[b] + b + k)
+// or tile-interleaved (state k < n at the slot of step k, state n at T_y + b)
+template <typename T, int NX>
+struct NomRef {
+    MargRef<T, NX> r;
+    int64_t T_y;
+    int ilv;
+    PSS_INL int64_t slot(const int64_t *y_off, const TileInfo &ti, int64_t k) const
+    {
+        if (!ilv)
+            return ti.off + ti.b + k;
+        return k < ti.cnt ? ilv_slot(ti, k) : T_y + ti.b;
+    }
+};
+
+// stored slot of step k of sequence b for tiles of TS = threads x E steps
+PSS_INL int64_t step_slot(const int64_t *y_off, int b, int64_t k, int64_t TS, int E)
+{
+    const int64_t cnt = y_off[b + 1] - y_off[b], start = (k / TS) * TS;
+    const int tcnt = (int)(cnt - start < TS ? cnt - start : TS);
+    return y_off[b] + start + ilv((int)(k - start), tcnt, E);
+}
+// its inverse: the step stored at slot i
+PSS_INL int64_t slot_step(const int64_t *y_off, int b, int64_t i, int64_t TS, int E)
+{
+    const int64_t q = i - y_off[b], cnt = y_off[b + 1] - y_off[b], start = (q / TS) * TS;
+    const int tcnt = (int)(cnt - start < TS ? cnt - start : TS);
+    return start + ilv_inv((int)(q - start), tcnt, E);
+}
+
+// place of thread v's aggregate among the level-1 elements of its sequence
+PSS_INL int64_t agg_slot(const int64_t *next_off, int b, int64_t v, int nT, int nE)
+{
+    const int64_t off = next_off[b], cnt = next_off[b + 1] - off;
+    const int64_t TS = (int64_t)nT * nE, start = (v / TS) * TS;
+    const int tcnt = (int)((cnt - start) < TS ? (cnt - start) : TS);
+    return off + start + ilv((int)(v - start), tcnt, nE);
+}
+
+// measurement half of a step: Q = [[H L, S_O], [L, 0]] with L lower, its NY
+// upper rows reduced.  Y = Q[0..NY)[0..NY), P21 = lower rows' first NY columns,
+// a square root of the updated covariance in the NX columns after them.
+template <typename T, int NX, int NY, int R, int C>
+PSS_INL void step_update(const T (&H)[NY][NX], const T (&L)[R][C], const T (&SO)[NY][NY],
+                         T (&Q)[NY + NX][NX + NY])
+{
+#pragma unroll
+    for (int a = 0; a < NY; ++a) {
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            T s = H[a][j] * L[j][j];
+#pragma unroll
+            for (int t = j + 1; t < NX; ++t)
+                s = pfma(H[a][t], L[t][j], s);
+            Q[a][j] = s;
+        }
+#pragma unroll
+        for (int j = 0; j < NY; ++j)
+            Q[a][NX + j] = j <= a ? SO[a][j] : T(0);
+    }
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            Q[NY + i][j] = j <= i ? L[i][j] : T(0);
+#pragma unroll
+        for (int j = 0; j < NY; ++j)
+            Q[NY + i][NX + j] = T(0);
+    }
+    lq_rows<NY, NX>(Q);
+}
+
+// x <- Y^{-1} x in place for NC columns (Y the reduced rows of Q)
+template <typename T, int NY, int NC, int R, int C>
+PSS_INL void step_solve(const T (&Q)[R][C], T (&x)[NY][NC])
+{
+#pragma unroll
+    for (int a = 0; a < NY; ++a) {
+        const T inv = prcp(Q[a][a]);
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            T s = x[a][j];
+#pragma unroll
+            for (int t = 0; t < a; ++t)
+                s = pfma(-Q[a][t], x[t][j], s);
+            x[a][j] = s * inv;
+        }
+    }
+}
+
+// where the filter starts: the prior (m0, N0), its mean relative to r_0 in
+// deviation coordinates
+template <typename T, int NX>
+struct StepPrior {
+    const T *m0, *N0;
+    const T *dev_m; // nominal means, component i of state 0 of sequence b at
+    int64_t dev_ld; // dev_m[i * dev_ld + s0]; null: absolute coordinates
+    PSS_INL T mean(int i, int64_t s0) const
+    {
+        using W = typename BranchPrec<T>::type;
+        return dev_m ? T(W(m0[i]) - W(dev_m[i * dev_ld + s0])) : m0[i];
+    }
+};
+
+template <typename T, int NX, int NY, class AggRef>
+__global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, NY> gam,
+                                                   const T *y, int64_t T_y,
+                                                   StepPrior<T, NX> prior, NomRef<T, NX> nom,
+                                                   AggRef agg, const int64_t *next_off, int nT,
+                                                   int nE)
+{
+    const TileInfo ti = tile_info(g);
+    if ((int)threadIdx.x >= ti.nvalid)
+        return;
+    const int64_t p0 = ti.start + (int64_t)threadIdx.x * ti.E;
+    int64_t pe = p0 + ti.E;
+    if (pe > ti.start + ti.tcnt)
+        pe = ti.start + ti.tcnt;
+    FElem<T, NX> e; // U dense between steps
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        e.b[i] = e.eta[i] = T(0);
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            e.A[i][j] = (i == j) ? T(1) : T(0);
+            e.U[i][j] = e.Z[i][j] = T(0);
+        }
+    }
+    if (p0 == 0) { // the sequence's first thread: a true prefix (A = 0)
+        const int64_t s0 = nom.slot(g.y_off, ti, 0);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            e.b[i] = prior.mean(i, s0);
+            e.A[i][i] = T(0);
+#pragma unroll
+            for (int j = 0; j <= i; ++j)
+                e.U[i][j] = prior.N0[tri_idx(i, j)];
+        }
+    }
+    for (int64_t p = p0; p < pe; ++p) {
+        const int64_t u = gam.stride ? ilv_slot(ti, p) : 0;
+        T M[NX][2 * NX];
+        {
+            T F[NX][NX];
+#pragma unroll
+            for (int i = 0; i < NX; ++i)
+#pragma unroll
+                for (int j = 0; j < NX; ++j)
+                    F[i][j] = gam.F[(i * NX + j) * gam.ld + u];
+            T FA[NX][NX], Fb[NX];
+            mm(F, e.A, FA);
+            mv(F, e.b, Fb);
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                e.b[i] = Fb[i] + gam.c[i * gam.ld + u];
+#pragma unroll
+                for (int j = 0; j < NX; ++j)
+                    e.A[i][j] = FA[i][j];
+            }
+#pragma unroll
+            for (int i = 0; i < NX; ++i)
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    T s = F[i][0] * e.U[0][j];
+#pragma unroll
+                    for (int t = 1; t < NX; ++t)
+                        s = pfma(F[i][t], e.U[t][j], s);
+                    M[i][j] = s;
+                    M[i][NX + j] = j <= i ? gam.SL[tri_idx(i, j <= i ? j : i) * gam.ld + u] : T(0);
+                }
+        }
+        lq_rows<NX, NX>(M);
+        T H[NY][NX], d[NY], SO[NY][NY];
+        gam.load_obs(gam.stride ? u : 0, H, d, SO);
+        T Q[NY + NX][NX + NY];
+        step_update(H, M, SO, Q);
+        // G = Y^{-1} H A, w = Y^{-1} (y - H b - d)
+        T G[NY][NX], w[NY][1];
+        mm(H, e.A, G);
+#pragma unroll
+        for (int a = 0; a < NY; ++a) {
+            T s = y[a * T_y + ti.off + p] - d[a];
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                s = pfma(-H[a][j], e.b[j], s);
+            w[a][0] = s;
+        }
+        step_solve<T, NY, NX>(Q, G);
+        step_solve<T, NY, 1>(Q, w);
+        T Gt[NX][NY];
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+#pragma unroll
+            for (int a = 0; a < NY; ++a) {
+                Gt[i][a] = G[a][i];
+                e.eta[i] = pfma(G[a][i], w[a][0], e.eta[i]);
+                e.b[i] = pfma(Q[NY + i][a], w[a][0], e.b[i]);
+            }
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                T s = e.A[i][j];
+#pragma unroll
+                for (int a = 0; a < NY; ++a)
+                    s = pfma(-Q[NY + i][a], G[a][j], s);
+                e.A[i][j] = s;
+                e.U[i][j] = Q[NY + i][NY + j];
+            }
+        T Zn[NX][NX];
+        tria_cols_lower(Gt, e.Z, Zn);
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j)
+                e.Z[i][j] = Zn[i][j];
+    }
+    {
+        T Un[NX][NX];
+        tria_rect(e.U, Un);
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j)
+                e.U[i][j] = Un[i][j];
+    }
+    const int64_t v = ti.start / ti.E + threadIdx.x;
+    felem_copy<T, NX>(FRegV<T, NX>{&e}, view_of(agg, agg_slot(next_off, ti.b, v, nT, nE)));
+}
+
+// filtering marginals on request: state k of sequence b at plain slot
+// y_off[b] + b + k of (m, N); m null: not taken
+template <typename T, int NX, int NY, class AggRef, class PreRef>
+__global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, NY> gam,
+                                                   const T *y, int64_t T_y,
+                                                   StepPrior<T, NX> prior, NomRef<T, NX> nom,
+                                                   PreRef pre, SElemRef<T, NX> stash,
+                                                   AggRef agg, MargAos<T, NX> last,
+                                                   MargRef<T, NX> filt, const int64_t *next_off,
+                                                   int nT, int nE)
+{
+    const TileInfo ti = tile_info(g);
+    if ((int)threadIdx.x >= ti.nvalid)
+        return;
+    const int64_t p0 = ti.start + (int64_t)threadIdx.x * ti.E;
+    int64_t pe = p0 + ti.E;
+    if (pe > ti.start + ti.tcnt)
+        pe = ti.start + ti.tcnt;
+    const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
+    T m[NX], N[NX][NX]; // N dense between steps
+    {
+        Marg<T, NX> f;
+        if (p0 == 0) {
+            const int64_t s0 = nom.slot(g.y_off, ti, 0);
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                f.m[i] = prior.mean(i, s0);
+#pragma unroll
+                for (int j = 0; j <= i; ++j)
+                    f.N[i][j] = prior.N0[tri_idx(i, j)];
+            }
+            if (filt.m)
+                filt.store(ti.off + ti.b, f);
+        } else {
+            pre.load(next_off[ti.b] + v, f);
+        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            m[i] = f.m[i];
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                N[i][j] = j <= i ? f.N[i][j] : T(0);
+        }
+    }
+    SElem<T, NX> a; // the thread's smoother aggregate
+    for (int64_t p = p0; p < pe; ++p) {
+        const int64_t u = ilv_slot(ti, p), ug = gam.stride ? u : 0;
+        // [[F N, S_L], [N, 0]], upper rows reduced: N^- = M11, E = M21 M11^{-1},
+        // D D^T = M22 M22^T (Table 4)
+        T M[2 * NX][2 * NX], mp[NX];
+        {
+            T F[NX][NX];
+#pragma unroll
+            for (int i = 0; i < NX; ++i)
+#pragma unroll
+                for (int j = 0; j < NX; ++j)
+                    F[i][j] = gam.F[(i * NX + j) * gam.ld + ug];
+            mv(F, m, mp);
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                mp[i] += gam.c[i * gam.ld + ug];
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    T s = F[i][0] * N[0][j];
+#pragma unroll
+                    for (int t = 1; t < NX; ++t)
+                        s = pfma(F[i][t], N[t][j], s);
+                    M[i][j] = s;
+                    M[i][NX + j] =
+                        j <= i ? gam.SL[tri_idx(i, j <= i ? j : i) * gam.ld + ug] : T(0);
+                    M[NX + i][j] = N[i][j];
+                    M[NX + i][NX + j] = T(0);
+                }
+            }
+        }
+        lq_rows<NX, NX>(M);
+        {
+            SElem<T, NX> e;
+            {
+                T P11[NX][NX], P21[NX][NX], P22[NX][NX];
+#pragma unroll
+                for (int i = 0; i < NX; ++i)
+#pragma unroll
+                    for (int j = 0; j < NX; ++j) {
+                        P11[i][j] = M[i][j];
+                        P21[i][j] = M[NX + i][j];
+                        P22[i][j] = M[NX + i][NX + j];
+                    }
+                rsolve_lower(P21, P11, e.E);
+                tria_rect(P22, e.D);
+            }
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                T s = m[i];
+#pragma unroll
+                for (int j = 0; j < NX; ++j)
+                    s = pfma(-e.E[i][j], mp[j], s);
+                e.g[i] = s;
+            }
+            stash.store(u, e);
+            if (p == p0)
+                a = e;
+            else
+                smoother_combine_v<T, NX>(SRegV<T, NX>{&a}, SRegV<T, NX>{&e}, SRegV<T, NX>{&a});
+        }
+        T H[NY][NX], d[NY], SO[NY][NY];
+        gam.load_obs(ug, H, d, SO);
+        T Q[NY + NX][NX + NY], w[NY][1];
+        step_update(H, M, SO, Q);
+#pragma unroll
+        for (int q = 0; q < NY; ++q) {
+            T s = y[q * T_y + ti.off + p] - d[q];
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                s = pfma(-H[q][j], mp[j], s);
+            w[q][0] = s;
+        }
+        step_solve<T, NY, 1>(Q, w);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            m[i] = mp[i];
+#pragma unroll
+            for (int q = 0; q < NY; ++q)
+                m[i] = pfma(Q[NY + i][q], w[q][0], m[i]);
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                N[i][j] = Q[NY + i][NY + j];
+        }
+        if (filt.m) {
+            Marg<T, NX> f;
+            tria_rect(N, f.N);
+#pragma unroll
+            for (int i = 0; i < NX; ++i)
+                f.m[i] = m[i];
+            filt.store(ti.off + ti.b + p + 1, f);
+        }
+    }
+    if (v == cnt1 - 1) {
+        // the sequence's end: the filtering marginal of state n is the
+        // smoother's start (its element {0, m, N}), folded in here
+        Marg<T, NX> f, o;
+        tria_rect(N, f.N);
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+            f.m[i] = m[i];
+        T *q = last.p + (int64_t)ti.b * Sizes<NX>::marg;
+        visit(f, [&](int c, T &x) { q[c] = x; });
+        smoother_apply(a, f, o);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            a.g[i] = o.m[i];
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                a.E[i][j] = T(0);
+                if (j <= i)
+                    a.D[i][j] = o.N[i][j];
+            }
+        }
+    }
+    // the smoother scans backwards: its element cnt1 - 1 - v
+    selem_copy<T, NX>(SRegV<T, NX>{&a},
+                      view_of(agg, agg_slot(next_off, ti.b, cnt1 - 1 - v, nT, nE)));
+}
+
+template <typename T, int NX, class PreRef>
+__global__ __launch_bounds__(256) void k_step_smooth(LevelGeom g, SElemRef<T, NX> stash,
+                                                     PreRef pre, MargAos<T, NX> last,
+                                                     NomRef<T, NX> dev, NomRef<T, NX> out,
+                                                     const int64_t *next_off)
+{
+    const TileInfo ti = tile_info(g);
+    if ((int)threadIdx.x >= ti.nvalid)
+        return;
+    const int64_t p0 = ti.start + (int64_t)threadIdx.x * ti.E;
+    int64_t pe = p0 + ti.E;
+    if (pe > ti.start + ti.tcnt)
+        pe = ti.start + ti.tcnt;
+    const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
+    Marg<T, NX> s;
+    // deviation coordinates: the stored mean is r_k plus the deviation
+    auto put = [&](int64_t k, const Marg<T, NX> &x) {
+        const int64_t at = out.slot(g.y_off, ti, k);
+        Marg<T, NX> o = x;
+        if (dev.r.m) {
+            const int64_t rk = dev.slot(g.y_off, ti, k);
+#pragma unroll
+            for (int i = 0; i < NX; ++i)
+                o.m[i] += dev.r.m[i * dev.r.ld + rk];
+        }
+        out.r.store(at, o);
+    };
+    if (v == cnt1 - 1) {
+        last.load(ti.b, s);
+        put(ti.cnt, s);
+    } else {
+        pre.load(next_off[ti.b] + cnt1 - 1 - v, s);
+    }
+    for (int64_t p = pe - 1; p >= p0; --p) {
+        const auto e = view_of(stash, ilv_slot(ti, p));
+        Marg<T, NX> o;
+        smoother_apply_v<T, NX>(e, s, o);
+        s = o;
+        put(p, s);
+    }
+}
+
+// interleaved marginals to plain ones, one thread per state
+template <typename T, int NX>
+__global__ __launch_bounds__(256) void k_nominal_plain(const int64_t *y_off, int B, int64_t T_y,
+                                                       int64_t T_x, MargRef<T, NX> src,
+                                                       MargRef<T, NX> dst, int64_t TS, int E)
+{
+    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= T_x)
+        return;
+    const int b = find_seq(y_off, B, s, 1);
+    const int64_t k = s - y_off[b] - b, n = y_off[b + 1] - y_off[b];
+    Marg<T, NX> x;
+    src.load(k < n ? step_slot(y_off, b, k, TS, E) : T_y + b, x);
+    dst.store(s, x);
+}
+
+// a caller's per-step linearisation into interleaved slots, one thread per slot
+template <typename T, int NX, int NY>
+__global__ __launch_bounds__(256) void k_gamma_ilv(const int64_t *y_off, int B, int64_t T_y,
+                                                   GammaRef<T, NX, NY> src,
+                                                   GammaRef<T, NX, NY> dst, int64_t TS, int E)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= T_y)
+        return;
+    const int b = find_seq(y_off, B, i, 0);
+    const int64_t t = y_off[b] + slot_step(y_off, b, i, TS, E);
+    T F[NX][NX], c[NX], S[NX][NX], H[NY][NX], d[NY], O[NY][NY];
+    src.load_trans(t, F, c, S);
+    src.load_obs(t, H, d, O);
+    dst.store_trans(i, F, c, S);
+    dst.store_obs(i, H, d, O);
+}
+
+// Linearisation of every step into its interleaved slot, one thread per stored
+// slot: the transition at state k, the measurement at state k + 1.  A block
+// covers whole tiles, so the strided reads of neighbouring states meet in one
+// cache.  Lin: trans(marginal, F, c, S_L) and obs(marginal, y, H, d, S_O).
+template <class Lin>
+__global__ __launch_bounds__(256) void k_step_lin(const int64_t *y_off, int B, int64_t T_y,
+                                                  Lin lin, NomRef<typename Lin::T, Lin::NX> nom,
+                                                  const typename Lin::T *y,
+                                                  GammaRef<typename Lin::T, Lin::NX, Lin::NY> out,
+                                                  int64_t TS, int E, int dev)
+{
+    using T = typename Lin::T;
+    constexpr int NX = Lin::NX, NY = Lin::NY;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= T_y)
+        return;
+    const int b = find_seq(y_off, B, i, 0);
+    const int64_t n = y_off[b + 1] - y_off[b], k = slot_step(y_off, b, i, TS, E);
+    auto at = [&](int64_t s) -> int64_t {
+        if (!nom.ilv)
+            return y_off[b] + b + s;
+        return s < n ? step_slot(y_off, b, s, TS, E) : T_y + b;
+    };
+    const int64_t s0 = at(k), s1 = at(k + 1);
+    T rk[NX];
+    {
+        Marg<T, NX> mg;
+        nom.r.load(s0, mg);
+        T F[NX][NX], c[NX], S[NX][NX];
+        lin.trans(mg, F, c, S);
+        if (dev) {
+#pragma unroll
+            for (int q = 0; q < NX; ++q)
+                rk[q] = nom.r.m[q * nom.r.ld + s1];
+            dev_trans_offset(F, mg.m, rk, c);
+        }
+        out.store_trans(i, F, c, S);
+    }
+    {
+        Marg<T, NX> mg;
+        nom.r.load(s1, mg);
+        T yy[NY], H[NY][NX], d[NY], S[NY][NY];
+#pragma unroll
+        for (int a = 0; a < NY; ++a)
+            yy[a] = y[a * T_y + y_off[b] + k];
+        lin.obs(mg, yy, H, d, S);
+        if (dev)
+            dev_obs_offset(H, mg.m, d);
+        out.store_obs(i, H, d, S);
+    }
+}
+
+template <typename T_, bool TAYLOR>
+struct LinCT {
+    using T = T_;
+    static constexpr int NX = 5, NY = 2;
+    CTParams<T> P;
+    PSS_INL void trans(const Marg<T, 5> &mg, T (&F)[5][5], T (&c)[5], T (&S)[5][5]) const
+    {
+        if constexpr (TAYLOR)
+            ct_taylor_transition(P, mg, F, c, S);
+        else
+            ct_slr_transition(P, mg, F, c, S);
+    }
+    PSS_INL void obs(const Marg<T, 5> &mg, const T (&y)[2], T (&H)[2][5], T (&d)[2],
+                     T (&S)[2][2]) const
+    {
+        if constexpr (TAYLOR)
+            ct_taylor_bearings(P, mg, y, H, d, S);
+        else
+            ct_slr_bearings(P, mg, y, H, d, S);
+    }
+};
+
+template <typename T_>
+struct LinCTRule {
+    using T = T_;
+    static constexpr int NX = 5, NY = 2;
+    CTParams<T> P;
+    RuleSpec<T> R;
+    PSS_INL void trans(const Marg<T, 5> &mg, T (&F)[5][5], T (&c)[5], T (&S)[5][5]) const
+    {
+        ct_rule_transition(R, P, mg, F, c, S);
+    }
+    PSS_INL void obs(const Marg<T, 5> &mg, const T (&y)[2], T (&H)[2][5], T (&d)[2],
+                     T (&S)[2][2]) const
+    {
+        ct_rule_bearings(R, P, mg, y, H, d, S);
+    }
+};
+
+template <typename T_>
+struct LinRicker {
+    using T = T_;
+    static constexpr int NX = 1, NY = 1;
+    RickerParams<T> P;
+    RuleSpec<T> R;
+    int taylor;
+    PSS_INL void trans(const Marg<T, 1> &mg, T (&F)[1][1], T (&c)[1], T (&S)[1][1]) const
+    {
+        if (taylor) {
+            T H[1][1], d[1], O[1][1];
+            ricker_taylor(P, mg, mg, true, false, F, c, S, H, d, O);
+        } else {
+            ricker_rule_transition(R, P, mg, F, c, S);
+        }
+    }
+    PSS_INL void obs(const Marg<T, 1> &mg, const T (&y)[1], T (&H)[1][1], T (&d)[1],
+                     T (&S)[1][1]) const
+    {
+        if (taylor) {
+            T F[1][1], c[1], O[1][1];
+            ricker_taylor(P, mg, mg, false, true, F, c, O, H, d, S);
+        } else {
+            ricker_rule_poisson(R, P, mg, H, d, S);
+        }
+    }
+};
+
+} // namespace pss
