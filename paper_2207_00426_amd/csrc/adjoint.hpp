@@ -1,13 +1,18 @@
 // Adjoint (reverse-mode) pass of the square-root filter's pseudo-log-
 // likelihood: the VJP of the filter scan as a reverse associative scan of
-// affine cotangent maps (device_adj.hpp), its finest level built from the
-// filtering marginals and the linearisation, and the per-step VJP with
-// respect to the linearisation Gamma_k (Section 5.2, eq. gradient, at a
-// frozen nominal).
+// affine cotangent maps (device_adj.hpp) and the per-step VJP with respect to
+// the linearisation Gamma_k (Section 5.2, eq. gradient, at a frozen nominal).
+// Its finest level works on the tiles of steps.hpp, a thread on E consecutive
+// steps:
+//   k_filter_walk  filters from the marginal before the thread's first step;
+//                  writes the log-likelihood terms, the filtering marginals,
+//                  and the aggregate of its cotangent maps, each on request
+//   k_adj_down     from the cotangent of the state after its last step back to
+//                  its first: every step's cotangents and the prior's
 #pragma once
 
 #include "device_adj.hpp"
-#include "kernels.hpp"
+#include "steps.hpp"
 
 namespace pss {
 
@@ -47,6 +52,22 @@ struct AdjScan {
     }
 };
 
+template <typename T, int NX>
+struct GroupOp<AdjScan<T, NX>> {
+    static constexpr bool value = NX >= 2;
+    using Ref = SAosRef<T, NX>;
+    static __device__ __forceinline__ void combine(const T *a, const T *b, T *o,
+                                                   const grp::Lane<NX> &ln)
+    {
+        grp::adj_combine<T, NX>(b, a, o, ln);
+    }
+    static __device__ __forceinline__ void apply(const T *p, const T *a, T *o,
+                                                 const grp::Lane<NX> &ln)
+    {
+        grp::adj_apply<T, NX>(a, p, o, ln);
+    }
+};
+
 // theta contraction of the coordinated-turn model: dl/dtheta_j =
 // sum_k tr(Lam_bar_k dQ/dtheta_j) + tr(Om_bar_k dR/dtheta_j) with
 // dQ/dlog q1 = q1 Qv, dQ/dlog q2 = q2 Qw, dR/dlog sigma = 2 sigma^2 I.
@@ -62,7 +83,7 @@ template <typename T, int NX, int NY>
 struct ThetaOut {
     static constexpr bool kGamma = false;
     AdjTheta<T, NX> th;
-    double *terms;
+    double *terms; // at the steps' interleaved slots
     int64_t T_y;
 };
 
@@ -74,54 +95,369 @@ struct GammaOut {
     static constexpr bool kGamma = true;
     GammaRef<T, NX, NY> bar; // stride 1, ld = T_y
     const double *w;         // [B] or null (ones)
+    int ilv;                 // at interleaved slots instead of plain ones
 };
 
-// the finest level of the adjoint scan: element p of sequence b is the map
-// of step k = n - p, built from the filtering marginal of state k - 1 and
-// Gamma at step slot y_off[b] + k - 1.  down_apply also forms the step's
-// cotangents with the suffix lambda_k.
-template <typename T, int NX, int NY, class Out>
-struct AdjSrc {
-    static constexpr bool lazy_up = false, lazy_down = false, fused_down = true;
-    static constexpr int leaf_nz = 0;
-    GammaRef<T, NX, NY> gam;
-    MargRef<T, NX> filt; // ld = T_x
-    const T *y;
-    int64_t T_y;
-    Out out;
+// cotangents of one step, given the cotangent lam of its filtering marginal
+// and the step's quantities q, Np = N^-, P22 P22^T = P_k, mp = m^-; t: the
+// step's slot in the output
+template <typename T, int NX, int NY>
+PSS_INL void adj_emit(const ThetaOut<T, NX, NY> &out, int b, int64_t t, const T (&F)[NX][NX],
+                      const T (&SL)[NX][NX], const T (&H)[NY][NX], const T (&SO)[NY][NY],
+                      const Marg<T, NX> &f, const StepQ<T, NX, NY> &q, const T (&Np)[NX][NX],
+                      const T (&P22)[NX][NX], const T (&mp)[NX], const Marg<T, NX> &lam)
+{
+    T Lb[NX][NX], Ob[NY][NY], cb[NX], db[NY];
+    adj_gram_bars(H, q, lam, Lb, Ob, cb, db);
+    double g1 = 0.0, g2 = 0.0, g3 = 0.0;
+#pragma unroll
+    for (int i = 0; i < NX; ++i)
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            g1 += (double)(Lb[i][j] * out.th.dQ1[i][j]);
+            g2 += (double)(Lb[i][j] * out.th.dQ2[i][j]);
+        }
+#pragma unroll
+    for (int a = 0; a < NY; ++a)
+        g3 += (double)(Ob[a][a] * out.th.dR);
+    out.terms[t] = g1;
+    out.terms[out.T_y + t] = g2;
+    out.terms[2 * out.T_y + t] = g3;
+}
 
-    PSS_INL void load(const TileInfo &ti, int64_t p, int64_t &t, T (&F)[NX][NX], T (&c)[NX],
-                      T (&SL)[NX][NX], T (&H)[NY][NX], T (&d)[NY], T (&SO)[NY][NY],
-                      T (&yy)[NY], Marg<T, NX> &f) const
+template <typename T, int NX, int NY>
+PSS_INL void adj_emit(const GammaOut<T, NX, NY> &out, int b, int64_t t, const T (&F)[NX][NX],
+                      const T (&SL)[NX][NX], const T (&H)[NY][NX], const T (&SO)[NY][NY],
+                      const Marg<T, NX> &f, const StepQ<T, NX, NY> &q, const T (&Np)[NX][NX],
+                      const T (&P22)[NX][NX], const T (&mp)[NX], const Marg<T, NX> &lam)
+{
+    T Lb[NX][NX], Ob[NY][NY], cb[NX], db[NY];
+    adj_gram_bars(H, q, lam, Lb, Ob, cb, db);
+    const T w = out.w ? (T)out.w[b] : T(1);
+    // Sl = (W v v^T W - W) / 2
+    T Sl[NY][NY];
+#pragma unroll
+    for (int a = 0; a < NY; ++a)
+#pragma unroll
+        for (int b = 0; b <= a; ++b) {
+            T s = T(0);
+#pragma unroll
+            for (int u = a; u < NY; ++u)
+                s = pfma(q.Yi[u][a], q.Yi[u][b], s);
+            Sl[a][b] = Sl[b][a] = T(0.5) * (q.Wv[a] * q.Wv[b] - s);
+        }
+    // factor cotangents of S_L and S_O: lower triangles of 2 G_bar S
+    T SLb[NX][NX], SOb[NY][NY];
+    mm_lower(Lb, SL, SLb);
+    mm_lower(Ob, SO, SOb);
+    // F_bar = c_bar m^T + 2 Lam_bar F N N^T
+    T Fb[NX][NX];
     {
-        t = ti.off + ti.cnt - 1 - p; // step slot of step k = n - p
-        gam.load_trans(t, F, c, SL);
-        gam.load_obs(t, H, d, SO);
+        T FN[NX][NX], X[NX][NX];
+        mm_lower(F, f.N, FN);
+        mm(Lb, FN, X);
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                T s = cb[i] * f.m[j];
+#pragma unroll
+                for (int u = 0; u <= j; ++u)
+                    s = pfma(T(2) * X[i][u], f.N[j][u], s);
+                Fb[i][j] = s;
+            }
+    }
+    // H_bar = 2 Sl H P^- + W v (m^- + P_k m_bar)^T - (K^T m_bar) m_k^T
+    //         - 2 K^T P_bar P_k,  P^- = Np Np^T, P_k = P22 P22^T,
+    //         m_k = m^- + K v with v = Y w
+    T Hb[NY][NX];
+    {
+        T Pm[NX][NX], Pk[NX][NX], Pb[NX][NX], kb[NY], mk[NX], pm[NX];
+        sym_from_lower(Pm, [&](int i, int j) {
+            T s = T(0);
+            for (int u = 0; u <= j; ++u)
+                s = pfma(Np[i][u], Np[j][u], s);
+            return s;
+        });
+        sym_from_lower(Pk, [&](int i, int j) {
+            T s = T(0);
+            for (int u = 0; u < NX; ++u)
+                s = pfma(P22[i][u], P22[j][u], s);
+            return s;
+        });
+        sym_from_lower(Pb, [&](int i, int j) { return lam.N[i][j]; });
+        mtv(q.K, lam.m, kb);
+        // K v = Psi21 w (K = Psi21 Y^{-1}) -- recovered as K (Y w)
+        T v[NY];
+#pragma unroll
+        for (int a = 0; a < NY; ++a) {
+            // Y = Yi^{-1}: solve Yi v = w
+            T s = q.w[a];
+#pragma unroll
+            for (int u = 0; u < a; ++u)
+                s = pfma(-q.Yi[a][u], v[u], s);
+            v[a] = s * prcp(q.Yi[a][a]);
+        }
+        mv(Pk, lam.m, pm);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            T s = mp[i];
+#pragma unroll
+            for (int a = 0; a < NY; ++a)
+                s = pfma(q.K[i][a], v[a], s);
+            mk[i] = s;
+        }
+        T SH[NY][NX], KP[NY][NX];
+        mm(Sl, H, SH);
 #pragma unroll
         for (int a = 0; a < NY; ++a)
-            yy[a] = y[a * T_y + t];
-        filt.load(t + ti.b, f); // state k - 1
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                T s = T(0);
+#pragma unroll
+                for (int u = 0; u < NX; ++u)
+                    s = pfma(q.K[u][a], Pb[u][j], s);
+                KP[a][j] = s;
+            }
+#pragma unroll
+        for (int a = 0; a < NY; ++a)
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                T s = q.Wv[a] * (mp[j] + pm[j]) - kb[a] * mk[j];
+#pragma unroll
+                for (int u = 0; u < NX; ++u) {
+                    s = pfma(T(2) * SH[a][u], Pm[u][j], s);
+                    s = pfma(T(-2) * KP[a][u], Pk[u][j], s);
+                }
+                Hb[a][j] = s;
+            }
     }
-
-    PSS_INL void up(const TileInfo &ti, int64_t p, SElem<T, NX> &e) const
-    {
-        int64_t t;
-        T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
-        Marg<T, NX> f;
-        load(ti, p, t, F, c, SL, H, d, SO, yy, f);
-        StepQ<T, NX, NY> q;
-        T Np[NX][NX], P22[NX][NX], mp[NX];
-        adj_step(F, c, SL, H, d, SO, yy, f, q, Np, P22, mp);
-        adj_element(F, q, e);
+    // scale by the sequence's cotangent and store
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        cb[i] *= w;
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            Fb[i][j] *= w;
+            SLb[i][j] *= T(2) * w;
+        }
     }
+#pragma unroll
+    for (int a = 0; a < NY; ++a) {
+        db[a] *= w;
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            Hb[a][j] *= w;
+#pragma unroll
+        for (int j = 0; j < NY; ++j)
+            SOb[a][j] *= T(2) * w;
+    }
+    out.bar.store_trans(t, Fb, cb, SLb);
+    out.bar.store_obs(t, Hb, db, SOb);
+}
 
-    PSS_INL void down_apply(const TileInfo &ti, int64_t p, const Marg<T, NX> &lam,
-                            Marg<T, NX> &o) const
+// cotangent of the prior (m0, P0) from lambda_0, per sequence: m0_bar [NX][B],
+// N0_bar [P][B] = lower triangle of 2 P0_bar N0, scaled by w_b; m0_bar null:
+// not wanted
+template <typename T, int NX>
+struct AdjPrior {
+    T *m0_bar;
+    T *N0_bar;
+    const T *N0; // packed prior factor
+    const double *w;
+    int B;
+    PSS_INL void put(int b, const Marg<T, NX> &lam) const
     {
-        int64_t t;
+        if (!m0_bar)
+            return;
+        const T s = w ? (T)w[b] : T(1);
+        T Pb[NX][NX], L[NX][NX];
+        sym_from_lower(Pb, [&](int i, int j) { return lam.N[i][j]; });
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                L[i][j] = (j <= i) ? N0[tri_idx(i, j)] : T(0);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            m0_bar[(int64_t)i * B + b] = s * lam.m[i];
+#pragma unroll
+            for (int j = 0; j <= i; ++j) {
+                T a = T(0);
+#pragma unroll
+                for (int u = j; u < NX; ++u)
+                    a = pfma(Pb[i][u], L[u][j], a);
+                N0_bar[(int64_t)tri_idx(i, j) * B + b] = T(2) * s * a;
+            }
+        }
+    }
+};
+
+// The thread's start is its level-1 prefix (pre), or with `have` the stored
+// marginal of its first state.  marg (m null: not written) receives the
+// filtering marginal of state k at the interleaved slot of step k + 1; ell
+// (nullable) the log-likelihood terms at the interleaved slots.  ADJ: the maps
+// T_k folded into an element of the adjoint scan's level 1 (scanned backwards).
+template <typename T, int NX, int NY, bool ADJ, class AggRef, class PreRef>
+__global__ __launch_bounds__(256) void k_filter_walk(LevelGeom g, GammaRef<T, NX, NY> gam,
+                                                     const T *y, int64_t T_y,
+                                                     StepPrior<T, NX> prior, PreRef pre,
+                                                     MargRef<T, NX> have, MargRef<T, NX> marg,
+                                                     double *ell, AggRef agg,
+                                                     const int64_t *next_off, int nT, int nE)
+{
+    const TileInfo ti = tile_info(g);
+    if ((int)threadIdx.x >= ti.nvalid)
+        return;
+    const int64_t p0 = ti.start + (int64_t)threadIdx.x * ti.E;
+    int64_t pe = p0 + ti.E;
+    if (pe > ti.start + ti.tcnt)
+        pe = ti.start + ti.tcnt;
+    const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
+    Marg<T, NX> f;
+    if (p0 == 0) {
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            f.m[i] = prior.m0[i];
+#pragma unroll
+            for (int j = 0; j <= i; ++j)
+                f.N[i][j] = prior.N0[tri_idx(i, j)];
+        }
+    } else if (have.m) {
+        have.load(ilv_slot(ti, p0), f);
+    } else {
+        pre.load(next_off[ti.b] + v, f);
+    }
+    SElem<T, NX> a;
+    for (int64_t p = p0; p < pe; ++p) {
+        const int64_t u = ilv_slot(ti, p), ug = gam.stride ? u : 0;
+        if (marg.m)
+            marg.store(u, f);
+        T F[NX][NX], M[NX][2 * NX], mp[NX];
+#pragma unroll
+        for (int i = 0; i < NX; ++i)
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                F[i][j] = gam.F[(i * NX + j) * gam.ld + ug];
+        mv(F, f.m, mp);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            mp[i] += gam.c[i * gam.ld + ug];
+#pragma unroll
+            for (int j = 0; j < NX; ++j) {
+                T s = F[i][j] * f.N[j][j];
+#pragma unroll
+                for (int t = j + 1; t < NX; ++t)
+                    s = pfma(F[i][t], f.N[t][j], s);
+                M[i][j] = s;
+                M[i][NX + j] = j <= i ? gam.SL[tri_idx(i, j <= i ? j : i) * gam.ld + ug] : T(0);
+            }
+        }
+        lq_rows<NX, NX>(M);
+        T H[NY][NX], d[NY], SO[NY][NY];
+        gam.load_obs(ug, H, d, SO);
+        T Q[NY + NX][NX + NY], w[NY][1];
+        step_update(H, M, SO, Q);
+#pragma unroll
+        for (int q = 0; q < NY; ++q) {
+            T s = y[q * T_y + ti.off + p] - d[q];
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                s = pfma(-H[q][j], mp[j], s);
+            w[q][0] = s;
+        }
+        step_solve<T, NY, 1>(Q, w);
+        if (ell) {
+            double l = -0.5 * NY * 1.8378770664093454835606594728112; // log(2 pi)
+#pragma unroll
+            for (int q = 0; q < NY; ++q)
+                l -= (double)plog(Q[q][q]) + 0.5 * (double)w[q][0] * (double)w[q][0];
+            ell[u] = l;
+        }
+        if constexpr (ADJ) {
+            // T_k = {Phi = F - P21 G, u = G^T w, Gam = (u u^T - G^T G) / 2},
+            // G = Y^{-1} H F
+            T G[NY][NX];
+            mm(H, F, G);
+            step_solve<T, NY, NX>(Q, G);
+            SElem<T, NX> e;
+#pragma unroll
+            for (int i = 0; i < NX; ++i) {
+                T uu = T(0);
+#pragma unroll
+                for (int q = 0; q < NY; ++q)
+                    uu = pfma(G[q][i], w[q][0], uu);
+                e.g[i] = uu;
+#pragma unroll
+                for (int j = 0; j < NX; ++j) {
+                    T s = F[i][j];
+#pragma unroll
+                    for (int q = 0; q < NY; ++q)
+                        s = pfma(-Q[NY + i][q], G[q][j], s);
+                    e.E[i][j] = s;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < NX; ++i)
+#pragma unroll
+                for (int j = 0; j <= i; ++j) {
+                    T s = e.g[i] * e.g[j];
+#pragma unroll
+                    for (int q = 0; q < NY; ++q)
+                        s = pfma(-G[q][i], G[q][j], s);
+                    e.D[i][j] = T(0.5) * s;
+                }
+            if (p == p0)
+                a = e;
+            else
+                adj_combine_v<T, NX>(SRegV<T, NX>{&a}, SRegV<T, NX>{&e}, SRegV<T, NX>{&a});
+        }
+        // the factor is made triangular at every step, stored or not: a
+        // gradient that starts from stored marginals repeats this arithmetic
+        T P22[NX][NX];
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            f.m[i] = mp[i];
+#pragma unroll
+            for (int q = 0; q < NY; ++q)
+                f.m[i] = pfma(Q[NY + i][q], w[q][0], f.m[i]);
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                P22[i][j] = Q[NY + i][NY + j];
+        }
+        tria_rect(P22, f.N);
+    }
+    if constexpr (ADJ)
+        selem_copy<T, NX>(SRegV<T, NX>{&a},
+                          view_of(agg, agg_slot(next_off, ti.b, cnt1 - 1 - v, nT, nE)));
+}
+
+template <typename T, int NX, int NY, class Out, class PreRef>
+__global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, NY> gam,
+                                                  const T *y, int64_t T_y, MargRef<T, NX> marg,
+                                                  PreRef pre, Out out, AdjPrior<T, NX> prior,
+                                                  const int64_t *next_off)
+{
+    const TileInfo ti = tile_info(g);
+    if ((int)threadIdx.x >= ti.nvalid)
+        return;
+    const int64_t p0 = ti.start + (int64_t)threadIdx.x * ti.E;
+    int64_t pe = p0 + ti.E;
+    if (pe > ti.start + ti.tcnt)
+        pe = ti.start + ti.tcnt;
+    const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
+    Marg<T, NX> lam;
+    pre.load(next_off[ti.b] + cnt1 - 1 - v, lam);
+    for (int64_t p = pe - 1; p >= p0; --p) {
+        const int64_t u = ilv_slot(ti, p), ug = gam.stride ? u : 0;
         T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
-        Marg<T, NX> f;
-        load(ti, p, t, F, c, SL, H, d, SO, yy, f);
+        gam.load_trans(ug, F, c, SL);
+        gam.load_obs(ug, H, d, SO);
+#pragma unroll
+        for (int a = 0; a < NY; ++a)
+            yy[a] = y[a * T_y + ti.off + p];
+        Marg<T, NX> f, o;
+        marg.load(u, f); // state p, before the step
         StepQ<T, NX, NY> q;
         T Np[NX][NX], P22[NX][NX], mp[NX];
         adj_step(F, c, SL, H, d, SO, yy, f, q, Np, P22, mp);
@@ -130,187 +466,32 @@ struct AdjSrc {
             adj_element(F, q, e);
             adj_apply_v<T, NX>(SRegV<T, NX>{&e}, lam, o);
         }
-        T Lb[NX][NX], Ob[NY][NY], cb[NX], db[NY];
-        adj_gram_bars(H, q, lam, Lb, Ob, cb, db);
-        if constexpr (!Out::kGamma) {
-            double g1 = 0.0, g2 = 0.0, g3 = 0.0;
-#pragma unroll
-            for (int i = 0; i < NX; ++i)
-#pragma unroll
-                for (int j = 0; j < NX; ++j) {
-                    g1 += (double)(Lb[i][j] * out.th.dQ1[i][j]);
-                    g2 += (double)(Lb[i][j] * out.th.dQ2[i][j]);
-                }
-#pragma unroll
-            for (int a = 0; a < NY; ++a)
-                g3 += (double)(Ob[a][a] * out.th.dR);
-            out.terms[t] = g1;
-            out.terms[out.T_y + t] = g2;
-            out.terms[2 * out.T_y + t] = g3;
-        } else {
-            const T w = out.w ? (T)out.w[ti.b] : T(1);
-            // Sl = (W v v^T W - W) / 2
-            T Sl[NY][NY];
-#pragma unroll
-            for (int a = 0; a < NY; ++a)
-#pragma unroll
-                for (int b = 0; b <= a; ++b) {
-                    T s = T(0);
-#pragma unroll
-                    for (int u = a; u < NY; ++u)
-                        s = pfma(q.Yi[u][a], q.Yi[u][b], s);
-                    Sl[a][b] = Sl[b][a] = T(0.5) * (q.Wv[a] * q.Wv[b] - s);
-                }
-            // factor cotangents of S_L and S_O: lower triangles of 2 G_bar S
-            T SLb[NX][NX], SOb[NY][NY];
-            mm_lower(Lb, SL, SLb);
-            mm_lower(Ob, SO, SOb);
-            // F_bar = c_bar m^T + 2 Lam_bar F N N^T
-            T Fb[NX][NX];
-            {
-                T FN[NX][NX], X[NX][NX];
-                mm_lower(F, f.N, FN);
-                mm(Lb, FN, X);
-#pragma unroll
-                for (int i = 0; i < NX; ++i)
-#pragma unroll
-                    for (int j = 0; j < NX; ++j) {
-                        T s = cb[i] * f.m[j];
-#pragma unroll
-                        for (int u = 0; u <= j; ++u)
-                            s = pfma(T(2) * X[i][u], f.N[j][u], s);
-                        Fb[i][j] = s;
-                    }
-            }
-            // H_bar = 2 Sl H P^- + W v (m^- + P_k m_bar)^T - (K^T m_bar) m_k^T
-            //         - 2 K^T P_bar P_k,  P^- = Np Np^T, P_k = P22 P22^T,
-            //         m_k = m^- + K v with v = Y w
-            T Hb[NY][NX];
-            {
-                T Pm[NX][NX], Pk[NX][NX], Pb[NX][NX], kb[NY], mk[NX], pm[NX];
-                sym_from_lower(Pm, [&](int i, int j) {
-                    T s = T(0);
-                    for (int u = 0; u <= j; ++u)
-                        s = pfma(Np[i][u], Np[j][u], s);
-                    return s;
-                });
-                sym_from_lower(Pk, [&](int i, int j) {
-                    T s = T(0);
-                    for (int u = 0; u <= j; ++u)
-                        s = pfma(P22[i][u], P22[j][u], s);
-                    return s;
-                });
-                sym_from_lower(Pb, [&](int i, int j) { return lam.N[i][j]; });
-                mtv(q.K, lam.m, kb);
-                // K v = Psi21 w (K = Psi21 Y^{-1}) -- recovered as K (Y w)
-                T v[NY];
-#pragma unroll
-                for (int a = 0; a < NY; ++a) {
-                    // Y = Yi^{-1}: solve Yi v = w
-                    T s = q.w[a];
-#pragma unroll
-                    for (int u = 0; u < a; ++u)
-                        s = pfma(-q.Yi[a][u], v[u], s);
-                    v[a] = s * prcp(q.Yi[a][a]);
-                }
-                mv(Pk, lam.m, pm);
-#pragma unroll
-                for (int i = 0; i < NX; ++i) {
-                    T s = mp[i];
-#pragma unroll
-                    for (int a = 0; a < NY; ++a)
-                        s = pfma(q.K[i][a], v[a], s);
-                    mk[i] = s;
-                }
-                T SH[NY][NX], KP[NY][NX];
-                mm(Sl, H, SH);
-#pragma unroll
-                for (int a = 0; a < NY; ++a)
-#pragma unroll
-                    for (int j = 0; j < NX; ++j) {
-                        T s = T(0);
-#pragma unroll
-                        for (int u = 0; u < NX; ++u)
-                            s = pfma(q.K[u][a], Pb[u][j], s);
-                        KP[a][j] = s;
-                    }
-#pragma unroll
-                for (int a = 0; a < NY; ++a)
-#pragma unroll
-                    for (int j = 0; j < NX; ++j) {
-                        T s = q.Wv[a] * (mp[j] + pm[j]) - kb[a] * mk[j];
-#pragma unroll
-                        for (int u = 0; u < NX; ++u) {
-                            s = pfma(T(2) * SH[a][u], Pm[u][j], s);
-                            s = pfma(T(-2) * KP[a][u], Pk[u][j], s);
-                        }
-                        Hb[a][j] = s;
-                    }
-            }
-            // scale by the sequence's cotangent and store
-#pragma unroll
-            for (int i = 0; i < NX; ++i) {
-                cb[i] *= w;
-#pragma unroll
-                for (int j = 0; j < NX; ++j) {
-                    Fb[i][j] *= w;
-                    SLb[i][j] *= T(2) * w;
-                }
-            }
-#pragma unroll
-            for (int a = 0; a < NY; ++a) {
-                db[a] *= w;
-#pragma unroll
-                for (int j = 0; j < NX; ++j)
-                    Hb[a][j] *= w;
-#pragma unroll
-                for (int j = 0; j < NY; ++j)
-                    SOb[a][j] *= T(2) * w;
-            }
-            out.bar.store_trans(t, Fb, cb, SLb);
-            out.bar.store_obs(t, Hb, db, SOb);
-        }
+        int64_t at = u;
+        if constexpr (Out::kGamma)
+            at = out.ilv ? u : ti.off + p;
+        adj_emit(out, ti.b, at, F, SL, H, SO, f, q, Np, P22, mp, lam);
+        lam = o;
     }
-};
+    if (p0 == 0)
+        prior.put(ti.b, lam);
+}
 
-// finest-level sink of the adjoint scan: the inclusive suffix at the last
-// scan position is lambda_0, the cotangent of the prior (m0, P0); with
-// m0_bar set it is stored per sequence as (m0_bar [NX][B], N0_bar [P][B],
-// N0_bar = lower triangle of 2 P0_bar N0), scaled by w_b
-template <typename T, int NX>
-struct AdjDst {
-    static constexpr bool stageable = false, stage_excl = false;
-    T *m0_bar;
-    T *N0_bar;
-    const T *N0; // packed prior factor
-    const double *w;
-    int B;
-    PSS_INL void put(const TileInfo &ti, int64_t p, const Marg<T, NX> &excl,
-                     const Marg<T, NX> &incl) const
-    {
-        if (!m0_bar || p != ti.cnt - 1)
-            return;
-        const T s = w ? (T)w[ti.b] : T(1);
-        T Pb[NX][NX], L[NX][NX];
-        sym_from_lower(Pb, [&](int i, int j) { return incl.N[i][j]; });
-#pragma unroll
-        for (int i = 0; i < NX; ++i)
-#pragma unroll
-            for (int j = 0; j < NX; ++j)
-                L[i][j] = (j <= i) ? N0[tri_idx(i, j)] : T(0);
-#pragma unroll
-        for (int i = 0; i < NX; ++i) {
-            m0_bar[(int64_t)i * B + ti.b] = s * incl.m[i];
-#pragma unroll
-            for (int j = 0; j <= i; ++j) {
-                T a = T(0);
-#pragma unroll
-                for (int u = j; u < NX; ++u)
-                    a = pfma(Pb[i][u], L[u][j], a);
-                N0_bar[(int64_t)tri_idx(i, j) * B + ti.b] = T(2) * s * a;
-            }
-        }
-    }
-};
+// cotangents at interleaved slots to plain ones, one thread per step
+template <typename T, int NX, int NY>
+__global__ __launch_bounds__(256) void k_gamma_plain(const int64_t *y_off, int B, int64_t T_y,
+                                                     GammaRef<T, NX, NY> src,
+                                                     GammaRef<T, NX, NY> dst, StepTiles tiles)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= T_y)
+        return;
+    const int b = find_seq(y_off, B, t, 0);
+    const int64_t i = step_slot(y_off, b, t - y_off[b], tiles);
+    T F[NX][NX], c[NX], S[NX][NX], H[NY][NX], d[NY], O[NY][NY];
+    src.load_trans(i, F, c, S);
+    src.load_obs(i, H, d, O);
+    dst.store_trans(t, F, c, S);
+    dst.store_obs(t, H, d, O);
+}
 
 } // namespace pss

@@ -82,13 +82,17 @@ struct ScanShape {
     int T[kMaxLevels] = {};
     int E[kMaxLevels] = {};
     int flat[kMaxLevels] = {};
+    // level 0 of a flat plan: sequences of at most n_short elements fold
+    // E_short per thread instead of E[0] (0: no such rule)
+    int E_short = 0;
+    int64_t n_short = 0;
     int64_t ntiles[kMaxLevels] = {};
     int64_t nelem[kMaxLevels] = {};
 };
 
 // level 0 takes (T0, E0), level 1 (Tup, E1), the levels above (Tup, Eup)
 ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, int Eup,
-                    bool flat0);
+                    bool flat0, int E_short = 0, int64_t n_short = 0);
 // device tile offsets of every level and, where elem_off is given, the
 // element offsets of every level >= 1 (both [B + 1] per level)
 int launch_plan(const Ctx &c, const ScanShape &sh, int extra, int64_t *const *tile_off,

@@ -76,8 +76,9 @@ struct StepQ {
 
 // Y = Tria([H N^-, S_O]) with N^- = Tria([F N, S_L]); [[Y, 0], [Psi21, Psi22]]
 // = Tria([[H N^-, S_O], [N^-, 0]]) gives K = Psi21 Y^{-1} (the blocks of the
-// Lemma 1 step, eq. sqrt-filter-step1).  Np / P22 / mp receive N^-, Psi22 and
-// m^- when the caller needs them (the Gamma cotangent), else may be ignored.
+// Lemma 1 step, eq. sqrt-filter-step1).  Np / P22 / mp receive N^-, a square
+// root of P_k (dense: the sweep stops after its NY measurement rows) and m^-
+// when the caller needs them (the Gamma cotangent), else may be ignored.
 template <typename T, int NX, int NY>
 PSS_INL void adj_step(const T (&F)[NX][NX], const T (&c)[NX], const T (&SL)[NX][NX],
                       const T (&H)[NY][NX], const T (&d)[NY], const T (&SO)[NY][NY],
@@ -90,7 +91,24 @@ PSS_INL void adj_step(const T (&F)[NX][NX], const T (&c)[NX], const T (&SL)[NX][
         tria_dense_lower(FN, SL, Np);
     }
     T Y[NY][NY], P21[NX][NY];
-    psi_blocks(H, Np, SO, Y, P21, P22);
+    {
+        T Q[NY + NX][NX + NY];
+        step_update(H, Np, SO, Q);
+#pragma unroll
+        for (int a = 0; a < NY; ++a)
+#pragma unroll
+            for (int b = 0; b <= a; ++b)
+                Y[a][b] = Q[a][b];
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+#pragma unroll
+            for (int a = 0; a < NY; ++a)
+                P21[i][a] = Q[NY + i][a];
+#pragma unroll
+            for (int j = 0; j < NX; ++j)
+                P22[i][j] = Q[NY + i][NY + j];
+        }
+    }
     rsolve_lower(P21, Y, q.K);
     mv(F, f.m, mp);
 #pragma unroll

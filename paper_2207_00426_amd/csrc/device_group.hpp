@@ -487,5 +487,101 @@ __device__ __forceinline__ void smoother_apply(const T *ei, const T *s, T *o, co
     lds_order();
 }
 
+// shared by the two forms of the adjoint map below: a = Phi^T m2 + u (row r)
+// and row r (j <= r) of Phi^T S2 Phi + sym((Phi^T m2) u^T) + Gam, for the map
+// t = {Phi, u, Gam} (stored as {E, g, D}) and (m2, S2 = packed symmetric)
+template <typename T, int NX>
+__device__ __forceinline__ void adj_rows(const T *t, const T *m2, const T *S2,
+                                         const Lane<NX> &ln, T &a, T (&row)[NX])
+{
+    using O = SOff<NX>;
+    const int r = ln.r;
+    T P[NX][NX], af[NX], X[NX], ar = T(0), pc[NX];
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+        af[q] = X[q] = T(0);
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            P[q][j] = t[O::E + q * NX + j];
+    }
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+        const T mq = m2[q], sq = S2[q < r ? r * (r + 1) / 2 + q : q * (q + 1) / 2 + r];
+        pc[q] = t[O::E + q * NX + r];
+        ar = pfma(pc[q], mq, ar);
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            af[j] = pfma(P[q][j], mq, af[j]);
+            X[j] = pfma(sq, P[q][j], X[j]); // row r of S2 Phi
+        }
+    }
+    const T ur = t[O::g + r];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) {
+        T s = t[O::D + r * (r + 1) / 2 + (j < r ? j : r)];
+        s = pfma(T(0.5) * ar, t[O::g + j], s);
+        row[j] = pfma(T(0.5) * ur, af[j], s);
+    }
+    each<NX>([&](auto ic) {
+        constexpr int q = decltype(ic)::value;
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            row[j] = pfma(pc[q], bc<q>(X[j]), row[j]);
+    });
+    a = ar + ur;
+}
+
+// adj_combine_v: o = t1 o t2, t2 applied first
+template <typename T, int NX>
+__device__ __forceinline__ void adj_combine(const T *t1, const T *t2, T *o, const Lane<NX> &ln)
+{
+    using O = SOff<NX>;
+    const int r = ln.r;
+    T a, row[NX], PP[NX];
+    adj_rows<T, NX>(t1, t2 + O::g, t2 + O::D, ln, a, row);
+#pragma unroll
+    for (int j = 0; j < NX; ++j)
+        PP[j] = T(0);
+#pragma unroll
+    for (int q = 0; q < NX; ++q) {
+        const T p2 = t2[O::E + r * NX + q];
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            PP[j] = pfma(p2, t1[O::E + q * NX + j], PP[j]);
+    }
+    lds_order();
+    if (ln.stores && !ln.hi) {
+        o[O::g + r] = a;
+        T *D = o + O::D + r * (r + 1) / 2;
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            o[O::E + r * NX + j] = PP[j];
+            if (j <= r)
+                D[j] = row[j];
+        }
+    }
+    lds_order();
+}
+
+// adj_apply_v: o = t(lam), lam = (m_bar, packed P_bar)
+template <typename T, int NX>
+__device__ __forceinline__ void adj_apply(const T *t, const T *lam, T *o, const Lane<NX> &ln)
+{
+    using M = MOff<NX>;
+    const int r = ln.r;
+    T a, row[NX];
+    adj_rows<T, NX>(t, lam + M::m, lam + M::N, ln, a, row);
+    lds_order();
+    if (ln.stores && !ln.hi) {
+        o[M::m + r] = a;
+        T *D = o + M::N + r * (r + 1) / 2;
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            if (j <= r)
+                D[j] = row[j];
+    }
+    lds_order();
+}
+
 } // namespace grp
 } // namespace pss

@@ -151,6 +151,57 @@ PSS_INL void psi_blocks(const T (&H)[NY][NX], const T (&L)[NX][NX], const T (&SO
     }
 }
 
+// measurement half of a step: Q = [[H L, S_O], [L, 0]] with L lower, its NY
+// upper rows reduced.  Y = Q[0..NY)[0..NY), P21 = lower rows' first NY columns,
+// a square root of the updated covariance in the NX columns after them.
+template <typename T, int NX, int NY, int R, int C>
+PSS_INL void step_update(const T (&H)[NY][NX], const T (&L)[R][C], const T (&SO)[NY][NY],
+                         T (&Q)[NY + NX][NX + NY])
+{
+#pragma unroll
+    for (int a = 0; a < NY; ++a) {
+#pragma unroll
+        for (int j = 0; j < NX; ++j) {
+            T s = H[a][j] * L[j][j];
+#pragma unroll
+            for (int t = j + 1; t < NX; ++t)
+                s = pfma(H[a][t], L[t][j], s);
+            Q[a][j] = s;
+        }
+#pragma unroll
+        for (int j = 0; j < NY; ++j)
+            Q[a][NX + j] = j <= a ? SO[a][j] : T(0);
+    }
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            Q[NY + i][j] = j <= i ? L[i][j] : T(0);
+#pragma unroll
+        for (int j = 0; j < NY; ++j)
+            Q[NY + i][NX + j] = T(0);
+    }
+    lq_rows<NY, NX>(Q);
+}
+
+// x <- Y^{-1} x in place for NC columns (Y the reduced rows of Q)
+template <typename T, int NY, int NC, int R, int C>
+PSS_INL void step_solve(const T (&Q)[R][C], T (&x)[NY][NC])
+{
+#pragma unroll
+    for (int a = 0; a < NY; ++a) {
+        const T inv = prcp(Q[a][a]);
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            T s = x[a][j];
+#pragma unroll
+            for (int t = 0; t < a; ++t)
+                s = pfma(-Q[a][t], x[t][j], s);
+            x[a][j] = s * inv;
+        }
+    }
+}
+
 // Z_k = F^T H^T Y^{-T} (nx x ny), stored squared as Tria([Z_k, 0]); and
 // eta_k = Z_k Y^{-1} r with r = y_k - H_k c_{k-1} - d_k.
 template <typename T, int NX, int NY>

@@ -33,7 +33,18 @@ struct Defaults {
     static constexpr int T0 = 64;
     static constexpr int E0_filter = 4;
     static constexpr int E0_smoother = 2;
-    static constexpr int E0_step = 8;
+    // Kalman steps per thread (steps.hpp): 8 balance the level above, which
+    // costs most per element, against the thread's serial steps; a short
+    // sequence leaves the chip idle and only the serial steps count.  The rule
+    // looks at the sequence alone, so that its result does not depend on its
+    // batch.  us per call at 2 and 8 steps: 10 passes of 100 FP64 steps 830 and
+    // 1278, 2 passes of 300 243 and 282, 10 passes of 1003 1685 and 1658; 200
+    // FP32 sequences of ~1800 569 and 317, 2 passes of 10^6 3556 and 2124.
+    // A scalar state has cheap operators and folds 2 (2 passes of 10^4 Ricker
+    // steps: 112 us, with 8 129).
+    static constexpr int E0_step = NX == 1 ? 2 : 8;
+    static constexpr int E0_step_short = 2;
+    static constexpr int64_t n_step_short = 768;
     static constexpr int Tup = 64;
     static constexpr int E1_filter = 4;
     static constexpr int E1_smoother = 2;
@@ -161,6 +172,20 @@ struct Core {
         return g;
     }
 
+    // one in space of exactly its size (component arrays back to back)
+    static pss_gamma carve_gamma_packed(T *p, int64_t T_y)
+    {
+        pss_gamma g;
+        g.F = p;
+        g.c = p += (int64_t)NX * NX * T_y;
+        g.SL = p += (int64_t)NX * T_y;
+        g.H = p += (int64_t)P * T_y;
+        g.d = p += (int64_t)NY * NX * T_y;
+        g.SO = p += (int64_t)NY * T_y;
+        g.stride = 1;
+        return g;
+    }
+
     template <class Op>
     static size_t lds_bytes(int Tb, int E, bool stage)
     {
@@ -214,6 +239,8 @@ struct Core {
         g.B = c.B;
         g.E = sh.E[l];
         g.stage = scan_stage(Op::NE, Op::NP, sh.T[l], sh.E[l], sizeof(T));
+        g.E_short = sh.E_short;
+        g.n_short = l == 0 ? sh.n_short : 0;
         return g;
     }
 
@@ -351,7 +378,7 @@ struct Core {
     template <class Op, bool Flat, class Src0, class Dst0, class AggRef, class Start>
     static int run_scan(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int extra,
                         const Src0 &src0, const Dst0 &dst0, const Start &start,
-                        AggRef (*agg_ref)(T *, int64_t), int stop = 0)
+                        AggRef (*agg_ref)(T *, int64_t))
     {
         int rc = launch_plan(c, sh, extra, w.tile_off, w.elem_off);
         if (rc)
@@ -408,7 +435,7 @@ struct Core {
             hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, dst0, w.tree[0], tree_ld, pin);
             return hip_check(hipGetLastError(), "scan down launch");
         };
-        return run_levels<Op, Flat>(c, sh, w, extra, start, agg_ref, stop, up0, top0, down0);
+        return run_levels<Op, Flat>(c, sh, w, extra, start, agg_ref, 0, up0, top0, down0);
     }
 
     // ------------------------------------------------------------------
@@ -424,22 +451,6 @@ struct Core {
         int T0, E0, Tup, E1, Eup;
         shapes(c, true, T0, E0, Tup, E1, Eup);
         return plan_scan(c, 1, T0, E0, Tup, E1, Eup, kFlatS);
-    }
-
-    // the adjoint scan (reverse time, one element per step): tree level 0
-    // with 2 elements per thread, as the smoother (its element -- a Kalman
-    // step from the filtering marginal -- dominates the operator)
-    static ScanShape adj_shape(const Ctx &c)
-    {
-        const int T0 = c.p->scan_threads > 0 ? c.p->scan_threads : Defaults<T, NX>::T0;
-        const int Tup = std::min(T0, (int)Defaults<T, NX>::Tup);
-        return plan_scan(c, 0, T0, 2, Tup, 2, 2, false);
-    }
-    static size_t ascan_bytes(const Ctx &c)
-    {
-        Carver cv{nullptr};
-        carve_scan<AdjScan<T, NX>>(cv, c, adj_shape(c));
-        return cv.used;
     }
 
     static size_t fscan_bytes(const Ctx &c)
@@ -459,21 +470,12 @@ struct Core {
     // ilv: the elements are stored tile-interleaved for this scan's level 0
     // (as written by felem(..., true)); the library's own passes use that
     // cov: the standard (covariance-form) scan of the same storage layout
-    // ck_pre (square-root form only): the exclusive prefixes of the filter
-    // scan's level ck_level (1 <= ck_level < levels) -- written there by a
-    // full scan, or, with resume, read from there and only the levels below
-    // re-run (the backward pass of a checkpointed log-likelihood)
     static int fscan(const Ctx &c, const pss_felem *el, void *mf, void *Nf, void *ws,
-                     bool ilv = false, bool cov = false, int ck_level = 0, T *ck_pre = nullptr,
-                     bool resume = false)
+                     bool ilv = false, bool cov = false)
     {
         const ScanShape sh = filter_shape(c);
         Carver cv{static_cast<char *>(ws)};
         auto w = carve_scan<FS>(cv, c, sh);
-        const bool ck = ck_pre && ck_level >= 1 && ck_level < sh.L;
-        if (ck)
-            w.pre[ck_level] = ck_pre;
-        const int stop = (ck && resume) ? ck_level : 0;
         FElemRef<T, NX> er;
         er.A = mptr<T>(el->A);
         er.b = mptr<T>(el->b);
@@ -500,10 +502,10 @@ struct Core {
         }
         if (ilv) {
             RefSrc<FS, FElemRef<T, NX>, true, LZ> src{er};
-            return run_scan<FS, kFlatF>(c, sh, w, 0, src, dst, st, &felem_ref, stop);
+            return run_scan<FS, kFlatF>(c, sh, w, 0, src, dst, st, &felem_ref);
         }
         RefSrc<FS, FElemRef<T, NX>, false, LZ> src{er};
-        return run_scan<FS, kFlatF>(c, sh, w, 0, src, dst, st, &felem_ref, stop);
+        return run_scan<FS, kFlatF>(c, sh, w, 0, src, dst, st, &felem_ref);
     }
 
     static int sscan(const Ctx &c, const pss_gamma *g, const void *mf, const void *Nf, void *ms,
@@ -527,23 +529,6 @@ struct Core {
         SmootherSrc<T, NX, NY> src{gamma_ref(g, c.T_y), marg_ref2(mf, Nf, c.T_x),
                                    selem_ref(stash, c.T_x), c.p->y_off};
         return run_scan<SS, kFlatS>(c, sh, w, 1, src, dst, st, &selem_ref);
-    }
-
-    // the adjoint scan: the reverse scan of the cotangent maps T_k from the
-    // filtering marginals (mf, Nf) and the linearisation, emitting through
-    // `out` the step cotangents and through `dst` the prior's
-    template <class Out>
-    static int ascan(const Ctx &c, const pss_gamma *g, const void *y, const void *mf,
-                     const void *Nf, const Out &out, const AdjDst<T, NX> &dst, void *ws)
-    {
-        using AS = AdjScan<T, NX>;
-        const ScanShape sh = adj_shape(c);
-        Carver cv{static_cast<char *>(ws)};
-        auto w = carve_scan<AS>(cv, c, sh);
-        AdjSrc<T, NX, NY, Out> src{gamma_ref(g, c.T_y), marg_ref2(mf, Nf, c.T_x), cptr<T>(y),
-                                   c.T_y, out};
-        StartPre<T, NX> st{nullptr, nullptr};
-        return run_scan<AS, false>(c, sh, w, 0, src, dst, st, &selem_ref);
     }
 
     static int felem(const Ctx &c, const pss_gamma *g, const void *y, const pss_felem *out,
@@ -614,6 +599,13 @@ struct Core {
     // nonlinear models are linearised on every pass; a linear one is given
     static bool nonlinear(const Ctx &c) { return c.p->model != PSS_MODEL_LINEAR; }
 
+    // scan and sum space of the log-likelihood calls (shared in time); the
+    // covariance form scans stored elements
+    static size_t grad_scans(const Ctx &c, int nc)
+    {
+        return std::max({fscan_bytes(c), scan_bytes(c, grad_shape(c)), seq_sum_bytes(c, nc)});
+    }
+
     static size_t ws_size(const Ctx &c, int op)
     {
         const size_t scans = fscan_bytes(c) > sscan_bytes(c) ? fscan_bytes(c) : sscan_bytes(c);
@@ -628,14 +620,15 @@ struct Core {
         case PSS_OP_SMOOTHER_SCAN:
             return sscan_bytes(c);
         case PSS_OP_IPLS:
-            return gamma_bytes(c) + felem_bytes(c) + marg_bytes(c) + scans;
+            return gamma_bytes(c) + felem_bytes(c) + marg_bytes(c) +
+                   std::max(scans, scan_bytes(c, step_shape(c)));
         case PSS_OP_LOGLIK:
-            return fwd + std::max(fscan_bytes(c), seq_sum_bytes(c, 1));
+            return fwd + grad_scans(c, 1);
         case PSS_OP_LOGLIK_GRAD:
-            return fwd + std::max({fscan_bytes(c), ascan_bytes(c), seq_sum_bytes(c, 3)}) +
-                   align256(3 * c.T_y * sizeof(double)) + align256(3 * c.B * sizeof(double));
+            return fwd + grad_scans(c, 3) + align256(3 * c.T_y * sizeof(double)) +
+                   align256(3 * c.B * sizeof(double));
         case PSS_OP_LOGLIK_VJP:
-            return fwd + std::max({fscan_bytes(c), ascan_bytes(c), seq_sum_bytes(c, 1)});
+            return fwd + grad_scans(c, 1);
         case PSS_OP_SCORE_FISHER:
             return gamma_bytes(c) + felem_bytes(c) + marg_bytes(c) +
                    align256(c.T_y * sizeof(double)) + std::max(scans, seq_sum_bytes(c, 3)) +
@@ -680,13 +673,10 @@ struct Core {
         v.level = ck->level;
         Carver cv{static_cast<char *>(ck->buf)};
         v.ll = cv.template take<double>((size_t)c.B);
-        if (ck->level == 0) {
+        if (ck->level == 0)
             v.marg = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
-        } else {
-            const ScanShape sh = filter_shape(c);
-            if (ck->level < sh.L)
-                v.pre = cv.template take<T>((size_t)Sizes<NX>::marg * sh.nelem[ck->level]);
-        }
+        else if (ck->level < grad_shape(c).L)
+            v.pre = cv.template take<T>(0);
         return v;
     }
     // the filter scan's level count for this problem (checkpoint levels
@@ -698,9 +688,52 @@ struct Core {
     {
         int T0, E0, Tup, E1, Eup;
         shapes(c, false, T0, E0, Tup, E1, Eup);
-        if (c.p->scan_elems <= 0)
-            E0 = Defaults<T, NX>::E0_step;
-        return plan_scan(c, 0, T0, E0, Tup, E1, Eup, true);
+        if (c.p->scan_elems > 0)
+            return plan_scan(c, 0, T0, E0, Tup, E1, Eup, true);
+        using D = Defaults<T, NX>;
+        return plan_scan(c, 0, T0, D::E0_step, Tup, E1, Eup, true, D::E0_step_short,
+                         D::n_step_short);
+    }
+    static StepTiles step_tiles(const ScanShape &sh)
+    {
+        return StepTiles{sh.T[0], sh.E[0], sh.E_short, sh.n_short};
+    }
+
+    // the same for the log-likelihood calls: at least 4 steps a thread, so that
+    // a checkpoint of level 1 holds a prefix per 4 states at most.  Their
+    // walks are longer per step and their scans above cheaper, so 8 steps pay
+    // only on long sequences (us per gradient at 4 and 8 steps, FP64: 1 x 1500
+    // 210 and 220, 8 x 6000 of a linear model 253 and 313, 1 x 10^4 227 and 274,
+    // 64 x 10^4 889 and 806).
+    static ScanShape grad_shape(const Ctx &c)
+    {
+        int T0, E0, Tup, E1, Eup;
+        shapes(c, false, T0, E0, Tup, E1, Eup);
+        if (c.p->scan_elems > 0)
+            return plan_scan(c, 0, T0, E0, Tup, E1, Eup, true);
+        using D = Defaults<T, NX>;
+        return plan_scan(c, 0, T0, std::max(4, D::E0_step), Tup, E1, Eup, true,
+                         std::max(4, D::E0_step_short), 8192);
+    }
+    static size_t scan_bytes(const Ctx &c, const ScanShape &sh)
+    {
+        Carver cv{nullptr};
+        carve_scan<FS>(cv, c, sh);
+        return cv.used;
+    }
+    template <class Op>
+    static ScanWs<Op> share_ws(const ScanShape &sh, const ScanWs<FS> &w)
+    {
+        static_assert(Op::NE <= FS::NE && Op::NP <= FS::NP, "shares the filter scan's space");
+        ScanWs<Op> o{};
+        for (int l = 0; l < sh.L; ++l) {
+            o.tile_off[l] = w.tile_off[l];
+            o.elem_off[l] = w.elem_off[l];
+            o.agg[l] = w.agg[l];
+            o.pre[l] = w.pre[l];
+            o.tree[l] = w.tree[l];
+        }
+        return o;
     }
 
     // linearisation of every step into its interleaved slot
@@ -762,31 +795,14 @@ struct Core {
         const SElemRef<T, NX> stash = selem_ref(fel, c.T_y);
         const MargAos<T, NX> last{fel + (size_t)Sizes<NX>::selem * c.T_y};
         // the smoother's upper levels take over the filter's space
-        ScanWs<SS> ws_s{};
-        for (int l = 0; l < sh.L; ++l) {
-            ws_s.tile_off[l] = w.tile_off[l];
-            ws_s.elem_off[l] = w.elem_off[l];
-            ws_s.agg[l] = w.agg[l];
-            ws_s.pre[l] = w.pre[l];
-            ws_s.tree[l] = w.tree[l];
-        }
+        const auto ws_s = share_ws<SS>(sh, w);
         int rc = launch_plan(c, sh, 0, w.tile_off, w.elem_off);
         if (rc)
             return rc;
-        const int64_t TS = (int64_t)sh.T[0] * sh.E[0];
-        pss_gamma gl = gw;
-        if (!nonlinear(c)) {
-            if (gin->stride == 0) {
-                gl = *gin;
-            } else {
-                hipLaunchKernelGGL((k_gamma_ilv<T, NX, NY>), dim3((unsigned)((c.T_y + 255) / 256)),
-                                   dim3(256), 0, c.s, c.p->y_off, c.B, c.T_y,
-                                   gamma_ref(gin, c.T_y), gamma_ref(&gw, c.T_y), TS, sh.E[0]);
-                if ((rc = hip_check(hipGetLastError(), "linearisation layout launch")))
-                    return rc;
-            }
-        }
-        const GammaRef<T, NX, NY> gam = gamma_ref(&gl, c.T_y);
+        const StepTiles tiles = step_tiles(sh);
+        GammaRef<T, NX, NY> gam = gamma_ref(&gw, c.T_y);
+        if (!nonlinear(c) && (rc = step_given(c, gin, gw, tiles, gam)))
+            return rc;
         const NomRef<T, NX> plain{marg_ref2(m_nom, N_nom, c.T_x), c.T_y, 0};
         const NomRef<T, NX> inner{marg_ref(mid, c.T_x), c.T_y, 1};
         // The last pass writes the caller's layout itself while the lines it
@@ -822,10 +838,39 @@ struct Core {
             KTime kt(c.s, "nominal_plain", "", 0);
             hipLaunchKernelGGL((k_nominal_plain<T, NX>), dim3((unsigned)((c.T_x + 255) / 256)),
                                dim3(256), 0, c.s, c.p->y_off, c.B, c.T_y, c.T_x, inner.r, plain.r,
-                               TS, sh.E[0]);
+                               tiles);
             rc = hip_check(hipGetLastError(), "nominal layout launch");
         }
         return rc;
+    }
+
+    // a linear model's given linearisation: shared by all steps as it is, per
+    // step into interleaved slots
+    static int step_given(const Ctx &c, const pss_gamma *gin, const pss_gamma &gw,
+                          const StepTiles &tiles, GammaRef<T, NX, NY> &gam)
+    {
+        if (gin->stride == 0) {
+            gam = gamma_ref(gin, c.T_y);
+            return PSS_OK;
+        }
+        hipLaunchKernelGGL((k_gamma_ilv<T, NX, NY>), dim3((unsigned)((c.T_y + 255) / 256)),
+                           dim3(256), 0, c.s, c.p->y_off, c.B, c.T_y, gamma_ref(gin, c.T_y),
+                           gamma_ref(&gw, c.T_y), tiles);
+        return hip_check(hipGetLastError(), "linearisation layout launch");
+    }
+
+    // fold of the finest level into the filter scan's level 1
+    static int step_fold(const Ctx &c, const ScanShape &sh, const ScanWs<FS> &w,
+                         const GammaRef<T, NX, NY> &gam, const void *y,
+                         const StepPrior<T, NX> &prior, const NomRef<T, NX> &nom)
+    {
+        KTime kt(c.s, "step_fold", "", 0);
+        const auto agg = agg_of(sh, w, 1, &felem_ref);
+        using Agg = std::decay_t<decltype(agg)>;
+        hipLaunchKernelGGL((k_step_fold<T, NX, NY, Agg>), dim3((unsigned)sh.ntiles[0]),
+                           dim3(sh.T[0]), 0, c.s, level_geom(c, sh, w, 0, 0), gam, cptr<T>(y),
+                           c.T_y, prior, nom, agg, w.elem_off[1], sh.T[1], agg_ilv<FS>(sh));
+        return hip_check(hipGetLastError(), "step fold launch");
     }
 
     // one filter and smoother pass over interleaved linearisation slots
@@ -843,15 +888,7 @@ struct Core {
         auto no_top = [&]() -> int { return PSS_OK; }; // a flat level 0 is never the top
         int rc = run_levels<FS, true>(
             c, sh, w, 0, st, &felem_ref, 0,
-            [&]() -> int {
-                KTime kt(c.s, "step_fold", "", 0);
-                const auto agg = agg_of(sh, w, 1, &felem_ref);
-                using Agg = std::decay_t<decltype(agg)>;
-                hipLaunchKernelGGL((k_step_fold<T, NX, NY, Agg>), grid, block, 0, c.s, g, gam,
-                                   cptr<T>(y), c.T_y, prior, nom, agg, w.elem_off[1], sh.T[1],
-                                   agg_ilv<FS>(sh));
-                return hip_check(hipGetLastError(), "step fold launch");
-            },
+            [&]() -> int { return step_fold(c, sh, w, gam, y, prior, nom); },
             no_top,
             [&]() -> int {
                 KTime kt(c.s, "step_walk", "", 0);
@@ -898,14 +935,11 @@ struct Core {
         return PSS_OK;
     }
 
-    // filter pass shared by loglik and the gradients; returns the carved
-    // state.  With a checkpoint (square-root form) the filtering marginals
-    // go to it (level 0) or the scan's level-`level` prefixes do, and the
-    // log-likelihoods are copied into it.
+    // filter pass over stored elements: the covariance form's log-likelihood
+    // and the score by Fisher's identity; returns the carved state
     static int loglik_core(const Ctx &c, const pss_gamma *gin, const void *m_nom,
                            const void *N_nom, const void *y, double *ll, Carver &cv,
-                           pss_gamma &gw, T *&mfb, void *&scan_ws, const CkView &ck = CkView{},
-                           bool use_ck = false)
+                           pss_gamma &gw, T *&mfb, void *&scan_ws)
     {
         gw = carve_gamma(cv, c.T_y);
         T *fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
@@ -915,16 +949,13 @@ struct Core {
         if (!nonlinear(c))
             gw = *gin;
         const pss_gamma *g = &gw;
-        if (use_ck && ck.level == 0)
-            mfb = ck.marg;
         FElemRef<T, NX> fr = felem_ref(fel, c.T_y);
         pss_felem el{fr.A, fr.b, fr.U, fr.eta, fr.Z};
         int rc;
         const bool cov = c.p->form == PSS_FORM_COV;
         if ((rc = lin_elements(c, gin, m_nom, N_nom, y, gw, &el)))
             return rc;
-        if ((rc = fscan(c, &el, mfb, mfb + (size_t)NX * c.T_x, scan_ws, true, cov,
-                        use_ck ? ck.level : 0, use_ck ? ck.pre : nullptr, false)))
+        if ((rc = fscan(c, &el, mfb, mfb + (size_t)NX * c.T_x, scan_ws, true, cov)))
             return rc;
         const int tb = 128;
         {
@@ -941,69 +972,153 @@ struct Core {
             if ((rc = hip_check(hipGetLastError(), "loglik launch")))
                 return rc;
         }
-        if ((rc = launch_seq_sum(c, 1, ell, c.T_y, ll, scan_ws)))
+        return launch_seq_sum(c, 1, ell, c.T_y, ll, scan_ws);
+    }
+
+    // state of a log-likelihood or gradient call in square-root form, whose
+    // finest level runs Kalman steps
+    struct GradState {
+        ScanShape sh;
+        ScanWs<FS> w;
+        pss_gamma gw;
+        GammaRef<T, NX, NY> gam;
+        T *fel;              // the filter elements' space, not used by the scans
+        MargRef<T, NX> marg; // filtering marginals, state k at the slot of step k + 1
+        double *ell;
+        void *sums;
+    };
+    static int grad_state(const Ctx &c, const pss_gamma *gin, const void *m_nom,
+                          const void *N_nom, const void *y, void *ws, GradState &s)
+    {
+        Carver cv{static_cast<char *>(ws)};
+        s.gw = carve_gamma(cv, c.T_y);
+        s.fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
+        s.marg = marg_ref(cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x), c.T_x);
+        s.ell = cv.template take<double>((size_t)c.T_y);
+        s.sums = cv.base + cv.used; // after the scans, in their space
+        s.sh = grad_shape(c);
+        s.w = carve_scan<FS>(cv, c, s.sh);
+        s.gam = gamma_ref(&s.gw, c.T_y);
+        int rc = launch_plan(c, s.sh, 0, s.w.tile_off, s.w.elem_off);
+        if (rc)
             return rc;
-        if (use_ck)
-            rc = hip_check(hipMemcpyAsync(ck.ll, ll, (size_t)c.B * sizeof(double),
-                                          hipMemcpyDeviceToDevice, c.s),
-                           "checkpoint log-likelihood copy");
-        return rc;
+        if (!nonlinear(c))
+            return step_given(c, gin, s.gw, step_tiles(s.sh), s.gam);
+        return step_lin(c, NomRef<T, NX>{marg_ref2(m_nom, N_nom, c.T_x), c.T_y, 0}, y, &s.gw,
+                        s.sh);
+    }
+
+    // the walk over the finest level (k_filter_walk); have: from stored
+    // marginals instead of the scan's prefixes
+    template <bool ADJ>
+    static int filter_walk(const Ctx &c, const GradState &s, const void *y,
+                           const MargRef<T, NX> &have, const MargRef<T, NX> &out, double *ell)
+    {
+        using AS = AdjScan<T, NX>;
+        KTime kt(c.s, "filter_walk", "", 0);
+        const auto wa = share_ws<AS>(s.sh, s.w);
+        const auto pre = pre_of(s.sh, s.w, 1);
+        const auto agg = agg_of(s.sh, wa, 1, &selem_ref);
+        using Pre = std::decay_t<decltype(pre)>;
+        using Agg = std::decay_t<decltype(agg)>;
+        const StepPrior<T, NX> prior{cptr<T>(c.p->m0), cptr<T>(c.p->N0), nullptr, 0};
+        hipLaunchKernelGGL((k_filter_walk<T, NX, NY, ADJ, Agg, Pre>),
+                           dim3((unsigned)s.sh.ntiles[0]), dim3(s.sh.T[0]), 0, c.s,
+                           level_geom(c, s.sh, s.w, 0, 0), s.gam, cptr<T>(y), c.T_y, prior, pre,
+                           have, out, ell, agg, s.w.elem_off[1], s.sh.T[1], agg_ilv<AS>(s.sh));
+        return hip_check(hipGetLastError(), "filter walk launch");
+    }
+
+    // forward filter pass; stop: only the levels under a checkpoint's
+    template <bool ADJ>
+    static int grad_filter(const Ctx &c, const GradState &s, const void *y,
+                           const MargRef<T, NX> &out, double *ell, int stop = 0)
+    {
+        const StepPrior<T, NX> prior{cptr<T>(c.p->m0), cptr<T>(c.p->N0), nullptr, 0};
+        const StartPre<T, NX> st{cptr<T>(c.p->m0), cptr<T>(c.p->N0)};
+        const MargRef<T, NX> none{nullptr, nullptr, 0};
+        return run_levels<FS, true>(
+            c, s.sh, s.w, 0, st, &felem_ref, stop,
+            [&]() -> int {
+                return step_fold(c, s.sh, s.w, s.gam, y, prior, NomRef<T, NX>{none, c.T_y, 0});
+            },
+            []() -> int { return PSS_OK; },
+            [&]() -> int { return filter_walk<ADJ>(c, s, y, none, out, ell); });
+    }
+
+    static int copy_ll(const Ctx &c, double *dst, const double *src)
+    {
+        return hip_check(hipMemcpyAsync(dst, src, (size_t)c.B * sizeof(double),
+                                        hipMemcpyDeviceToDevice, c.s),
+                         "checkpoint log-likelihood copy");
     }
 
     static int loglik(const Ctx &c, const pss_gamma *gin, const void *m_nom, const void *N_nom,
                       const void *y, double *ll, const pss_ckpt *ckpt, void *ws)
     {
-        Carver cv{static_cast<char *>(ws)};
-        pss_gamma gw;
-        T *mfb;
-        void *scan_ws;
-        return loglik_core(c, gin, m_nom, N_nom, y, ll, cv, gw, mfb, scan_ws, ckpt_view(c, ckpt),
-                           ckpt != nullptr);
+        if (c.p->form == PSS_FORM_COV) {
+            Carver cv{static_cast<char *>(ws)};
+            pss_gamma gw;
+            T *mfb;
+            void *scan_ws;
+            return loglik_core(c, gin, m_nom, N_nom, y, ll, cv, gw, mfb, scan_ws);
+        }
+        GradState s;
+        int rc = grad_state(c, gin, m_nom, N_nom, y, ws, s);
+        if (rc)
+            return rc;
+        const CkView ck = ckpt_view(c, ckpt);
+        MargRef<T, NX> out{nullptr, nullptr, 0};
+        if (ck.marg)
+            out = marg_ref(ck.marg, c.T_x);
+        if (ck.pre)
+            s.w.pre[ck.level] = ck.pre;
+        if ((rc = grad_filter<false>(c, s, y, out, s.ell)))
+            return rc;
+        if ((rc = launch_seq_sum(c, 1, s.ell, c.T_y, ll, s.sums)))
+            return rc;
+        return ckpt ? copy_ll(c, ck.ll, ll) : PSS_OK;
     }
 
-    // forward state of a gradient pass: the linearisation and the filtering
-    // marginals at the nominal, from a checkpoint (re-running the filter
-    // scan's levels under it) or from a full filter pass; ll receives the
-    // log-likelihoods
-    static int grad_forward(const Ctx &c, const pss_gamma *gin, const void *m_nom,
-                            const void *N_nom, const void *y, const pss_ckpt *ckpt, double *ll,
-                            Carver &cv, pss_gamma &gw, T *&mf, void *&scan_ws)
+    // reverse pass: the filtering marginals and the maps' level-1 aggregates
+    // from a checkpoint (re-running what it does not hold) or a full filter
+    // pass, the scan of the maps, the cotangents of every step; ll last (its
+    // sums use the scans' space)
+    template <class Out>
+    static int grad_core(const Ctx &c, GradState &s, const void *y, const pss_ckpt *ckpt,
+                         const Out &out, const AdjPrior<T, NX> &prior, double *ll)
     {
-        if (!ckpt) {
-            T *mfb;
-            int rc = loglik_core(c, gin, m_nom, N_nom, y, ll, cv, gw, mfb, scan_ws);
-            mf = mfb;
-            return rc;
-        }
+        using AS = AdjScan<T, NX>;
         const CkView ck = ckpt_view(c, ckpt);
-        gw = carve_gamma(cv, c.T_y);
-        T *fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
-        T *mfb = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
-        cv.template take<double>((size_t)c.T_y);
-        scan_ws = cv.base + cv.used;
-        if (!nonlinear(c))
-            gw = *gin;
+        const MargRef<T, NX> none{nullptr, nullptr, 0};
         int rc;
-        if (ck.level == 0) {
-            // every marginal is stored: only the linearisation is redone
-            if (nonlinear(c) && (rc = slr(c, m_nom, N_nom, y, &gw)))
-                return rc;
-            mf = ck.marg;
+        if (ck.marg) {
+            s.marg = marg_ref(ck.marg, c.T_x);
+            rc = filter_walk<true>(c, s, y, s.marg, none, nullptr);
         } else {
-            FElemRef<T, NX> fr = felem_ref(fel, c.T_y);
-            pss_felem el{fr.A, fr.b, fr.U, fr.eta, fr.Z};
-            if ((rc = lin_elements(c, gin, m_nom, N_nom, y, gw, &el)))
-                return rc;
-            // levels under the checkpoint re-run from its prefixes; without
-            // stored prefixes (a level at or above the top) the whole scan
-            if ((rc = fscan(c, &el, mfb, mfb + (size_t)NX * c.T_x, scan_ws, true, false,
-                            ck.level, ck.pre, true)))
-                return rc;
-            mf = mfb;
+            if (ck.pre)
+                s.w.pre[ck.level] = ck.pre;
+            rc = grad_filter<true>(c, s, y, s.marg, ckpt ? nullptr : s.ell,
+                                   ck.pre ? ck.level : 0);
         }
-        return hip_check(hipMemcpyAsync(ll, ck.ll, (size_t)c.B * sizeof(double),
-                                        hipMemcpyDeviceToDevice, c.s),
-                         "checkpoint log-likelihood copy");
+        if (rc)
+            return rc;
+        Carver cv{static_cast<char *>(s.sums)};
+        const auto wa = share_ws<AS>(s.sh, carve_scan<FS>(cv, c, s.sh));
+        const StartPre<T, NX> st{nullptr, nullptr};
+        auto nothing = []() -> int { return PSS_OK; };
+        rc = run_levels<AS, true>(c, s.sh, wa, 0, st, &selem_ref, 0, nothing, nothing, [&]() -> int {
+            KTime kt(c.s, "adjoint_down", "", 0);
+            const auto pre = pre_of(s.sh, wa, 1);
+            using Pre = std::decay_t<decltype(pre)>;
+            hipLaunchKernelGGL((k_adj_down<T, NX, NY, Out, Pre>), dim3((unsigned)s.sh.ntiles[0]),
+                               dim3(s.sh.T[0]), 0, c.s, level_geom(c, s.sh, wa, 0, 0), s.gam,
+                               cptr<T>(y), c.T_y, s.marg, pre, out, prior, wa.elem_off[1]);
+            return hip_check(hipGetLastError(), "adjoint down launch");
+        });
+        if (rc)
+            return rc;
+        return ckpt ? copy_ll(c, ll, ck.ll) : launch_seq_sum(c, 1, s.ell, c.T_y, ll, s.sums);
     }
 
     // gradient with respect to theta (coordinated-turn model) by the
@@ -1015,16 +1130,12 @@ struct Core {
                            double *theta_bar, void *ws)
     {
         if constexpr (NX == 5 && NY == 2) {
-            const size_t scans = std::max({fscan_bytes(c), ascan_bytes(c), seq_sum_bytes(c, 3)});
             Carver tail{static_cast<char *>(ws) + gamma_bytes(c) + felem_bytes(c) +
-                        marg_bytes(c) + align256(c.T_y * sizeof(double)) + scans};
+                        marg_bytes(c) + align256(c.T_y * sizeof(double)) + grad_scans(c, 3)};
             double *gterms = tail.template take<double>((size_t)3 * c.T_y);
             double *gseq = tail.template take<double>((size_t)3 * c.B);
-            Carver cv{static_cast<char *>(ws)};
-            pss_gamma gw;
-            T *mf;
-            void *scan_ws;
-            int rc = grad_forward(c, nullptr, m_nom, N_nom, y, ckpt, ll, cv, gw, mf, scan_ws);
+            GradState s;
+            int rc = grad_state(c, nullptr, m_nom, N_nom, y, ws, s);
             if (rc)
                 return rc;
             const CTHost h = ct_host(c.p);
@@ -1042,11 +1153,11 @@ struct Core {
             out.th.dR = (T)(2.0 * h.sigma * h.sigma);
             out.terms = gterms;
             out.T_y = c.T_y;
-            AdjDst<T, NX> dst{nullptr, nullptr, nullptr, nullptr, c.B};
-            if ((rc = ascan(c, &gw, y, mf, mf + (size_t)NX * c.T_x, out, dst, scan_ws)))
+            const AdjPrior<T, NX> prior{nullptr, nullptr, nullptr, nullptr, c.B};
+            if ((rc = grad_core(c, s, y, ckpt, out, prior, ll)))
                 return rc;
             double *gout = grad ? grad : gseq;
-            if ((rc = launch_seq_sum(c, 3, gterms, c.T_y, gout, scan_ws)))
+            if ((rc = launch_seq_sum(c, 3, gterms, c.T_y, gout, s.sums)))
                 return rc;
             if (theta_bar)
                 rc = launch_weighted_grad(c, gout, ll_bar, theta_bar);
@@ -1064,18 +1175,31 @@ struct Core {
                           const pss_ckpt *ckpt, double *ll, const pss_gamma *gbar, void *m0_bar,
                           void *N0_bar, void *ws)
     {
-        Carver cv{static_cast<char *>(ws)};
-        pss_gamma gw;
-        T *mf;
-        void *scan_ws;
-        int rc = grad_forward(c, gin, m_nom, N_nom, y, ckpt, ll, cv, gw, mf, scan_ws);
+        GradState s;
+        int rc = grad_state(c, gin, m_nom, N_nom, y, ws, s);
         if (rc)
             return rc;
+        // as the smoothed marginals: long outputs are written interleaved (into
+        // the filter elements' space, where that holds them) and copied
+        constexpr int NG = NX * NX + NX + P + NY * NX + NY + PY;
+        const bool direct =
+            NG > Sizes<NX>::felem || (size_t)NG * c.T_y * sizeof(T) <= kDirectBytes;
+        pss_gamma gi{};
+        if (!direct) {
+            gi = carve_gamma_packed(s.fel, c.T_y);
+        }
         GammaOut<T, NX, NY> out;
-        out.bar = gamma_ref(gbar, c.T_y);
+        out.bar = gamma_ref(direct ? gbar : &gi, c.T_y);
         out.w = ll_bar;
-        AdjDst<T, NX> dst{mptr<T>(m0_bar), mptr<T>(N0_bar), cptr<T>(c.p->N0), ll_bar, c.B};
-        return ascan(c, &gw, y, mf, mf + (size_t)NX * c.T_x, out, dst, scan_ws);
+        out.ilv = direct ? 0 : 1;
+        const AdjPrior<T, NX> prior{mptr<T>(m0_bar), mptr<T>(N0_bar), cptr<T>(c.p->N0), ll_bar,
+                                    c.B};
+        if ((rc = grad_core(c, s, y, ckpt, out, prior, ll)) || direct)
+            return rc;
+        hipLaunchKernelGGL((k_gamma_plain<T, NX, NY>), dim3((unsigned)((c.T_y + 255) / 256)),
+                           dim3(256), 0, c.s, c.p->y_off, c.B, c.T_y, out.bar,
+                           gamma_ref(gbar, c.T_y), step_tiles(s.sh));
+        return hip_check(hipGetLastError(), "cotangent layout launch");
     }
 
     // the frozen-nominal score by Fisher's identity from the parallel
@@ -1234,12 +1358,12 @@ int Core<T, NX, NY>::step_lin(const Ctx &c, const NomRef<T, NX> &nom, const void
 {
     const dim3 grid((unsigned)((c.T_y + 255) / 256)), block(256);
     const int lin = c.p->linearization, dev = c.dev_m ? 1 : 0;
-    const int64_t TS = (int64_t)sh.T[0] * sh.E[0];
+    const StepTiles tiles = step_tiles(sh);
     auto run = [&](const auto &l) -> int {
         using Lin = std::decay_t<decltype(l)>;
         KTime kt(c.s, "slr", "", 0);
         hipLaunchKernelGGL((k_step_lin<Lin>), grid, block, 0, c.s, c.p->y_off, c.B, c.T_y, l, nom,
-                           cptr<T>(y), gamma_ref(out, c.T_y), TS, sh.E[0], dev);
+                           cptr<T>(y), gamma_ref(out, c.T_y), tiles, dev);
         return hip_check(hipGetLastError(), "slr launch");
     };
     if constexpr (NX == 5 && NY == 2) {

@@ -474,6 +474,9 @@ struct LevelGeom {
     int E;
     int stage; // outputs staged in LDS and written by the whole block (needs
                // NP * T * E values of LDS)
+    // level 0: sequences of at most n_short elements take E_short
+    int E_short;
+    int64_t n_short;
 };
 
 PSS_INL void seq_range(const LevelGeom &g, int b, int64_t &off, int64_t &cnt)
@@ -534,12 +537,12 @@ PSS_INL TileInfo tile_info(const LevelGeom &g)
     ti.b = find_seq(g.tile_off, g.B, tile, 0);
     const int64_t tin = tile - g.tile_off[ti.b];
     seq_range(g, ti.b, ti.off, ti.cnt);
-    const int64_t TS = (int64_t)blockDim.x * g.E;
+    ti.E = ti.cnt <= g.n_short ? g.E_short : g.E;
+    const int64_t TS = (int64_t)blockDim.x * ti.E;
     ti.start = tin * TS;
     const int64_t rem = ti.cnt - ti.start;
     ti.tcnt = (int)(rem < TS ? rem : TS);
-    ti.nvalid = (ti.tcnt + g.E - 1) / g.E;
-    ti.E = g.E;
+    ti.nvalid = (ti.tcnt + ti.E - 1) / ti.E;
     return ti;
 }
 
@@ -764,22 +767,12 @@ PSS_INL void src_fold(const Src &src, const TileInfo &ti, int64_t p, const V &ac
     }
 }
 
-// A source with fused_down (the adjoint's finest level) applies element p to
-// the prefix itself and may emit per-element results from both.
-template <class S, class = void>
-struct fused_down_of : std::false_type {};
-template <class S>
-struct fused_down_of<S, std::void_t<decltype(S::fused_down)>>
-    : std::integral_constant<bool, S::fused_down> {};
-
 template <class Op, class Src>
 PSS_INL void src_apply(const Src &src, const TileInfo &ti, int64_t p, const typename Op::Pre &P,
                        typename Op::Pre &Q)
 {
     constexpr int nz = leaf_cols<Src, Op::NX>();
-    if constexpr (fused_down_of<Src>::value) {
-        src.down_apply(ti, p, P, Q);
-    } else if constexpr (Src::lazy_down) {
+    if constexpr (Src::lazy_down) {
         Op::template apply_v<nz>(P, src.dview(ti, p), Q);
     } else {
         typename Op::Elem e;
@@ -986,6 +979,7 @@ struct PlanArgs {
     int L;
     int64_t TS[kMaxLevels]; // tile size of level l
     int64_t D[kMaxLevels];  // elements of level l per element of level l + 1
+    int64_t n_short, TS_short, D_short; // level 0 of short sequences (ScanShape)
     int64_t *tile_off[kMaxLevels];
     int64_t *elem_off[kMaxLevels]; // may be null
 };

@@ -343,7 +343,7 @@ PSS_INL void filter_tile(const PArgs<T> &a, const PGroup<T> &G, int64_t gt, T *l
     using Op = FilterScan<T, NX>;
     const int b = find_seq(G.tile_f, G.B, gt, 0);
     const int64_t t = gt - G.tile_f[b];
-    LevelGeom g;
+    LevelGeom g{};
     g.y_off = G.y_off;
     g.elem_off = nullptr;
     g.tile_off = G.tile_f;
@@ -397,7 +397,7 @@ PSS_INL void smoother_tile(const PArgs<T> &a, const PGroup<T> &G, int64_t gu, T 
     using Op = SmootherScan<T, NX>;
     const int b = find_seq(G.tile_s, G.B, gu, 0);
     const int64_t u = gu - G.tile_s[b];
-    LevelGeom g;
+    LevelGeom g{};
     g.y_off = G.y_off;
     g.elem_off = nullptr;
     g.tile_off = G.tile_s;

@@ -50,17 +50,29 @@ struct NomRef {
     }
 };
 
-// stored slot of step k of sequence b for tiles of TS = threads x E steps
-PSS_INL int64_t step_slot(const int64_t *y_off, int b, int64_t k, int64_t TS, int E)
+// tiles of the finest level: T threads of E steps each, E_short for a sequence
+// of at most n_short steps
+struct StepTiles {
+    int T, E, E_short;
+    int64_t n_short;
+    PSS_INL int elems(int64_t n) const { return n <= n_short ? E_short : E; }
+};
+
+// stored slot of step k of sequence b
+PSS_INL int64_t step_slot(const int64_t *y_off, int b, int64_t k, const StepTiles &tl)
 {
-    const int64_t cnt = y_off[b + 1] - y_off[b], start = (k / TS) * TS;
+    const int64_t cnt = y_off[b + 1] - y_off[b];
+    const int E = tl.elems(cnt);
+    const int64_t TS = (int64_t)tl.T * E, start = (k / TS) * TS;
     const int tcnt = (int)(cnt - start < TS ? cnt - start : TS);
     return y_off[b] + start + ilv((int)(k - start), tcnt, E);
 }
 // its inverse: the step stored at slot i
-PSS_INL int64_t slot_step(const int64_t *y_off, int b, int64_t i, int64_t TS, int E)
+PSS_INL int64_t slot_step(const int64_t *y_off, int b, int64_t i, const StepTiles &tl)
 {
-    const int64_t q = i - y_off[b], cnt = y_off[b + 1] - y_off[b], start = (q / TS) * TS;
+    const int64_t q = i - y_off[b], cnt = y_off[b + 1] - y_off[b];
+    const int E = tl.elems(cnt);
+    const int64_t TS = (int64_t)tl.T * E, start = (q / TS) * TS;
     const int tcnt = (int)(cnt - start < TS ? cnt - start : TS);
     return start + ilv_inv((int)(q - start), tcnt, E);
 }
@@ -72,57 +84,6 @@ PSS_INL int64_t agg_slot(const int64_t *next_off, int b, int64_t v, int nT, int 
     const int64_t TS = (int64_t)nT * nE, start = (v / TS) * TS;
     const int tcnt = (int)((cnt - start) < TS ? (cnt - start) : TS);
     return off + start + ilv((int)(v - start), tcnt, nE);
-}
-
-// measurement half of a step: Q = [[H L, S_O], [L, 0]] with L lower, its NY
-// upper rows reduced.  Y = Q[0..NY)[0..NY), P21 = lower rows' first NY columns,
-// a square root of the updated covariance in the NX columns after them.
-template <typename T, int NX, int NY, int R, int C>
-PSS_INL void step_update(const T (&H)[NY][NX], const T (&L)[R][C], const T (&SO)[NY][NY],
-                         T (&Q)[NY + NX][NX + NY])
-{
-#pragma unroll
-    for (int a = 0; a < NY; ++a) {
-#pragma unroll
-        for (int j = 0; j < NX; ++j) {
-            T s = H[a][j] * L[j][j];
-#pragma unroll
-            for (int t = j + 1; t < NX; ++t)
-                s = pfma(H[a][t], L[t][j], s);
-            Q[a][j] = s;
-        }
-#pragma unroll
-        for (int j = 0; j < NY; ++j)
-            Q[a][NX + j] = j <= a ? SO[a][j] : T(0);
-    }
-#pragma unroll
-    for (int i = 0; i < NX; ++i) {
-#pragma unroll
-        for (int j = 0; j < NX; ++j)
-            Q[NY + i][j] = j <= i ? L[i][j] : T(0);
-#pragma unroll
-        for (int j = 0; j < NY; ++j)
-            Q[NY + i][NX + j] = T(0);
-    }
-    lq_rows<NY, NX>(Q);
-}
-
-// x <- Y^{-1} x in place for NC columns (Y the reduced rows of Q)
-template <typename T, int NY, int NC, int R, int C>
-PSS_INL void step_solve(const T (&Q)[R][C], T (&x)[NY][NC])
-{
-#pragma unroll
-    for (int a = 0; a < NY; ++a) {
-        const T inv = prcp(Q[a][a]);
-#pragma unroll
-        for (int j = 0; j < NC; ++j) {
-            T s = x[a][j];
-#pragma unroll
-            for (int t = 0; t < a; ++t)
-                s = pfma(-Q[a][t], x[t][j], s);
-            x[a][j] = s * inv;
-        }
-    }
 }
 
 // where the filter starts: the prior (m0, N0), its mean relative to r_0 in
@@ -475,7 +436,7 @@ __global__ __launch_bounds__(256) void k_step_smooth(LevelGeom g, SElemRef<T, NX
 template <typename T, int NX>
 __global__ __launch_bounds__(256) void k_nominal_plain(const int64_t *y_off, int B, int64_t T_y,
                                                        int64_t T_x, MargRef<T, NX> src,
-                                                       MargRef<T, NX> dst, int64_t TS, int E)
+                                                       MargRef<T, NX> dst, StepTiles tiles)
 {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= T_x)
@@ -483,7 +444,7 @@ __global__ __launch_bounds__(256) void k_nominal_plain(const int64_t *y_off, int
     const int b = find_seq(y_off, B, s, 1);
     const int64_t k = s - y_off[b] - b, n = y_off[b + 1] - y_off[b];
     Marg<T, NX> x;
-    src.load(k < n ? step_slot(y_off, b, k, TS, E) : T_y + b, x);
+    src.load(k < n ? step_slot(y_off, b, k, tiles) : T_y + b, x);
     dst.store(s, x);
 }
 
@@ -491,13 +452,13 @@ __global__ __launch_bounds__(256) void k_nominal_plain(const int64_t *y_off, int
 template <typename T, int NX, int NY>
 __global__ __launch_bounds__(256) void k_gamma_ilv(const int64_t *y_off, int B, int64_t T_y,
                                                    GammaRef<T, NX, NY> src,
-                                                   GammaRef<T, NX, NY> dst, int64_t TS, int E)
+                                                   GammaRef<T, NX, NY> dst, StepTiles tiles)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= T_y)
         return;
     const int b = find_seq(y_off, B, i, 0);
-    const int64_t t = y_off[b] + slot_step(y_off, b, i, TS, E);
+    const int64_t t = y_off[b] + slot_step(y_off, b, i, tiles);
     T F[NX][NX], c[NX], S[NX][NX], H[NY][NX], d[NY], O[NY][NY];
     src.load_trans(t, F, c, S);
     src.load_obs(t, H, d, O);
@@ -514,7 +475,7 @@ __global__ __launch_bounds__(256) void k_step_lin(const int64_t *y_off, int B, i
                                                   Lin lin, NomRef<typename Lin::T, Lin::NX> nom,
                                                   const typename Lin::T *y,
                                                   GammaRef<typename Lin::T, Lin::NX, Lin::NY> out,
-                                                  int64_t TS, int E, int dev)
+                                                  StepTiles tiles, int dev)
 {
     using T = typename Lin::T;
     constexpr int NX = Lin::NX, NY = Lin::NY;
@@ -522,11 +483,11 @@ __global__ __launch_bounds__(256) void k_step_lin(const int64_t *y_off, int B, i
     if (i >= T_y)
         return;
     const int b = find_seq(y_off, B, i, 0);
-    const int64_t n = y_off[b + 1] - y_off[b], k = slot_step(y_off, b, i, TS, E);
+    const int64_t n = y_off[b + 1] - y_off[b], k = slot_step(y_off, b, i, tiles);
     auto at = [&](int64_t s) -> int64_t {
         if (!nom.ilv)
             return y_off[b] + b + s;
-        return s < n ? step_slot(y_off, b, s, TS, E) : T_y + b;
+        return s < n ? step_slot(y_off, b, s, tiles) : T_y + b;
     };
     const int64_t s0 = at(k), s1 = at(k + 1);
     T rk[NX];
