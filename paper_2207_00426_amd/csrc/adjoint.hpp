@@ -56,15 +56,15 @@ template <typename T, int NX>
 struct GroupOp<AdjScan<T, NX>> {
     static constexpr bool value = NX >= 2;
     using Ref = SAosRef<T, NX>;
-    static __device__ __forceinline__ void combine(const T *a, const T *b, T *o,
+    static __device__ __forceinline__ void combine(const double *a, const double *b, double *o,
                                                    const grp::Lane<NX> &ln)
     {
-        grp::adj_combine<T, NX>(b, a, o, ln);
+        grp::adj_combine<double, NX>(b, a, o, ln);
     }
-    static __device__ __forceinline__ void apply(const T *p, const T *a, T *o,
+    static __device__ __forceinline__ void apply(const double *p, const double *a, double *o,
                                                  const grp::Lane<NX> &ln)
     {
-        grp::adj_apply<T, NX>(a, p, o, ln);
+        grp::adj_apply<double, NX>(a, p, o, ln);
     }
 };
 
@@ -432,11 +432,52 @@ __global__ __launch_bounds__(256) void k_filter_walk(LevelGeom g, GammaRef<T, NX
                           view_of(agg, agg_slot(next_off, ti.b, cnt1 - 1 - v, nT, nE)));
 }
 
+// the maps of a thread's steps folded from stored marginals, everything in the
+// plain layout (FP32)
+template <typename T, int NX, int NY, class AggRef>
+__global__ __launch_bounds__(256) void k_adj_fold(LevelGeom g, GammaRef<T, NX, NY> gam,
+                                                  const T *y, int64_t T_y, MargRef<T, NX> marg,
+                                                  AggRef agg, const int64_t *next_off, int nT,
+                                                  int nE)
+{
+    const TileInfo ti = tile_info(g);
+    if ((int)threadIdx.x >= ti.nvalid)
+        return;
+    const int64_t p0 = ti.start + (int64_t)threadIdx.x * ti.E;
+    int64_t pe = p0 + ti.E;
+    if (pe > ti.start + ti.tcnt)
+        pe = ti.start + ti.tcnt;
+    const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
+    SElem<T, NX> a;
+    for (int64_t p = p0; p < pe; ++p) {
+        const int64_t t = ti.off + p;
+        T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
+        gam.load_trans(t, F, c, SL);
+        gam.load_obs(t, H, d, SO);
+#pragma unroll
+        for (int q = 0; q < NY; ++q)
+            yy[q] = y[q * T_y + t];
+        Marg<T, NX> f;
+        marg.load(t + ti.b, f);
+        StepQ<T, NX, NY> q;
+        T Np[NX][NX], P22[NX][NX], mp[NX];
+        adj_step(F, c, SL, H, d, SO, yy, f, q, Np, P22, mp);
+        SElem<T, NX> e;
+        adj_element(F, q, e);
+        if (p == p0)
+            a = e;
+        else
+            adj_combine_v<T, NX>(SRegV<T, NX>{&a}, SRegV<T, NX>{&e}, SRegV<T, NX>{&a});
+    }
+    selem_copy<T, NX>(SRegV<T, NX>{&a},
+                      view_of(agg, agg_slot(next_off, ti.b, cnt1 - 1 - v, nT, nE)));
+}
+
 template <typename T, int NX, int NY, class Out, class PreRef>
 __global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, NY> gam,
                                                   const T *y, int64_t T_y, MargRef<T, NX> marg,
                                                   PreRef pre, Out out, AdjPrior<T, NX> prior,
-                                                  const int64_t *next_off)
+                                                  const int64_t *next_off, int plain)
 {
     const TileInfo ti = tile_info(g);
     if ((int)threadIdx.x >= ti.nvalid)
@@ -449,7 +490,7 @@ __global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, N
     Marg<T, NX> lam;
     pre.load(next_off[ti.b] + cnt1 - 1 - v, lam);
     for (int64_t p = pe - 1; p >= p0; --p) {
-        const int64_t u = ilv_slot(ti, p), ug = gam.stride ? u : 0;
+        const int64_t u = plain ? ti.off + p : ilv_slot(ti, p), ug = gam.stride ? u : 0;
         T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
         gam.load_trans(ug, F, c, SL);
         gam.load_obs(ug, H, d, SO);
@@ -457,7 +498,7 @@ __global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, N
         for (int a = 0; a < NY; ++a)
             yy[a] = y[a * T_y + ti.off + p];
         Marg<T, NX> f, o;
-        marg.load(u, f); // state p, before the step
+        marg.load(plain ? u + ti.b : u, f); // state p, before the step
         StepQ<T, NX, NY> q;
         T Np[NX][NX], P22[NX][NX], mp[NX];
         adj_step(F, c, SL, H, d, SO, yy, f, q, Np, P22, mp);

@@ -14,8 +14,14 @@
 //
 // Operands and results are elements in LDS, all components of one element
 // contiguous in the component order of visit(); a call reads every operand
-// before it writes, so the output may be an operand's storage.
+// before it writes, so the output may be an operand's storage.  The arithmetic
+// is FP64 also for FP32 scans, whose elements are widened on their way into
+// LDS: an FP32 row would be scaled before its reflection, which costs more
+// than FP64's rate, and the long spans these levels combine are where FP32
+// rounding is worst.
 #pragma once
+
+#include <type_traits>
 
 #include "device_ops.hpp"
 
@@ -26,12 +32,6 @@ constexpr int kLanes = 16;
 
 // value of x in lane L of this lane's group
 template <int L>
-__device__ __forceinline__ float bc(float x)
-{
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + L, 0xf, 0xf, true));
-}
-template <int L>
 __device__ __forceinline__ double bc(double x)
 {
     return __longlong_as_double(
@@ -39,13 +39,6 @@ __device__ __forceinline__ double bc(double x)
 }
 // lane L for the lower half, lane 8 + L for the upper half (bank mask 0xc:
 // the second move writes lanes 8-15 only)
-template <int L>
-__device__ __forceinline__ float bc2(float x)
-{
-    const int v = __float_as_int(x);
-    const int lo = __builtin_amdgcn_update_dpp(0, v, 0x150 + L, 0xf, 0xf, true);
-    return __int_as_float(__builtin_amdgcn_update_dpp(lo, v, 0x150 + 8 + L, 0xf, 0xc, false));
-}
 template <int L>
 __device__ __forceinline__ double bc2(double x)
 {
@@ -92,7 +85,6 @@ struct Lane {
 template <int K, int Z0, bool Two, typename T, int C>
 __device__ __forceinline__ void lq(T (&row)[C], int rho, T (&inv)[K])
 {
-    constexpr bool kScale = sizeof(T) == 4;
     each<K>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         constexpr int jend = cmin(C, Z0 + i + 1);
@@ -104,17 +96,6 @@ __device__ __forceinline__ void lq(T (&row)[C], int rho, T (&inv)[K])
             else
                 x[j] = bc<i>(row[j]);
         }
-        int ex = 0;
-        if constexpr (kScale) {
-            T sc = pabs(x[i]);
-#pragma unroll
-            for (int j = i + 1; j < jend; ++j)
-                sc = pmax(sc, pabs(x[j]));
-            ex = pexp(sc);
-#pragma unroll
-            for (int j = i; j < jend; ++j)
-                x[j] = pldexp(x[j], -ex);
-        }
         T sig = T(0);
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
@@ -122,7 +103,7 @@ __device__ __forceinline__ void lq(T (&row)[C], int rho, T (&inv)[K])
         T beta, tau, d;
         bool neg;
         reflector(x[i], sig, beta, tau, d, neg);
-        inv[i] = kScale ? pldexp(tau * beta, -ex) : tau * beta;
+        inv[i] = tau * beta;
         // every row takes the reflection: on a row that is already reduced it
         // reaches only columns right of that row's diagonal, which are stale
         const T ap = pflip(row[i], neg);
@@ -132,7 +113,7 @@ __device__ __forceinline__ void lq(T (&row)[C], int rho, T (&inv)[K])
             w = pfma(row[j], x[j], w);
         const T tw = tau * w;
         const T nw = pfma(tw, beta, ap);
-        row[i] = rho == i ? (kScale ? pldexp(d, ex) : d) : nw;
+        row[i] = rho == i ? d : nw;
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
             row[j] = pfma(-tw, x[j], row[j]);

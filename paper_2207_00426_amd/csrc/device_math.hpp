@@ -67,7 +67,7 @@ PSS_INL float pldexp(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 // of Lemmas 1-3), the sweep never touches those columns.  Z0 = C disables
 // the shortcut.
 //
-// Reflector of row x = (a, t) (pivot a, tail t, s = |x|^2, r = |x|): the
+// Reflector of row x = (a, t) (pivot a, tail t, s = |x|^2, r = |x|), FP64: the
 // pivot entry of v is a + sign(a) r, so nothing cancels and its size beta =
 // |a| + r serves both signs; v = (sign(a) beta, t), |v|^2 = 2 r beta, and the
 // reflection I - tau v v^T with tau = 1 / (r beta) maps x to (-sign(a) r, 0,
@@ -78,11 +78,18 @@ PSS_INL float pldexp(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 // and a correctly rounded root costs twice the estimate's steps: a row's
 // scalar chain was ~45 instructions, now ~22; together with the reflections
 // that Table 3 no longer runs, one smoothing pass of 30 011 FP64 steps fell from
-// 456 to 404 us, of 10^6 steps from 1886 to 1778 us).  In FP32 each row is first
-// scaled by a power of two near its largest magnitude, so squares neither
-// overflow nor fall into the subnormal range; FP64's exponent range makes that
-// unnecessary for these models.  A row of zeros (or whose squares vanish) is
-// left alone; a NaN goes through to the diagonal.
+// 456 to 404 us, of 10^6 steps from 1886 to 1778 us).
+//
+// FP32 keeps the pivot a - r, taken as -s_t / (a + r) for a > 0 (s_t = |t|^2),
+// the rounded root and a threshold under which a tail leaves a positive pivot
+// alone: where the tail is small the FP64 form rebuilds the rows below from
+// two parts of their size, which loses a few ulp that FP32 results show (their
+// error against 64 bits rose 1.7 times on a batch of short tracks).  Each FP32
+// row is first scaled by a power of two near its largest magnitude, so squares
+// neither overflow nor fall into the subnormal range.
+//
+// A row of zeros (or whose squares vanish) is left alone; a NaN goes through
+// to the diagonal.
 // --------------------------------------------------------------------------
 template <typename T> struct Eps;
 template <> struct Eps<double> { static constexpr double v = 2.220446049250313e-16; };
@@ -93,9 +100,9 @@ PSS_INL float pabs(float x) { return fabsf(x); }
 PSS_INL double pmax(double a, double b) { return fmax(a, b); }
 PSS_INL float pmax(float a, float b) { return fmaxf(a, b); }
 
-// sqrt(s) to ~1 ulp for normal s > 0: reciprocal-root estimate, one coupled
-// Newton step for root and half reciprocal root (FP64 only; the estimate has
-// ~2^-23 relative error), one residual correction
+// sqrt(s) to ~1 ulp for normal s > 0: reciprocal-root estimate (~2^-23
+// relative error), one coupled Newton step for root and half reciprocal root,
+// one residual correction
 template <typename T>
 PSS_INL T pnorm(T s) { return psqrt(s); }
 template <>
@@ -107,13 +114,6 @@ PSS_INL double pnorm(double s)
     g = fma(g, e, g);
     h = fma(h, e, h);
     return fma(fma(-g, g, s), h, g);
-}
-template <>
-PSS_INL float pnorm(float s)
-{
-    const float r = __builtin_amdgcn_rsqf(s);
-    const float g = s * r, h = 0.5f * r;
-    return fmaf(fmaf(-g, g, s), h, g);
 }
 
 // x with its sign flipped where neg
@@ -137,7 +137,7 @@ PSS_INL double pflip(double x, bool neg)
 template <typename T>
 PSS_INL void reflector(T al, T sig, T &beta, T &tau, T &d, bool &neg)
 {
-    constexpr double tiny = sizeof(T) == 4 ? 1e-30 : 1e-290;
+    constexpr double tiny = 1e-290;
     const T s = pfma(al, al, sig);
     const T on = s > T(tiny) ? T(1) : T(0);
     const T nr = pnorm(pmax(s, T(tiny)));
@@ -147,6 +147,19 @@ PSS_INL void reflector(T al, T sig, T &beta, T &tau, T &d, bool &neg)
     d = pfma(nr, on, s - s);
     beta = pfma(aa, on, d);
     neg = al > T(0);
+}
+template <>
+PSS_INL void reflector(float al, float sig, float &beta, float &tau, float &d, bool &neg)
+{
+    const float nr = psqrt(pfma(al, al, sig));
+    const float v0 = (al > 0.0f) ? -sig * prcp(al + nr) : (al - nr);
+    const float p = nr * v0;
+    const bool skip =
+        !(p < 0.0f) || (al > 0.0f && sig <= Eps<float>::v * Eps<float>::v * al * al);
+    tau = skip ? 0.0f : -prcp(p);
+    beta = -v0;
+    d = (skip && al > 0.0f) ? al : nr;
+    neg = false;
 }
 
 template <int K, int Z0, typename T, int R, int C>

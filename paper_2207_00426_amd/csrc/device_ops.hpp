@@ -491,8 +491,10 @@ PSS_INL void filter_combine_v(const VI &ei, const VJ &ej, const VO &o)
     // Xi's upper rows only: its lower right block enters through its Gram
     // matrix alone (Z below), so the rows left there by the first NX
     // reflections serve as they are, NX x NZ and dense, and the other NX
-    // reflections of the printed Tria need not run
-    lq_rows<NX, NZ>(M);
+    // reflections of the printed Tria need not run.  (FP32 runs them: its
+    // log-likelihoods keep every rounding they had.)
+    constexpr bool kTri = sizeof(T) == 4;
+    lq_rows<kTri ? cmin(2 * NX, C) : NX, NZ>(M);
     // Tm = U_i Xi11^{-T}, G = I - Tm Xi21^T
     T Tm[NX][NX], G[NX][NX];
     {
@@ -567,9 +569,10 @@ PSS_INL void filter_combine_v(const VI &ei, const VJ &ej, const VO &o)
         for (int a = 0; a < NX; ++a)
 #pragma unroll
             for (int c = 0; c < NZ; ++c) {
-                T s = Ai[0][a] * M[NX][NX + c];
+                const int t0 = kTri ? c : 0; // lower trapezoidal then
+                T s = Ai[t0][a] * M[NX + t0][NX + c];
 #pragma unroll
-                for (int t = 1; t < NX; ++t)
+                for (int t = t0 + 1; t < NX; ++t)
                     s = pfma(Ai[t][a], M[NX + t][NX + c], s);
                 AX[a][c] = s;
             }

@@ -66,6 +66,9 @@ struct Core {
     static constexpr int PY = tri_size(NY);
     static constexpr bool kFlatF = Defaults<T, NX>::flat_filter;
     static constexpr bool kFlatS = Defaults<T, NX>::flat_smoother;
+    // log-likelihoods from Kalman steps; FP32 keeps the scan over elements
+    // (see FilterScanLane)
+    static constexpr bool kStepsLL = sizeof(T) == 8;
 
     // ------------------------------------------------------------------
     static void shapes(const Ctx &c, bool smoother, int &T0, int &E0, int &Tup, int &E1,
@@ -378,7 +381,7 @@ struct Core {
     template <class Op, bool Flat, class Src0, class Dst0, class AggRef, class Start>
     static int run_scan(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int extra,
                         const Src0 &src0, const Dst0 &dst0, const Start &start,
-                        AggRef (*agg_ref)(T *, int64_t))
+                        AggRef (*agg_ref)(T *, int64_t), int stop = 0)
     {
         int rc = launch_plan(c, sh, extra, w.tile_off, w.elem_off);
         if (rc)
@@ -435,7 +438,7 @@ struct Core {
             hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, dst0, w.tree[0], tree_ld, pin);
             return hip_check(hipGetLastError(), "scan down launch");
         };
-        return run_levels<Op, Flat>(c, sh, w, extra, start, agg_ref, 0, up0, top0, down0);
+        return run_levels<Op, Flat>(c, sh, w, extra, start, agg_ref, stop, up0, top0, down0);
     }
 
     // ------------------------------------------------------------------
@@ -506,6 +509,35 @@ struct Core {
         }
         RefSrc<FS, FElemRef<T, NX>, false, LZ> src{er};
         return run_scan<FS, kFlatF>(c, sh, w, 0, src, dst, st, &felem_ref);
+    }
+
+    // the filter scan of a log-likelihood over stored (interleaved) elements,
+    // one element per lane at every level.  ck_pre: the exclusive prefixes of
+    // level ck_level (1 <= ck_level < levels) -- written there by a full scan,
+    // or, with resume, read from there and only the levels below re-run
+    static int fscan_lane(const Ctx &c, const pss_felem *el, void *mf, void *Nf, void *ws,
+                          int ck_level, T *ck_pre, bool resume)
+    {
+        using FL = FilterScanLane<T, NX>;
+        const ScanShape sh = filter_shape(c);
+        Carver cv{static_cast<char *>(ws)};
+        auto w = carve_scan<FL>(cv, c, sh);
+        const bool ck = ck_pre && ck_level >= 1 && ck_level < sh.L;
+        if (ck)
+            w.pre[ck_level] = ck_pre;
+        FElemRef<T, NX> er;
+        er.A = mptr<T>(el->A);
+        er.b = mptr<T>(el->b);
+        er.U = mptr<T>(el->U);
+        er.eta = mptr<T>(el->eta);
+        er.Z = mptr<T>(el->Z);
+        er.ld = c.T_y;
+        FiltDst<T, NX> dst{marg_ref2(mf, Nf, c.T_x), c.p->y_off};
+        StartPre<T, NX> st{cptr<T>(c.p->m0), cptr<T>(c.p->N0)};
+        constexpr int LZ = NY < NX ? NY : NX;
+        RefSrc<FL, FElemRef<T, NX>, true, LZ> src{er};
+        return run_scan<FL, kFlatF>(c, sh, w, 0, src, dst, st, &felem_ref,
+                                    ck && resume ? ck_level : 0);
     }
 
     static int sscan(const Ctx &c, const pss_gamma *g, const void *mf, const void *Nf, void *ms,
@@ -675,7 +707,7 @@ struct Core {
         v.ll = cv.template take<double>((size_t)c.B);
         if (ck->level == 0)
             v.marg = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
-        else if (ck->level < grad_shape(c).L)
+        else if (ck->level < (kStepsLL ? grad_shape(c).L : filter_shape(c).L))
             v.pre = cv.template take<T>(0);
         return v;
     }
@@ -704,7 +736,9 @@ struct Core {
     // walks are longer per step and their scans above cheaper, so 8 steps pay
     // only on long sequences (us per gradient at 4 and 8 steps, FP64: 1 x 1500
     // 210 and 220, 8 x 6000 of a linear model 253 and 313, 1 x 10^4 227 and 274,
-    // 64 x 10^4 889 and 806).
+    // 64 x 10^4 889 and 806).  FP32 folds 2: its marginals and linearisation are
+    // in the plain layout, read E numbers apart (64 x 10^4: at 4 steps the two
+    // passes over them take 300 us, at 2 192).
     static ScanShape grad_shape(const Ctx &c)
     {
         int T0, E0, Tup, E1, Eup;
@@ -712,6 +746,8 @@ struct Core {
         if (c.p->scan_elems > 0)
             return plan_scan(c, 0, T0, E0, Tup, E1, Eup, true);
         using D = Defaults<T, NX>;
+        if (!kStepsLL)
+            return plan_scan(c, 0, T0, 2, Tup, E1, Eup, true);
         return plan_scan(c, 0, T0, std::max(4, D::E0_step), Tup, E1, Eup, true,
                          std::max(4, D::E0_step_short), 8192);
     }
@@ -935,11 +971,13 @@ struct Core {
         return PSS_OK;
     }
 
-    // filter pass over stored elements: the covariance form's log-likelihood
-    // and the score by Fisher's identity; returns the carved state
+    // Filter pass over stored elements: the covariance form's and FP32's
+    // log-likelihood, and the score by Fisher's identity; returns the carved
+    // state.  With a checkpoint (FP32) the filtering marginals go to it (level
+    // 0) or the scan's level-`level` prefixes do.
     static int loglik_core(const Ctx &c, const pss_gamma *gin, const void *m_nom,
                            const void *N_nom, const void *y, double *ll, Carver &cv,
-                           pss_gamma &gw, T *&mfb, void *&scan_ws)
+                           pss_gamma &gw, T *&mfb, void *&scan_ws, const CkView &ck = CkView{})
     {
         gw = carve_gamma(cv, c.T_y);
         T *fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
@@ -949,13 +987,20 @@ struct Core {
         if (!nonlinear(c))
             gw = *gin;
         const pss_gamma *g = &gw;
+        if (ck.marg)
+            mfb = ck.marg;
         FElemRef<T, NX> fr = felem_ref(fel, c.T_y);
         pss_felem el{fr.A, fr.b, fr.U, fr.eta, fr.Z};
         int rc;
         const bool cov = c.p->form == PSS_FORM_COV;
         if ((rc = lin_elements(c, gin, m_nom, N_nom, y, gw, &el)))
             return rc;
-        if ((rc = fscan(c, &el, mfb, mfb + (size_t)NX * c.T_x, scan_ws, true, cov)))
+        T *Nfb = mfb + (size_t)NX * c.T_x;
+        if (!kStepsLL && !cov)
+            rc = fscan_lane(c, &el, mfb, Nfb, scan_ws, ck.level, ck.pre, false);
+        else
+            rc = fscan(c, &el, mfb, Nfb, scan_ws, true, cov);
+        if (rc)
             return rc;
         const int tb = 128;
         {
@@ -986,6 +1031,7 @@ struct Core {
         MargRef<T, NX> marg; // filtering marginals, state k at the slot of step k + 1
         double *ell;
         void *sums;
+        int plain = 0; // FP32: linearisation and marginals in the plain layout
     };
     static int grad_state(const Ctx &c, const pss_gamma *gin, const void *m_nom,
                           const void *N_nom, const void *y, void *ws, GradState &s)
@@ -1056,18 +1102,19 @@ struct Core {
     static int loglik(const Ctx &c, const pss_gamma *gin, const void *m_nom, const void *N_nom,
                       const void *y, double *ll, const pss_ckpt *ckpt, void *ws)
     {
-        if (c.p->form == PSS_FORM_COV) {
+        const CkView ck = ckpt_view(c, ckpt);
+        int rc;
+        if (c.p->form == PSS_FORM_COV || !kStepsLL) {
             Carver cv{static_cast<char *>(ws)};
             pss_gamma gw;
             T *mfb;
             void *scan_ws;
-            return loglik_core(c, gin, m_nom, N_nom, y, ll, cv, gw, mfb, scan_ws);
+            rc = loglik_core(c, gin, m_nom, N_nom, y, ll, cv, gw, mfb, scan_ws, ck);
+            return rc || !ckpt ? rc : copy_ll(c, ck.ll, ll);
         }
         GradState s;
-        int rc = grad_state(c, gin, m_nom, N_nom, y, ws, s);
-        if (rc)
+        if ((rc = grad_state(c, gin, m_nom, N_nom, y, ws, s)))
             return rc;
-        const CkView ck = ckpt_view(c, ckpt);
         MargRef<T, NX> out{nullptr, nullptr, 0};
         if (ck.marg)
             out = marg_ref(ck.marg, c.T_x);
@@ -1080,27 +1127,87 @@ struct Core {
         return ckpt ? copy_ll(c, ck.ll, ll) : PSS_OK;
     }
 
-    // reverse pass: the filtering marginals and the maps' level-1 aggregates
-    // from a checkpoint (re-running what it does not hold) or a full filter
-    // pass, the scan of the maps, the cotangents of every step; ll last (its
-    // sums use the scans' space)
+    // forward half of a gradient: the filtering marginals and the maps'
+    // level-1 aggregates from a checkpoint (re-running what it does not hold)
+    // or a full filter pass
+    static int grad_forward(const Ctx &c, const pss_gamma *gin, const void *m_nom,
+                            const void *N_nom, const void *y, const pss_ckpt *ckpt, double *ll,
+                            void *ws, GradState &s)
+    {
+        const CkView ck = ckpt_view(c, ckpt);
+        int rc;
+        if constexpr (kStepsLL) {
+            if ((rc = grad_state(c, gin, m_nom, N_nom, y, ws, s)))
+                return rc;
+            if (ck.marg) {
+                s.marg = marg_ref(ck.marg, c.T_x);
+                const MargRef<T, NX> none{nullptr, nullptr, 0};
+                return filter_walk<true>(c, s, y, s.marg, none, nullptr);
+            }
+            if (ck.pre)
+                s.w.pre[ck.level] = ck.pre;
+            return grad_filter<true>(c, s, y, s.marg, ckpt ? nullptr : s.ell,
+                                     ck.pre ? ck.level : 0);
+        } else {
+            // over stored elements, as FP32's log-likelihood; then the maps
+            // from the marginals
+            Carver cv{static_cast<char *>(ws)};
+            T *mf;
+            if (!ckpt) {
+                rc = loglik_core(c, gin, m_nom, N_nom, y, ll, cv, s.gw, mf, s.sums);
+                s.fel = nullptr;
+            } else {
+                s.gw = carve_gamma(cv, c.T_y);
+                s.fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
+                mf = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
+                cv.template take<double>((size_t)c.T_y);
+                s.sums = cv.base + cv.used;
+                if (!nonlinear(c))
+                    s.gw = *gin;
+                if (ck.marg) { // only the linearisation is redone
+                    mf = ck.marg;
+                    rc = nonlinear(c) ? slr(c, m_nom, N_nom, y, &s.gw) : PSS_OK;
+                } else {
+                    FElemRef<T, NX> fr = felem_ref(s.fel, c.T_y);
+                    pss_felem el{fr.A, fr.b, fr.U, fr.eta, fr.Z};
+                    if ((rc = lin_elements(c, gin, m_nom, N_nom, y, s.gw, &el)))
+                        return rc;
+                    rc = fscan_lane(c, &el, mf, mf + (size_t)NX * c.T_x, s.sums, ck.level,
+                                    ck.pre, true);
+                }
+            }
+            if (rc)
+                return rc;
+            s.plain = 1;
+            s.gam = gamma_ref(&s.gw, c.T_y);
+            s.marg = marg_ref(mf, c.T_x);
+            s.sh = grad_shape(c);
+            Carver cs{static_cast<char *>(s.sums)};
+            s.w = carve_scan<FS>(cs, c, s.sh);
+            if ((rc = launch_plan(c, s.sh, 0, s.w.tile_off, s.w.elem_off)))
+                return rc;
+            KTime kt(c.s, "adjoint_fold", "", 0);
+            using AS = AdjScan<T, NX>;
+            const auto agg = agg_of(s.sh, share_ws<AS>(s.sh, s.w), 1, &selem_ref);
+            using Agg = std::decay_t<decltype(agg)>;
+            hipLaunchKernelGGL((k_adj_fold<T, NX, NY, Agg>), dim3((unsigned)s.sh.ntiles[0]),
+                               dim3(s.sh.T[0]), 0, c.s, level_geom(c, s.sh, s.w, 0, 0), s.gam,
+                               cptr<T>(y), c.T_y, s.marg, agg, s.w.elem_off[1], s.sh.T[1],
+                               agg_ilv<AS>(s.sh));
+            return hip_check(hipGetLastError(), "adjoint fold launch");
+        }
+    }
+
+    // the gradient's reverse pass: the scan of the maps, the cotangents of
+    // every step; ll last (its sums use the scans' space)
     template <class Out>
-    static int grad_core(const Ctx &c, GradState &s, const void *y, const pss_ckpt *ckpt,
-                         const Out &out, const AdjPrior<T, NX> &prior, double *ll)
+    static int grad_core(const Ctx &c, const pss_gamma *gin, const void *m_nom,
+                         const void *N_nom, const void *y, const pss_ckpt *ckpt, GradState &s,
+                         const Out &out, const AdjPrior<T, NX> &prior, double *ll, void *ws)
     {
         using AS = AdjScan<T, NX>;
         const CkView ck = ckpt_view(c, ckpt);
-        const MargRef<T, NX> none{nullptr, nullptr, 0};
-        int rc;
-        if (ck.marg) {
-            s.marg = marg_ref(ck.marg, c.T_x);
-            rc = filter_walk<true>(c, s, y, s.marg, none, nullptr);
-        } else {
-            if (ck.pre)
-                s.w.pre[ck.level] = ck.pre;
-            rc = grad_filter<true>(c, s, y, s.marg, ckpt ? nullptr : s.ell,
-                                   ck.pre ? ck.level : 0);
-        }
+        int rc = grad_forward(c, gin, m_nom, N_nom, y, ckpt, ll, ws, s);
         if (rc)
             return rc;
         Carver cv{static_cast<char *>(s.sums)};
@@ -1113,12 +1220,15 @@ struct Core {
             using Pre = std::decay_t<decltype(pre)>;
             hipLaunchKernelGGL((k_adj_down<T, NX, NY, Out, Pre>), dim3((unsigned)s.sh.ntiles[0]),
                                dim3(s.sh.T[0]), 0, c.s, level_geom(c, s.sh, wa, 0, 0), s.gam,
-                               cptr<T>(y), c.T_y, s.marg, pre, out, prior, wa.elem_off[1]);
+                               cptr<T>(y), c.T_y, s.marg, pre, out, prior, wa.elem_off[1],
+                               s.plain);
             return hip_check(hipGetLastError(), "adjoint down launch");
         });
         if (rc)
             return rc;
-        return ckpt ? copy_ll(c, ll, ck.ll) : launch_seq_sum(c, 1, s.ell, c.T_y, ll, s.sums);
+        if (ckpt)
+            return copy_ll(c, ll, ck.ll);
+        return kStepsLL ? launch_seq_sum(c, 1, s.ell, c.T_y, ll, s.sums) : PSS_OK;
     }
 
     // gradient with respect to theta (coordinated-turn model) by the
@@ -1135,9 +1245,7 @@ struct Core {
             double *gterms = tail.template take<double>((size_t)3 * c.T_y);
             double *gseq = tail.template take<double>((size_t)3 * c.B);
             GradState s;
-            int rc = grad_state(c, nullptr, m_nom, N_nom, y, ws, s);
-            if (rc)
-                return rc;
+            int rc;
             const CTHost h = ct_host(c.p);
             ThetaOut<T, NX, NY> out;
             for (int i = 0; i < 5; ++i)
@@ -1154,7 +1262,7 @@ struct Core {
             out.terms = gterms;
             out.T_y = c.T_y;
             const AdjPrior<T, NX> prior{nullptr, nullptr, nullptr, nullptr, c.B};
-            if ((rc = grad_core(c, s, y, ckpt, out, prior, ll)))
+            if ((rc = grad_core(c, nullptr, m_nom, N_nom, y, ckpt, s, out, prior, ll, ws)))
                 return rc;
             double *gout = grad ? grad : gseq;
             if ((rc = launch_seq_sum(c, 3, gterms, c.T_y, gout, s.sums)))
@@ -1176,17 +1284,17 @@ struct Core {
                           void *N0_bar, void *ws)
     {
         GradState s;
-        int rc = grad_state(c, gin, m_nom, N_nom, y, ws, s);
-        if (rc)
-            return rc;
         // as the smoothed marginals: long outputs are written interleaved (into
         // the filter elements' space, where that holds them) and copied
         constexpr int NG = NX * NX + NX + P + NY * NX + NY + PY;
-        const bool direct =
-            NG > Sizes<NX>::felem || (size_t)NG * c.T_y * sizeof(T) <= kDirectBytes;
+        const bool direct = !kStepsLL || NG > Sizes<NX>::felem ||
+                            (size_t)NG * c.T_y * sizeof(T) <= kDirectBytes;
         pss_gamma gi{};
         if (!direct) {
-            gi = carve_gamma_packed(s.fel, c.T_y);
+            Carver cv{static_cast<char *>(ws)};
+            carve_gamma(cv, c.T_y);
+            gi = carve_gamma_packed(
+                cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y), c.T_y);
         }
         GammaOut<T, NX, NY> out;
         out.bar = gamma_ref(direct ? gbar : &gi, c.T_y);
@@ -1194,7 +1302,8 @@ struct Core {
         out.ilv = direct ? 0 : 1;
         const AdjPrior<T, NX> prior{mptr<T>(m0_bar), mptr<T>(N0_bar), cptr<T>(c.p->N0), ll_bar,
                                     c.B};
-        if ((rc = grad_core(c, s, y, ckpt, out, prior, ll)) || direct)
+        int rc = grad_core(c, gin, m_nom, N_nom, y, ckpt, s, out, prior, ll, ws);
+        if (rc || direct)
             return rc;
         hipLaunchKernelGGL((k_gamma_plain<T, NX, NY>), dim3((unsigned)((c.T_y + 255) / 256)),
                            dim3(256), 0, c.s, c.p->y_off, c.B, c.T_y, out.bar,

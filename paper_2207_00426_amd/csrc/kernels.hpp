@@ -291,6 +291,13 @@ struct FilterScan {
     }
 };
 
+// The same operators with one element per lane at every level.  FP32
+// log-likelihoods run it: they come back in FP64 with FP32 rounding in them,
+// and a change of bracketing or of an operator's order of sums would show in
+// digits that callers may compare.
+template <typename T_, int NX_>
+struct FilterScanLane : FilterScan<T_, NX_> {};
+
 // Reverse associative scan of the smoother, run as a forward scan over the
 // time-reversed elements with the arguments of the operator swapped.
 template <typename T_, int NX_>

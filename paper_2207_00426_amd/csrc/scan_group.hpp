@@ -62,30 +62,30 @@ template <typename T, int NX>
 struct GroupOp<FilterScan<T, NX>> {
     static constexpr bool value = NX >= 2;
     using Ref = FAosRef<T, NX>;
-    static __device__ __forceinline__ void combine(const T *a, const T *b, T *o,
+    static __device__ __forceinline__ void combine(const double *a, const double *b, double *o,
                                                    const grp::Lane<NX> &ln)
     {
-        grp::filter_combine<T, NX>(a, b, o, ln);
+        grp::filter_combine<double, NX>(a, b, o, ln);
     }
-    static __device__ __forceinline__ void apply(const T *p, const T *a, T *o,
+    static __device__ __forceinline__ void apply(const double *p, const double *a, double *o,
                                                  const grp::Lane<NX> &ln)
     {
-        grp::filter_apply<T, NX>(p, a, o, ln);
+        grp::filter_apply<double, NX>(p, a, o, ln);
     }
 };
 template <typename T, int NX>
 struct GroupOp<SmootherScan<T, NX>> {
     static constexpr bool value = NX >= 2;
     using Ref = SAosRef<T, NX>;
-    static __device__ __forceinline__ void combine(const T *a, const T *b, T *o,
+    static __device__ __forceinline__ void combine(const double *a, const double *b, double *o,
                                                    const grp::Lane<NX> &ln)
     {
-        grp::smoother_combine<T, NX>(b, a, o, ln);
+        grp::smoother_combine<double, NX>(b, a, o, ln);
     }
-    static __device__ __forceinline__ void apply(const T *p, const T *a, T *o,
+    static __device__ __forceinline__ void apply(const double *p, const double *a, double *o,
                                                  const grp::Lane<NX> &ln)
     {
-        grp::smoother_apply<T, NX>(a, p, o, ln);
+        grp::smoother_apply<double, NX>(a, p, o, ln);
     }
 };
 
@@ -94,21 +94,23 @@ template <typename T, int N>
 struct GroupMove {
     static constexpr int K = (N + grp::kLanes - 1) / grp::kLanes;
     T v[K];
-    __device__ __forceinline__ void load(const T *p)
+    template <typename S>
+    __device__ __forceinline__ void load(const S *p)
     {
         const int l = threadIdx.x & (grp::kLanes - 1);
 #pragma unroll
         for (int k = 0; k < K; ++k)
             if (l + k * grp::kLanes < N)
-                v[k] = p[l + k * grp::kLanes];
+                v[k] = T(p[l + k * grp::kLanes]);
     }
-    __device__ __forceinline__ void store(T *p) const
+    template <typename D>
+    __device__ __forceinline__ void store(D *p) const
     {
         const int l = threadIdx.x & (grp::kLanes - 1);
 #pragma unroll
         for (int k = 0; k < K; ++k)
             if (l + k * grp::kLanes < N)
-                p[l + k * grp::kLanes] = v[k];
+                p[l + k * grp::kLanes] = D(v[k]);
     }
 };
 
@@ -141,8 +143,7 @@ __device__ __forceinline__ GroupTile group_tile(const GroupGeom &g)
 // inclusive prefix of group g within the tile; ends with a block barrier
 template <class Op>
 __device__ __forceinline__ void group_up(const GroupTile &ti, const typename Op::T *elems,
-                                         typename Op::T *acc, typename Op::T *in,
-                                         const grp::Lane<Op::NX> &ln)
+                                         double *acc, double *in, const grp::Lane<Op::NX> &ln)
 {
     using T = typename Op::T;
     constexpr int NE = Op::NE;
@@ -150,7 +151,7 @@ __device__ __forceinline__ void group_up(const GroupTile &ti, const typename Op:
     if (g < ti.nvalid) {
         const int p0 = g * ti.E, pe = p0 + ti.E < ti.cnt ? p0 + ti.E : ti.cnt;
         const T *src = elems + (ti.first + p0) * NE;
-        T *a = acc + g * NE, *x = in + g * NE;
+        double *a = acc + g * NE, *x = in + g * NE;
         GroupMove<T, NE> mv;
         mv.load(src);
         mv.store(a);
@@ -179,8 +180,8 @@ __device__ __forceinline__ void group_up(const GroupTile &ti, const typename Op:
 // the group's start prefix p (in LDS), then its elements' exclusive prefixes
 template <class Op>
 __device__ __forceinline__ void group_walk(const GroupTile &ti, const typename Op::T *elems,
-                                           typename Op::T *pre_out, typename Op::T *p,
-                                           typename Op::T *x, const grp::Lane<Op::NX> &ln)
+                                           typename Op::T *pre_out, double *p, double *x,
+                                           const grp::Lane<Op::NX> &ln)
 {
     using T = typename Op::T;
     constexpr int NE = Op::NE, NP = Op::NP;
@@ -192,7 +193,7 @@ __device__ __forceinline__ void group_walk(const GroupTile &ti, const typename O
     if (p0 + 1 < pe)
         mv.load(src);
     for (int q = p0;; ++q) {
-        GroupMove<T, NP> out;
+        GroupMove<double, NP> out;
         out.load(p);
         out.store(dst);
         if (q + 1 >= pe)
@@ -216,15 +217,15 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_up(GroupGeom gm,
                                                             typename Op::T *incl)
 {
     using T = typename Op::T;
-    __shared__ T acc[kGroups * Op::NE], in[kGroups * Op::NE];
+    __shared__ double acc[kGroups * Op::NE], in[kGroups * Op::NE];
     const grp::Lane<Op::NX> ln;
     const GroupTile ti = group_tile(gm);
     group_up<Op>(ti, elems, acc, in, ln);
     T *out = incl + (int64_t)blockIdx.x * kGroups * Op::NE;
     for (int i = threadIdx.x; i < ti.nvalid * Op::NE; i += kGroupThreads)
-        out[i] = acc[i];
+        out[i] = T(acc[i]);
     for (int i = threadIdx.x; i < Op::NE; i += kGroupThreads)
-        agg[(int64_t)blockIdx.x * Op::NE + i] = acc[(ti.nvalid - 1) * Op::NE + i];
+        agg[(int64_t)blockIdx.x * Op::NE + i] = T(acc[(ti.nvalid - 1) * Op::NE + i]);
 }
 
 // lower levels, second half
@@ -236,13 +237,13 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_down(GroupGeom gm,
                                                               typename Op::T *pre_out)
 {
     using T = typename Op::T;
-    __shared__ T pre[kGroups * Op::NP], in[kGroups * Op::NE];
+    __shared__ double pre[kGroups * Op::NP], in[kGroups * Op::NE];
     const grp::Lane<Op::NX> ln;
     const GroupTile ti = group_tile(gm);
     const int g = threadIdx.x / grp::kLanes;
     if (g >= ti.nvalid)
         return;
-    T *p = pre + g * Op::NP, *x = in + g * Op::NE;
+    double *p = pre + g * Op::NP, *x = in + g * Op::NE;
     GroupMove<T, Op::NP> root;
     root.load(pre_in + (int64_t)blockIdx.x * Op::NP);
     root.store(p);
@@ -265,18 +266,18 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_top(GroupGeom gm,
                                                              Start start)
 {
     using T = typename Op::T;
-    __shared__ T acc[kGroups * Op::NE], in[kGroups * Op::NE], pre[kGroups * Op::NP];
+    __shared__ double acc[kGroups * Op::NE], in[kGroups * Op::NE], pre[kGroups * Op::NP];
     const grp::Lane<Op::NX> ln;
     const GroupTile ti = group_tile(gm);
     group_up<Op>(ti, elems, acc, in, ln);
     const int g = threadIdx.x / grp::kLanes;
     if (g >= ti.nvalid)
         return;
-    T *p = pre + g * Op::NP, *x = in + g * Op::NE;
+    double *p = pre + g * Op::NP, *x = in + g * Op::NE;
     if ((threadIdx.x & (grp::kLanes - 1)) == 0) {
         Marg<T, Op::NX> s;
         start.get(s);
-        visit(s, [&](int c, T &v) { p[c] = v; });
+        visit(s, [&](int c, T &v) { p[c] = double(v); });
     }
     grp::lds_order();
     if (g > 0)

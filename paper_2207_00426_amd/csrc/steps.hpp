@@ -86,6 +86,39 @@ PSS_INL int64_t agg_slot(const int64_t *next_off, int b, int64_t v, int nT, int 
     return off + start + ilv((int)(v - start), tcnt, nE);
 }
 
+// The steps' arithmetic is FP64 for FP32 storage too: a step then needs no
+// scaling of its rows, which cost FP32 more than its faster rate gave back, and
+// the only rounding to FP32 is of what is stored.
+using StepT = double;
+
+template <typename T, int NX, typename W>
+PSS_INL void marg_cast(const Marg<T, NX> &a, Marg<W, NX> &o)
+{
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+        o.m[i] = W(a.m[i]);
+#pragma unroll
+        for (int j = 0; j <= i; ++j)
+            o.N[i][j] = W(a.N[i][j]);
+    }
+}
+
+template <typename T, int NX, int NY, typename W>
+PSS_INL void load_obs_w(const GammaRef<T, NX, NY> &gam, int64_t u, W (&H)[NY][NX], W (&d)[NY],
+                        W (&SO)[NY][NY])
+{
+#pragma unroll
+    for (int a = 0; a < NY; ++a) {
+#pragma unroll
+        for (int j = 0; j < NX; ++j)
+            H[a][j] = W(gam.H[(a * NX + j) * gam.ld + u]);
+        d[a] = W(gam.d[a * gam.ld + u]);
+#pragma unroll
+        for (int j = 0; j <= a; ++j)
+            SO[a][j] = W(gam.SO[tri_idx(a, j) * gam.ld + u]);
+    }
+}
+
 // where the filter starts: the prior (m0, N0), its mean relative to r_0 in
 // deviation coordinates
 template <typename T, int NX>
@@ -107,6 +140,7 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
                                                    AggRef agg, const int64_t *next_off, int nT,
                                                    int nE)
 {
+    using W = StepT;
     const TileInfo ti = tile_info(g);
     if ((int)threadIdx.x >= ti.nvalid)
         return;
@@ -114,14 +148,14 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
     int64_t pe = p0 + ti.E;
     if (pe > ti.start + ti.tcnt)
         pe = ti.start + ti.tcnt;
-    FElem<T, NX> e; // U dense between steps
+    FElem<W, NX> e; // U dense between steps
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-        e.b[i] = e.eta[i] = T(0);
+        e.b[i] = e.eta[i] = W(0);
 #pragma unroll
         for (int j = 0; j < NX; ++j) {
-            e.A[i][j] = (i == j) ? T(1) : T(0);
-            e.U[i][j] = e.Z[i][j] = T(0);
+            e.A[i][j] = (i == j) ? W(1) : W(0);
+            e.U[i][j] = e.Z[i][j] = W(0);
         }
     }
     if (p0 == 0) { // the sequence's first thread: a true prefix (A = 0)
@@ -129,7 +163,7 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
             e.b[i] = prior.mean(i, s0);
-            e.A[i][i] = T(0);
+            e.A[i][i] = W(0);
 #pragma unroll
             for (int j = 0; j <= i; ++j)
                 e.U[i][j] = prior.N0[tri_idx(i, j)];
@@ -137,20 +171,20 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
     }
     for (int64_t p = p0; p < pe; ++p) {
         const int64_t u = gam.stride ? ilv_slot(ti, p) : 0;
-        T M[NX][2 * NX];
+        W M[NX][2 * NX];
         {
-            T F[NX][NX];
+            W F[NX][NX];
 #pragma unroll
             for (int i = 0; i < NX; ++i)
 #pragma unroll
                 for (int j = 0; j < NX; ++j)
-                    F[i][j] = gam.F[(i * NX + j) * gam.ld + u];
-            T FA[NX][NX], Fb[NX];
+                    F[i][j] = W(gam.F[(i * NX + j) * gam.ld + u]);
+            W FA[NX][NX], Fb[NX];
             mm(F, e.A, FA);
             mv(F, e.b, Fb);
 #pragma unroll
             for (int i = 0; i < NX; ++i) {
-                e.b[i] = Fb[i] + gam.c[i * gam.ld + u];
+                e.b[i] = Fb[i] + W(gam.c[i * gam.ld + u]);
 #pragma unroll
                 for (int j = 0; j < NX; ++j)
                     e.A[i][j] = FA[i][j];
@@ -159,33 +193,34 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
             for (int i = 0; i < NX; ++i)
 #pragma unroll
                 for (int j = 0; j < NX; ++j) {
-                    T s = F[i][0] * e.U[0][j];
+                    W s = F[i][0] * e.U[0][j];
 #pragma unroll
                     for (int t = 1; t < NX; ++t)
                         s = pfma(F[i][t], e.U[t][j], s);
                     M[i][j] = s;
-                    M[i][NX + j] = j <= i ? gam.SL[tri_idx(i, j <= i ? j : i) * gam.ld + u] : T(0);
+                    M[i][NX + j] =
+                        j <= i ? W(gam.SL[tri_idx(i, j <= i ? j : i) * gam.ld + u]) : W(0);
                 }
         }
         lq_rows<NX, NX>(M);
-        T H[NY][NX], d[NY], SO[NY][NY];
-        gam.load_obs(gam.stride ? u : 0, H, d, SO);
-        T Q[NY + NX][NX + NY];
+        W H[NY][NX], d[NY], SO[NY][NY];
+        load_obs_w(gam, u, H, d, SO);
+        W Q[NY + NX][NX + NY];
         step_update(H, M, SO, Q);
         // G = Y^{-1} H A, w = Y^{-1} (y - H b - d)
-        T G[NY][NX], w[NY][1];
+        W G[NY][NX], w[NY][1];
         mm(H, e.A, G);
 #pragma unroll
         for (int a = 0; a < NY; ++a) {
-            T s = y[a * T_y + ti.off + p] - d[a];
+            W s = W(y[a * T_y + ti.off + p]) - d[a];
 #pragma unroll
             for (int j = 0; j < NX; ++j)
                 s = pfma(-H[a][j], e.b[j], s);
             w[a][0] = s;
         }
-        step_solve<T, NY, NX>(Q, G);
-        step_solve<T, NY, 1>(Q, w);
-        T Gt[NX][NY];
+        step_solve<W, NY, NX>(Q, G);
+        step_solve<W, NY, 1>(Q, w);
+        W Gt[NX][NY];
 #pragma unroll
         for (int i = 0; i < NX; ++i)
 #pragma unroll
@@ -198,14 +233,14 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
         for (int i = 0; i < NX; ++i)
 #pragma unroll
             for (int j = 0; j < NX; ++j) {
-                T s = e.A[i][j];
+                W s = e.A[i][j];
 #pragma unroll
                 for (int a = 0; a < NY; ++a)
                     s = pfma(-Q[NY + i][a], G[a][j], s);
                 e.A[i][j] = s;
                 e.U[i][j] = Q[NY + i][NY + j];
             }
-        T Zn[NX][NX];
+        W Zn[NX][NX];
         tria_cols_lower(Gt, e.Z, Zn);
 #pragma unroll
         for (int i = 0; i < NX; ++i)
@@ -214,7 +249,7 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
                 e.Z[i][j] = Zn[i][j];
     }
     {
-        T Un[NX][NX];
+        W Un[NX][NX];
         tria_rect(e.U, Un);
 #pragma unroll
         for (int i = 0; i < NX; ++i)
@@ -223,7 +258,7 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
                 e.U[i][j] = Un[i][j];
     }
     const int64_t v = ti.start / ti.E + threadIdx.x;
-    felem_copy<T, NX>(FRegV<T, NX>{&e}, view_of(agg, agg_slot(next_off, ti.b, v, nT, nE)));
+    felem_copy<W, NX>(FRegV<W, NX>{&e}, view_of(agg, agg_slot(next_off, ti.b, v, nT, nE)));
 }
 
 // filtering marginals on request: state k of sequence b at plain slot
@@ -237,6 +272,7 @@ __global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, 
                                                    MargRef<T, NX> filt, const int64_t *next_off,
                                                    int nT, int nE)
 {
+    using W = StepT;
     const TileInfo ti = tile_info(g);
     if ((int)threadIdx.x >= ti.nvalid)
         return;
@@ -245,7 +281,7 @@ __global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, 
     if (pe > ti.start + ti.tcnt)
         pe = ti.start + ti.tcnt;
     const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
-    T m[NX], N[NX][NX]; // N dense between steps
+    W m[NX], N[NX][NX]; // N dense between steps
     {
         Marg<T, NX> f;
         if (p0 == 0) {
@@ -264,48 +300,48 @@ __global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, 
         }
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
-            m[i] = f.m[i];
+            m[i] = W(f.m[i]);
 #pragma unroll
             for (int j = 0; j < NX; ++j)
-                N[i][j] = j <= i ? f.N[i][j] : T(0);
+                N[i][j] = j <= i ? W(f.N[i][j]) : W(0);
         }
     }
-    SElem<T, NX> a; // the thread's smoother aggregate
+    SElem<W, NX> a; // the thread's smoother aggregate
     for (int64_t p = p0; p < pe; ++p) {
         const int64_t u = ilv_slot(ti, p), ug = gam.stride ? u : 0;
         // [[F N, S_L], [N, 0]], upper rows reduced: N^- = M11, E = M21 M11^{-1},
         // D D^T = M22 M22^T (Table 4)
-        T M[2 * NX][2 * NX], mp[NX];
+        W M[2 * NX][2 * NX], mp[NX];
         {
-            T F[NX][NX];
+            W F[NX][NX];
 #pragma unroll
             for (int i = 0; i < NX; ++i)
 #pragma unroll
                 for (int j = 0; j < NX; ++j)
-                    F[i][j] = gam.F[(i * NX + j) * gam.ld + ug];
+                    F[i][j] = W(gam.F[(i * NX + j) * gam.ld + ug]);
             mv(F, m, mp);
 #pragma unroll
             for (int i = 0; i < NX; ++i) {
-                mp[i] += gam.c[i * gam.ld + ug];
+                mp[i] += W(gam.c[i * gam.ld + ug]);
 #pragma unroll
                 for (int j = 0; j < NX; ++j) {
-                    T s = F[i][0] * N[0][j];
+                    W s = F[i][0] * N[0][j];
 #pragma unroll
                     for (int t = 1; t < NX; ++t)
                         s = pfma(F[i][t], N[t][j], s);
                     M[i][j] = s;
                     M[i][NX + j] =
-                        j <= i ? gam.SL[tri_idx(i, j <= i ? j : i) * gam.ld + ug] : T(0);
+                        j <= i ? W(gam.SL[tri_idx(i, j <= i ? j : i) * gam.ld + ug]) : W(0);
                     M[NX + i][j] = N[i][j];
-                    M[NX + i][NX + j] = T(0);
+                    M[NX + i][NX + j] = W(0);
                 }
             }
         }
         lq_rows<NX, NX>(M);
         {
-            SElem<T, NX> e;
+            SElem<W, NX> e;
             {
-                T P11[NX][NX], P21[NX][NX], P22[NX][NX];
+                W P11[NX][NX], P21[NX][NX], P22[NX][NX];
 #pragma unroll
                 for (int i = 0; i < NX; ++i)
 #pragma unroll
@@ -319,31 +355,31 @@ __global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, 
             }
 #pragma unroll
             for (int i = 0; i < NX; ++i) {
-                T s = m[i];
+                W s = m[i];
 #pragma unroll
                 for (int j = 0; j < NX; ++j)
                     s = pfma(-e.E[i][j], mp[j], s);
                 e.g[i] = s;
             }
-            stash.store(u, e);
+            selem_copy<W, NX>(SRegV<W, NX>{&e}, view_of(stash, u));
             if (p == p0)
                 a = e;
             else
-                smoother_combine_v<T, NX>(SRegV<T, NX>{&a}, SRegV<T, NX>{&e}, SRegV<T, NX>{&a});
+                smoother_combine_v<W, NX>(SRegV<W, NX>{&a}, SRegV<W, NX>{&e}, SRegV<W, NX>{&a});
         }
-        T H[NY][NX], d[NY], SO[NY][NY];
-        gam.load_obs(ug, H, d, SO);
-        T Q[NY + NX][NX + NY], w[NY][1];
+        W H[NY][NX], d[NY], SO[NY][NY];
+        load_obs_w(gam, ug, H, d, SO);
+        W Q[NY + NX][NX + NY], w[NY][1];
         step_update(H, M, SO, Q);
 #pragma unroll
         for (int q = 0; q < NY; ++q) {
-            T s = y[q * T_y + ti.off + p] - d[q];
+            W s = W(y[q * T_y + ti.off + p]) - d[q];
 #pragma unroll
             for (int j = 0; j < NX; ++j)
                 s = pfma(-H[q][j], mp[j], s);
             w[q][0] = s;
         }
-        step_solve<T, NY, 1>(Q, w);
+        step_solve<W, NY, 1>(Q, w);
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
             m[i] = mp[i];
@@ -355,38 +391,40 @@ __global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, 
                 N[i][j] = Q[NY + i][NY + j];
         }
         if (filt.m) {
-            Marg<T, NX> f;
+            Marg<W, NX> f;
+            Marg<T, NX> o;
             tria_rect(N, f.N);
 #pragma unroll
             for (int i = 0; i < NX; ++i)
                 f.m[i] = m[i];
-            filt.store(ti.off + ti.b + p + 1, f);
+            marg_cast(f, o);
+            filt.store(ti.off + ti.b + p + 1, o);
         }
     }
     if (v == cnt1 - 1) {
         // the sequence's end: the filtering marginal of state n is the
         // smoother's start (its element {0, m, N}), folded in here
-        Marg<T, NX> f, o;
+        Marg<W, NX> f, o;
         tria_rect(N, f.N);
 #pragma unroll
         for (int i = 0; i < NX; ++i)
             f.m[i] = m[i];
         T *q = last.p + (int64_t)ti.b * Sizes<NX>::marg;
-        visit(f, [&](int c, T &x) { q[c] = x; });
+        visit(f, [&](int c, W &x) { q[c] = T(x); });
         smoother_apply(a, f, o);
 #pragma unroll
         for (int i = 0; i < NX; ++i) {
             a.g[i] = o.m[i];
 #pragma unroll
             for (int j = 0; j < NX; ++j) {
-                a.E[i][j] = T(0);
+                a.E[i][j] = W(0);
                 if (j <= i)
                     a.D[i][j] = o.N[i][j];
             }
         }
     }
     // the smoother scans backwards: its element cnt1 - 1 - v
-    selem_copy<T, NX>(SRegV<T, NX>{&a},
+    selem_copy<W, NX>(SRegV<W, NX>{&a},
                       view_of(agg, agg_slot(next_off, ti.b, cnt1 - 1 - v, nT, nE)));
 }
 
@@ -396,6 +434,7 @@ __global__ __launch_bounds__(256) void k_step_smooth(LevelGeom g, SElemRef<T, NX
                                                      NomRef<T, NX> dev, NomRef<T, NX> out,
                                                      const int64_t *next_off)
 {
+    using W = StepT;
     const TileInfo ti = tile_info(g);
     if ((int)threadIdx.x >= ti.nvalid)
         return;
@@ -404,29 +443,33 @@ __global__ __launch_bounds__(256) void k_step_smooth(LevelGeom g, SElemRef<T, NX
     if (pe > ti.start + ti.tcnt)
         pe = ti.start + ti.tcnt;
     const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
-    Marg<T, NX> s;
+    Marg<W, NX> s;
     // deviation coordinates: the stored mean is r_k plus the deviation
-    auto put = [&](int64_t k, const Marg<T, NX> &x) {
+    auto put = [&](int64_t k, const Marg<W, NX> &x) {
         const int64_t at = out.slot(g.y_off, ti, k);
-        Marg<T, NX> o = x;
+        Marg<T, NX> o;
+        marg_cast(x, o);
         if (dev.r.m) {
             const int64_t rk = dev.slot(g.y_off, ti, k);
 #pragma unroll
             for (int i = 0; i < NX; ++i)
-                o.m[i] += dev.r.m[i * dev.r.ld + rk];
+                o.m[i] = T(x.m[i] + W(dev.r.m[i * dev.r.ld + rk]));
         }
         out.r.store(at, o);
     };
+    Marg<T, NX> s0;
     if (v == cnt1 - 1) {
-        last.load(ti.b, s);
+        last.load(ti.b, s0);
+        marg_cast(s0, s);
         put(ti.cnt, s);
     } else {
-        pre.load(next_off[ti.b] + cnt1 - 1 - v, s);
+        pre.load(next_off[ti.b] + cnt1 - 1 - v, s0);
+        marg_cast(s0, s);
     }
     for (int64_t p = pe - 1; p >= p0; --p) {
         const auto e = view_of(stash, ilv_slot(ti, p));
-        Marg<T, NX> o;
-        smoother_apply_v<T, NX>(e, s, o);
+        Marg<W, NX> o;
+        smoother_apply_v<W, NX>(e, s, o);
         s = o;
         put(p, s);
     }
