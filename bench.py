@@ -76,7 +76,7 @@ from paper_2207_00426_amd import workloads as wl  # noqa: E402
 # T_k; adjoint_cotangents: the Gram cotangents and the theta contraction.
 FLOPS = dict(filter_combine=3310, filter_combine_leaf=2517, filter_apply=1940,
              filter_apply_leaf=1432, smoother_combine=750, smoother_apply=525,
-             filter_element=1310, smoother_element=1545, slr_transition=1989, slr_bearings=441,
+             filter_element=1310, smoother_element=1545, slr_transition=1518, slr_bearings=323,
              adjoint_element=1272, adjoint_combine=740, adjoint_apply=515,
              adjoint_cotangents=966)
 PEAK = {"f64": 78.6, "f32": 78.6}  # TFLOP/s vector ALU (FP32 without packed instructions)

@@ -1220,12 +1220,10 @@ PSS_INL void ct_phi_mean(const CTParams<T> &P, const Marg<T, 5> &mg, CTPhiMean<T
 // s2 = dt (a/2) sinc(a/2)^2, the differences of s1 and s2 come from dsinc
 // and the rest is products of the offsets.
 template <typename T>
-PSS_INL void ct_phi_dev(const CTParams<T> &P, const CTPhiMean<T> &b, T dvx, T dvy, T dw,
-                        T (&e)[5])
+PSS_INL void ct_phi_dev(const CTParams<T> &P, const CTPhiMean<T> &b, T dvx, T dvy, T dw, T da,
+                        T dsa, T dS, T (&e)[5])
 {
-    const T da = dw * P.dt;
-    const T ds1 = P.dt * dsinc(b.a, da);
-    const T dS = dsinc(T(0.5) * b.a, T(0.5) * da), S1 = b.S + dS;
+    const T ds1 = P.dt * dsa, S1 = b.S + dS;
     const T ds2 = P.dt * (T(0.5) * da * S1 * S1 + T(0.5) * b.a * dS * (S1 + b.S));
     const T s1 = b.s1 + ds1, s2 = b.s2 + ds2;
     e[0] = s1 * dvx - s2 * dvy + ds1 * b.vx - ds2 * b.vy;
@@ -1236,23 +1234,78 @@ PSS_INL void ct_phi_dev(const CTParams<T> &P, const CTPhiMean<T> &b, T dvx, T dv
 }
 
 template <typename T>
+PSS_INL void ct_phi_dev(const CTParams<T> &P, const CTPhiMean<T> &b, T dvx, T dvy, T dw,
+                        T (&e)[5])
+{
+    const T da = dw * P.dt;
+    ct_phi_dev(P, b, dvx, dvy, dw, da, dsinc(b.a, da), dsinc(T(0.5) * b.a, T(0.5) * da), e);
+}
+
+// dsinc(x, d) for many d at one x, |x| and |x + d| below 1/2: the differenced
+// series, as a polynomial in (x + d)^2 whose coefficients depend on x alone
+// (g_j = sum of c_k (x^2)^(k-1-j) over k > j).  A step then takes 11 operations
+// where dsinc, which carries both squares through the sum, takes some 45.
+template <typename T>
+struct DSincAt {
+    static constexpr int n = SincTerms<T>::n;
+    T x, g[n];
+    PSS_INL explicit DSincAt(T x_) : x(x_)
+    {
+        const T u = x * x;
+        g[n - 1] = T(sinc_coef(n));
+#pragma unroll
+        for (int j = n - 2; j >= 0; --j)
+            g[j] = pfma(u, g[j + 1], T(sinc_coef(j + 1)));
+    }
+    PSS_INL T operator()(T d) const
+    {
+        const T x1 = x + d, u1 = x1 * x1;
+        T s = g[n - 1];
+#pragma unroll
+        for (int j = n - 2; j >= 0; --j)
+            s = pfma(u1, s, g[j]);
+        return d * (x1 + x) * s;
+    }
+};
+
+// SHARE: the turn angles' sinc differences from one expansion at the mean when
+// every sigma point turns by less than 1/2 in a step, which is nearly always.
+// (FP32 log-likelihoods keep dsinc, whose rounding they would show.)
+template <typename T, bool SHARE = (sizeof(T) == 8)>
 PSS_INL void ct_slr_transition(const CTParams<T> &P, const Marg<T, 5> &mg, T (&F)[5][5],
                                T (&c)[5], T (&S)[5][5])
 {
     CTPhiMean<T> b;
     ct_phi_mean(P, mg, b);
     T ep[5][5], em[5][5];
+    auto points = [&](auto &&dsa, auto &&dsh) {
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        T dlt[5], zp[5], zm[5];
-        sigma_offset(mg, i, dlt);
-        ct_phi_dev(P, b, dlt[2], dlt[3], dlt[4], zp);
-        ct_phi_dev(P, b, -dlt[2], -dlt[3], -dlt[4], zm);
+        for (int i = 0; i < 5; ++i) {
+            T dlt[5], zp[5], zm[5];
+            sigma_offset(mg, i, dlt);
+            const T da = dlt[4] * P.dt, ha = T(0.5) * da;
+            ct_phi_dev(P, b, dlt[2], dlt[3], dlt[4], da, dsa(da), dsh(ha), zp);
+            ct_phi_dev(P, b, -dlt[2], -dlt[3], -dlt[4], -da, dsa(-da), dsh(-ha), zm);
 #pragma unroll
-        for (int a = 0; a < 5; ++a) {
-            ep[a][i] = zp[a];
-            em[a][i] = zm[a];
+            for (int a = 0; a < 5; ++a) {
+                ep[a][i] = zp[a];
+                em[a][i] = zm[a];
+            }
         }
+    };
+    T far = T(0);
+    if constexpr (SHARE) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+            far = pmax(far, pabs(mg.N[4][i]));
+        far = pabs(b.a) + psqrt(T(5)) * far * pabs(P.dt);
+    }
+    if (SHARE && far < T(0.5)) {
+        const DSincAt<T> dsa(b.a), dsh(T(0.5) * b.a);
+        points(dsa, dsh);
+    } else {
+        points([&](T d) { return dsinc(b.a, d); },
+               [&](T d) { return dsinc(T(0.5) * b.a, d); });
     }
     cubature_from_dev(mg, P.LQ, ep, em, b.phi, F, c, S);
 #pragma unroll
@@ -1283,21 +1336,29 @@ PSS_INL void ct_slr_bearings(const CTParams<T> &P, const Marg<T, 5> &mg, const T
         W D0 = patan2(uy, ux) - W(y[q]);
         D0 = D0 - tp * pfloor((D0 + pi) / tp);
         r[q] = T(W(y[q]) + D0);
+        // 0, or not a number where the nominal or y is not finite
+        const W zero = (ux - ux) + (uy - uy) + (D0 - D0);
+        // branch jumps of D0 + angle back into [-pi, pi): both lie within one
+        // turn of it, so the jump is a comparison, not a division
+        auto branch = [&](W ang) {
+            const W t = D0 + ang;
+            return T(ang - (pi <= t ? tp : (t < -pi ? -tp : zero)));
+        };
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
+        for (int i = 0; i < 2; ++i) {
             // position part of column i of sqrt(nx) N (lower: rows >= i)
             const W d0 = (i == 0) ? sq * W(mg.N[0][0]) : W(0);
-            const W d1 = (i <= 1) ? sq * W(mg.N[1][i]) : W(0);
+            const W d1 = sq * W(mg.N[1][i]);
             const W cr = ux * d1 - uy * d0;
             const W dt = ux * d0 + uy * d1;
-            const W ap = patan2(cr, r2 + dt);
-            const W am = patan2(-cr, r2 - dt);
-            // branch jumps of D0 + angle back into [-pi, pi)
-            const W kp = pfloor((D0 + ap + pi) / tp);
-            const W km = pfloor((D0 + am + pi) / tp);
-            ep[q][i] = T(ap - tp * kp);
-            em[q][i] = T(am - tp * km);
+            ep[q][i] = branch(patan2(cr, r2 + dt));
+            em[q][i] = branch(patan2(-cr, r2 - dt));
         }
+        // the columns that do not move the position: their angle is zero
+        const T e0 = branch(zero);
+#pragma unroll
+        for (int i = 2; i < 5; ++i)
+            ep[q][i] = em[q][i] = e0;
     }
     const T Sn[2][2] = {{P.sigma, T(0)}, {T(0), P.sigma}};
     cubature_from_dev(mg, Sn, ep, em, r, H, d, S);

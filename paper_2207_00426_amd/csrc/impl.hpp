@@ -1465,7 +1465,7 @@ template <typename T, int NX, int NY>
 int Core<T, NX, NY>::step_lin(const Ctx &c, const NomRef<T, NX> &nom, const void *y,
                               const pss_gamma *out, const ScanShape &sh)
 {
-    const dim3 grid((unsigned)((c.T_y + 255) / 256)), block(256);
+    const dim3 grid((unsigned)((c.T_y + 255) / 256), 2), block(256);
     const int lin = c.p->linearization, dev = c.dev_m ? 1 : 0;
     const StepTiles tiles = step_tiles(sh);
     auto run = [&](const auto &l) -> int {

@@ -58,12 +58,21 @@ struct StepTiles {
     PSS_INL int elems(int64_t n) const { return n <= n_short ? E_short : E; }
 };
 
+// k / TS of a step index, in 32 bits wherever k fits (a 64-bit division takes
+// some forty instructions more)
+PSS_INL int64_t tile_of(int64_t k, int64_t TS)
+{
+    if (((k | TS) >> 32) == 0)
+        return (int64_t)((uint32_t)k / (uint32_t)TS);
+    return k / TS;
+}
+
 // stored slot of step k of sequence b
 PSS_INL int64_t step_slot(const int64_t *y_off, int b, int64_t k, const StepTiles &tl)
 {
     const int64_t cnt = y_off[b + 1] - y_off[b];
     const int E = tl.elems(cnt);
-    const int64_t TS = (int64_t)tl.T * E, start = (k / TS) * TS;
+    const int64_t TS = (int64_t)tl.T * E, start = tile_of(k, TS) * TS;
     const int tcnt = (int)(cnt - start < TS ? cnt - start : TS);
     return y_off[b] + start + ilv((int)(k - start), tcnt, E);
 }
@@ -72,7 +81,7 @@ PSS_INL int64_t slot_step(const int64_t *y_off, int b, int64_t i, const StepTile
 {
     const int64_t q = i - y_off[b], cnt = y_off[b + 1] - y_off[b];
     const int E = tl.elems(cnt);
-    const int64_t TS = (int64_t)tl.T * E, start = (q / TS) * TS;
+    const int64_t TS = (int64_t)tl.T * E, start = tile_of(q, TS) * TS;
     const int tcnt = (int)(cnt - start < TS ? cnt - start : TS);
     return start + ilv_inv((int)(q - start), tcnt, E);
 }
@@ -81,7 +90,7 @@ PSS_INL int64_t slot_step(const int64_t *y_off, int b, int64_t i, const StepTile
 PSS_INL int64_t agg_slot(const int64_t *next_off, int b, int64_t v, int nT, int nE)
 {
     const int64_t off = next_off[b], cnt = next_off[b + 1] - off;
-    const int64_t TS = (int64_t)nT * nE, start = (v / TS) * TS;
+    const int64_t TS = (int64_t)nT * nE, start = tile_of(v, TS) * TS;
     const int tcnt = (int)((cnt - start) < TS ? (cnt - start) : TS);
     return off + start + ilv((int)(v - start), tcnt, nE);
 }
@@ -509,10 +518,14 @@ __global__ __launch_bounds__(256) void k_gamma_ilv(const int64_t *y_off, int B, 
     dst.store_obs(i, H, d, O);
 }
 
-// Linearisation of every step into its interleaved slot, one thread per stored
-// slot: the transition at state k, the measurement at state k + 1.  A block
-// covers whole tiles, so the strided reads of neighbouring states meet in one
-// cache.  Lin: trans(marginal, F, c, S_L) and obs(marginal, y, H, d, S_O).
+// Linearisation of every step into its interleaved slot, two threads per stored
+// slot in blocks of their own: the transition at state k (blockIdx.y = 0) and
+// the measurement at state k + 1 (1).  They share nothing but the index, and one
+// after the other they made a chain of some 4000 instructions, all there is to a
+// short sequence's launch.  A block takes 256 steps that follow each other, so
+// that it reads a plain nominal's lines once, and its lanes follow the slots: a
+// run of 256 / E lanes stores whole lines.
+// Lin: trans(marginal, F, c, S_L) and obs(marginal, y, H, d, S_O).
 template <class Lin>
 __global__ __launch_bounds__(256) void k_step_lin(const int64_t *y_off, int B, int64_t T_y,
                                                   Lin lin, NomRef<typename Lin::T, Lin::NX> nom,
@@ -522,42 +535,50 @@ __global__ __launch_bounds__(256) void k_step_lin(const int64_t *y_off, int B, i
 {
     using T = typename Lin::T;
     constexpr int NX = Lin::NX, NY = Lin::NY;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t base = (int64_t)blockIdx.x * 256;
+    int64_t i = base + threadIdx.x;
+    int b = find_seq(y_off, B, base, 0); // the block's first; the threads go on from it
+    if (base + 256 <= T_y) { // the steps E apart side by side
+        const int E = tiles.elems(y_off[b + 1] - y_off[b]);
+        if ((E & (E - 1)) == 0 && E <= 16) {
+            const int run = 256 / E;
+            i = base + (threadIdx.x & (run - 1)) * E + threadIdx.x / run;
+        }
+    }
     if (i >= T_y)
         return;
-    const int b = find_seq(y_off, B, i, 0);
-    const int64_t n = y_off[b + 1] - y_off[b], k = slot_step(y_off, b, i, tiles);
-    auto at = [&](int64_t s) -> int64_t {
-        if (!nom.ilv)
-            return y_off[b] + b + s;
-        return s < n ? step_slot(y_off, b, s, tiles) : T_y + b;
-    };
-    const int64_t s0 = at(k), s1 = at(k + 1);
-    T rk[NX];
-    {
-        Marg<T, NX> mg;
+    while (y_off[b + 1] <= i)
+        ++b;
+    const int64_t n = y_off[b + 1] - y_off[b], k = i - y_off[b];
+    const int64_t u = step_slot(y_off, b, k, tiles);
+    // state k: in tile order it has the step's slot
+    const int64_t s0 = nom.ilv ? u : i + b;
+    const int64_t s1 = !nom.ilv ? s0 + 1
+                       : k + 1 < n ? step_slot(y_off, b, k + 1, tiles)
+                                   : T_y + b;
+    Marg<T, NX> mg;
+    if (blockIdx.y == 0) {
         nom.r.load(s0, mg);
         T F[NX][NX], c[NX], S[NX][NX];
         lin.trans(mg, F, c, S);
         if (dev) {
+            T rk[NX];
 #pragma unroll
             for (int q = 0; q < NX; ++q)
                 rk[q] = nom.r.m[q * nom.r.ld + s1];
             dev_trans_offset(F, mg.m, rk, c);
         }
-        out.store_trans(i, F, c, S);
-    }
-    {
-        Marg<T, NX> mg;
+        out.store_trans(u, F, c, S);
+    } else {
         nom.r.load(s1, mg);
         T yy[NY], H[NY][NX], d[NY], S[NY][NY];
 #pragma unroll
         for (int a = 0; a < NY; ++a)
-            yy[a] = y[a * T_y + y_off[b] + k];
+            yy[a] = y[a * T_y + i];
         lin.obs(mg, yy, H, d, S);
         if (dev)
             dev_obs_offset(H, mg.m, d);
-        out.store_obs(i, H, d, S);
+        out.store_obs(u, H, d, S);
     }
 }
 
@@ -571,7 +592,7 @@ struct LinCT {
         if constexpr (TAYLOR)
             ct_taylor_transition(P, mg, F, c, S);
         else
-            ct_slr_transition(P, mg, F, c, S);
+            ct_slr_transition<T, true>(P, mg, F, c, S);
     }
     PSS_INL void obs(const Marg<T, 5> &mg, const T (&y)[2], T (&H)[2][5], T (&d)[2],
                      T (&S)[2][2]) const
