@@ -1,0 +1,539 @@
+// Ragged batches of several model groups, and the autotuner of their launch
+// shape.
+//
+// Each group runs the passes of pss_ipls_iterate: its launches cover every
+// tile of every sequence, which is what fills the chip.  One persistent launch
+// per pass, whose tiles chained through a work queue, took 1.22 ms for a call of
+// 400 ragged FP32 sequences (830 000 steps of two models) where these launches
+// take 0.77 ms one group after the other and 0.63 ms side by side: it ran every stage at the registers of its heaviest one, a wave per
+// SIMD, and its chains wrote the L2 back tile by tile.
+//
+// The groups share nothing, so all but the first run on streams of their own
+// between two events: a few short sequences leave the chip idle through every
+// launch (three of each model, 206 to 1652 FP32 steps: 276 us instead of 368),
+// and long ones fill each other's last waves.
+#include <math.h>
+#include <stdio.h>
+
+#include <algorithm>
+#include <map>
+#include <mutex>
+#include <string>
+#include <vector>
+
+#include <hip/hip_runtime.h>
+
+#include "common.hpp"
+
+namespace pss {
+
+namespace {
+
+struct Shape {
+    int T = 0;   // block threads
+    int E_f = 0; // elements per thread at the finest level; 0 with T = 0: the
+    int E_s = 0; // library's rule.  (E_s: kept in the interface, equals E_f)
+};
+
+constexpr int kMaxGroups = 4;
+constexpr int kGroupCT = 1, kGroupLinear4 = 2;
+
+// ---- autotune cache (host, mutex-guarded) ---------------------------------
+std::mutex g_tune_mu;
+std::map<std::string, Shape> g_tune;
+bool g_tune_loaded = false;
+
+std::string sig_of(const pss_group *gs, int ng)
+{
+    std::string s = gs[0].p->dtype == PSS_F64 ? "f64" : "f32";
+    for (int i = 0; i < ng; ++i) {
+        const pss_problem *p = gs[i].p;
+        const int64_t T_y = p->y_off_host[p->B];
+        int lg = 0;
+        while ((int64_t(1) << lg) < T_y)
+            ++lg;
+        s += "|" + std::to_string(p->model) + ":" + std::to_string(p->nx) + ":B" +
+             std::to_string(p->B) + ":L" + std::to_string(lg);
+    }
+    return s;
+}
+
+void load_cache_file(const char *path)
+{
+    FILE *f = fopen(path, "r");
+    if (!f)
+        return;
+    char key[512];
+    int T, Ef, Es;
+    // one entry per line: "key" T E_f E_s
+    while (fscanf(f, " \"%511[^\"]\" %d %d %d", key, &T, &Ef, &Es) == 4) {
+        Shape sh;
+        sh.T = T;
+        sh.E_f = Ef;
+        sh.E_s = Es;
+        g_tune[key] = sh;
+    }
+    fclose(f);
+}
+
+void save_cache_file(const char *path)
+{
+    FILE *f = fopen(path, "w");
+    if (!f)
+        return;
+    for (auto &kv : g_tune)
+        fprintf(f, "\"%s\" %d %d %d\n", kv.first.c_str(), kv.second.T, kv.second.E_f,
+                kv.second.E_s);
+    fclose(f);
+}
+
+bool lookup(const std::string &key, Shape &sh)
+{
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    if (!g_tune_loaded) {
+        g_tune_loaded = true;
+        const char *env = getenv("PSS_TUNE_CACHE");
+        if (env)
+            load_cache_file(env);
+    }
+    auto it = g_tune.find(key);
+    if (it == g_tune.end())
+        return false;
+    sh = it->second;
+    return true;
+}
+
+int kind_of(const pss_problem *p)
+{
+    if (p->model == PSS_MODEL_CT_BEARINGS && p->nx == 5 && p->ny == 2)
+        return kGroupCT;
+    if (p->model == PSS_MODEL_LINEAR && p->nx == 4 && p->ny == 2)
+        return kGroupLinear4;
+    return 0;
+}
+
+Shape default_shape(const pss_group *gs, int ng)
+{
+    Shape sh;
+    sh.T = gs[0].p->scan_threads;
+    sh.E_f = sh.E_s = gs[0].p->scan_elems;
+    if (sh.T <= 0 && sh.E_f <= 0) {
+        Shape tuned;
+        if (lookup(sig_of(gs, ng), tuned))
+            sh = tuned;
+    }
+    return sh;
+}
+
+int validate_groups(const pss_group *gs, int ng)
+{
+    if (!gs || ng < 1 || ng > kMaxGroups) {
+        set_error("batched: need 1..4 groups");
+        return PSS_EINVAL;
+    }
+    for (int i = 0; i < ng; ++i) {
+        const int rc = pss_validate(gs[i].p);
+        if (rc)
+            return rc;
+        const pss_problem *p = gs[i].p;
+        if (!kind_of(p)) {
+            set_error("batched: groups must be CT (nx 5, ny 2) or linear (nx 4, ny 2)");
+            return PSS_EUNSUPPORTED;
+        }
+        if (p->form != PSS_FORM_SQRT) {
+            set_error("batched: defined for the square-root form only");
+            return PSS_EUNSUPPORTED;
+        }
+        if (p->model != PSS_MODEL_LINEAR && p->linearization != PSS_LIN_CUBATURE &&
+            p->linearization != PSS_LIN_TAYLOR) {
+            set_error("batched: defined for the cubature and the Taylor linearisation only");
+            return PSS_EUNSUPPORTED;
+        }
+        if (p->dtype != gs[0].p->dtype) {
+            set_error("batched: all groups need the same dtype");
+            return PSS_EINVAL;
+        }
+        if (p->scan_threads != gs[0].p->scan_threads || p->scan_elems != gs[0].p->scan_elems) {
+            set_error("batched: all groups need the same launch shape overrides");
+            return PSS_EINVAL;
+        }
+        if (!gs[i].y || !gs[i].m_nom || !gs[i].N_nom) {
+            set_error("batched: null y or nominal");
+            return PSS_EINVAL;
+        }
+        if (p->model == PSS_MODEL_LINEAR) {
+            const pss_gamma *g = gs[i].g;
+            if (!g || !g->F || !g->c || !g->SL || !g->H || !g->d || !g->SO ||
+                (g->stride != 0 && g->stride != 1)) {
+                set_error("batched: a linear group needs its parameters");
+                return PSS_EINVAL;
+            }
+        } else if (gs[i].g) {
+            set_error("batched: a CT group takes g = NULL");
+            return PSS_EINVAL;
+        }
+    }
+    return PSS_OK;
+}
+
+// the group's problem at this launch shape
+pss_problem shaped(const pss_group &g, const Shape &sh)
+{
+    pss_problem p = *g.p;
+    p.scan_threads = sh.T;
+    p.scan_elems = sh.E_f;
+    return p;
+}
+
+// the groups run side by side, each in its own part of the space
+size_t group_bytes(const pss_group &g, const Shape &sh)
+{
+    const pss_problem p = shaped(g, sh);
+    return align256(pss_workspace_size(&p, PSS_OP_IPLS));
+}
+size_t ws_bytes_for(const pss_group *gs, int ng, const Shape &sh)
+{
+    size_t m = 0;
+    for (int i = 0; i < ng; ++i)
+        m += group_bytes(gs[i], sh);
+    return m;
+}
+
+// ---- side streams ----------------------------------------------------------
+// Creating a stream costs more than a small batch, so they are lent: a call
+// takes one per further group and gives it back when its work is queued.  The
+// next borrower's work is then only ordered behind it.  At most kMaxIdle wait
+// in the pool; a call that finds none makes one, and one too many is destroyed.
+struct Side {
+    int dev = -1;
+    hipStream_t s = nullptr;
+    hipEvent_t done = nullptr;
+};
+constexpr size_t kMaxIdle = 8;
+std::mutex g_side_mu;
+std::vector<Side> g_side;
+
+void free_side(Side &x)
+{
+    if (x.done)
+        (void)hipEventDestroy(x.done);
+    if (x.s)
+        (void)hipStreamDestroy(x.s);
+    x = Side();
+}
+bool take_side(int dev, Side &x)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_side_mu);
+        for (size_t i = 0; i < g_side.size(); ++i)
+            if (g_side[i].dev == dev) {
+                x = g_side[i];
+                g_side.erase(g_side.begin() + i);
+                return true;
+            }
+    }
+    x.dev = dev;
+    if (hipStreamCreateWithFlags(&x.s, hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&x.done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        free_side(x);
+        return false;
+    }
+    return true;
+}
+void give_side(Side &x)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_side_mu);
+        if (g_side.size() < kMaxIdle) {
+            g_side.push_back(x);
+            return;
+        }
+    }
+    free_side(x);
+}
+
+// Streams forked off s, joined again by the destructor whatever happened in
+// between.  None while s is captured: a stream that is part of a graph could
+// not be lent to anyone else before the capture ends.  A group without a side
+// stream runs on s.
+struct Fork {
+    hipStream_t main;
+    int n = 0;
+    Side side[kMaxGroups - 1];
+    Fork(hipStream_t s, int want) : main(s)
+    {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        int dev = 0;
+        if (want <= 0)
+            return;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess || hipGetDevice(&dev) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if (cap != hipStreamCaptureStatusNone)
+            return;
+        while (n < want && take_side(dev, side[n])) {
+            // the side's own event marks the fork, later the join
+            Side &x = side[n];
+            if (hipEventRecord(x.done, s) != hipSuccess ||
+                hipStreamWaitEvent(x.s, x.done, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                free_side(x);
+                return;
+            }
+            ++n;
+        }
+    }
+    hipStream_t stream(int group) const
+    {
+        return group >= 1 && group <= n ? side[group - 1].s : main;
+    }
+    int join()
+    {
+        int rc = PSS_OK;
+        for (; n > 0; --n) {
+            Side &x = side[n - 1];
+            int r = hip_check(hipEventRecord(x.done, x.s), "side stream event");
+            if (!r)
+                r = hip_check(hipStreamWaitEvent(main, x.done, 0), "side stream join");
+            if (r) { // its work must not outlive the call's order
+                rc = r;
+                (void)hipStreamSynchronize(x.s);
+                free_side(x);
+            } else {
+                give_side(x);
+            }
+        }
+        return rc;
+    }
+    ~Fork() { (void)join(); }
+    Fork(const Fork &) = delete;
+    Fork &operator=(const Fork &) = delete;
+};
+
+__global__ __launch_bounds__(64) void k_clear_status(int32_t *status)
+{
+    if (threadIdx.x == 0)
+        *status = 0;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_copy(const T *src, T *dst, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        dst[i] = src[i];
+}
+
+int run(const pss_group *gs, int ng, int n_iter, int32_t *status, void *ws, size_t ws_bytes,
+        hipStream_t s, const Shape &sh)
+{
+    // a shape from a cache file may hold anything
+    if ((sh.T != 0 && sh.T != 64 && sh.T != 128 && sh.T != 256) || sh.E_f < 0) {
+        set_error("batched: block threads must be 64, 128 or 256, elements at least 1");
+        return PSS_EINVAL;
+    }
+    if (ws_bytes < ws_bytes_for(gs, ng, sh) || !ws) {
+        set_error("batched: workspace too small");
+        return PSS_EWORKSPACE;
+    }
+    if (status) {
+        hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(64), 0, s, status);
+        if (int rc = hip_check(hipGetLastError(), "status launch"))
+            return rc;
+    }
+    Fork fork(s, ng - 1);
+    Carver cv{static_cast<char *>(ws)};
+    for (int i = ng - 1; i >= 0; --i) { // the side streams' work first
+        const pss_problem p = shaped(gs[i], sh);
+        const size_t bytes = group_bytes(gs[i], sh);
+        char *part = cv.take<char>(bytes);
+        if (int rc = pss_ipls_iterate(&p, gs[i].g, gs[i].y, n_iter, gs[i].m_nom, gs[i].N_nom,
+                                      nullptr, nullptr, part, bytes, fork.stream(i)))
+            return rc;
+    }
+    return fork.join();
+}
+
+size_t max_ws(const pss_group *gs, int ng, const std::vector<Shape> &cands)
+{
+    size_t m = 0;
+    for (const Shape &sh : cands)
+        m = std::max(m, ws_bytes_for(gs, ng, sh));
+    return m;
+}
+
+std::vector<Shape> candidates()
+{
+    std::vector<Shape> c;
+    for (int T : {64, 128, 256})
+        for (int E : {1, 2, 4, 8}) {
+            Shape sh;
+            sh.T = T;
+            sh.E_f = sh.E_s = E;
+            c.push_back(sh);
+        }
+    return c;
+}
+
+} // namespace
+
+} // namespace pss
+
+using namespace pss;
+
+extern "C" {
+
+size_t pss_batched_workspace_size(const pss_group *groups, int32_t n_groups)
+{
+    try {
+        if (validate_groups(groups, n_groups))
+            return 0;
+        return ws_bytes_for(groups, n_groups, default_shape(groups, n_groups));
+    } catch (...) {
+        set_error("exception in pss_batched_workspace_size");
+        return 0;
+    }
+}
+
+int pss_ipls_batched(const pss_group *groups, int32_t n_groups, int32_t n_iter, int32_t *status,
+                     void *ws, size_t ws_bytes, hipStream_t stream)
+{
+    try {
+        int rc = validate_groups(groups, n_groups);
+        if (rc)
+            return rc;
+        if (n_iter < 0) {
+            set_error("batched: negative n_iter");
+            return PSS_EINVAL;
+        }
+        return run(groups, n_groups, n_iter, status, ws, ws_bytes, stream,
+                   default_shape(groups, n_groups));
+    } catch (...) {
+        set_error("exception in pss_ipls_batched");
+        return PSS_EINVAL;
+    }
+}
+
+size_t pss_autotune_workspace_size(const pss_group *groups, int32_t n_groups)
+{
+    try {
+        if (validate_groups(groups, n_groups))
+            return 0;
+        const bool f64 = groups[0].p->dtype == PSS_F64;
+        size_t nom = 0;
+        for (int i = 0; i < n_groups; ++i) {
+            const pss_problem *p = groups[i].p;
+            const int64_t T_x = p->y_off_host[p->B] + p->B;
+            nom += align256((size_t)(p->nx + p->nx * (p->nx + 1) / 2) * T_x * (f64 ? 8 : 4));
+        }
+        return max_ws(groups, n_groups, candidates()) + nom;
+    } catch (...) {
+        set_error("exception in pss_autotune_workspace_size");
+        return 0;
+    }
+}
+
+int pss_autotune(const pss_group *groups, int32_t n_groups, void *ws, size_t ws_bytes,
+                 const char *cache_path_host, int32_t *best_host, hipStream_t stream)
+{
+    try {
+        int rc = validate_groups(groups, n_groups);
+        if (rc)
+            return rc;
+        const bool f64 = groups[0].p->dtype == PSS_F64;
+        const std::vector<Shape> cands = candidates();
+        const size_t need = pss_autotune_workspace_size(groups, n_groups);
+        if (!ws || ws_bytes < need) {
+            set_error("autotune: workspace too small");
+            return PSS_EWORKSPACE;
+        }
+        // scratch nominal copies after the largest pass workspace
+        const size_t base = max_ws(groups, n_groups, cands);
+        Carver cv{static_cast<char *>(ws) + base};
+        std::vector<pss_group> tmp(groups, groups + n_groups);
+        std::vector<pss_problem> probs(n_groups);
+        for (int i = 0; i < n_groups; ++i) {
+            probs[i] = *groups[i].p;
+            tmp[i].p = &probs[i];
+            const int64_t T_x = probs[i].y_off_host[probs[i].B] + probs[i].B;
+            const int64_t cnt = (int64_t)(probs[i].nx + probs[i].nx * (probs[i].nx + 1) / 2) * T_x;
+            char *buf = f64 ? (char *)cv.take<double>((size_t)cnt) : (char *)cv.take<float>((size_t)cnt);
+            tmp[i].m_nom = buf;
+            tmp[i].N_nom = buf + (size_t)probs[i].nx * T_x * (f64 ? 8 : 4);
+        }
+        hipEvent_t e0, e1;
+        if ((rc = hip_check(hipEventCreate(&e0), "hipEventCreate")))
+            return rc;
+        if ((rc = hip_check(hipEventCreate(&e1), "hipEventCreate"))) {
+            (void)hipEventDestroy(e0);
+            return rc;
+        }
+        auto reset = [&]() {
+            for (int i = 0; i < n_groups; ++i) {
+                const pss_problem *p = groups[i].p;
+                const int64_t T_x = p->y_off_host[p->B] + p->B;
+                const int64_t nm = (int64_t)p->nx * T_x, nN = (int64_t)(p->nx * (p->nx + 1) / 2) * T_x;
+                if (f64) {
+                    hipLaunchKernelGGL(k_copy<double>, dim3(256), dim3(256), 0, stream,
+                                       (const double *)groups[i].m_nom, (double *)tmp[i].m_nom, nm);
+                    hipLaunchKernelGGL(k_copy<double>, dim3(256), dim3(256), 0, stream,
+                                       (const double *)groups[i].N_nom, (double *)tmp[i].N_nom, nN);
+                } else {
+                    hipLaunchKernelGGL(k_copy<float>, dim3(256), dim3(256), 0, stream,
+                                       (const float *)groups[i].m_nom, (float *)tmp[i].m_nom, nm);
+                    hipLaunchKernelGGL(k_copy<float>, dim3(256), dim3(256), 0, stream,
+                                       (const float *)groups[i].N_nom, (float *)tmp[i].N_nom, nN);
+                }
+            }
+        };
+        float best_ms = 1e30f;
+        Shape best = cands[0];
+        for (const Shape &sh : cands) {
+            float ms = 0.f;
+            for (int rep = 0; rep < 2 && rc == PSS_OK; ++rep) {
+                reset();
+                if (rep == 1)
+                    rc = hip_check(hipEventRecord(e0, stream), "hipEventRecord");
+                if (!rc)
+                    rc = run(tmp.data(), n_groups, 1, nullptr, ws, base, stream, sh);
+                if (rep == 1 && !rc) {
+                    rc = hip_check(hipEventRecord(e1, stream), "hipEventRecord");
+                    if (!rc)
+                        rc = hip_check(hipEventSynchronize(e1), "hipEventSynchronize");
+                    if (!rc)
+                        rc = hip_check(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime");
+                }
+            }
+            if (rc)
+                break;
+            if (ms < best_ms) {
+                best_ms = ms;
+                best = sh;
+            }
+        }
+        (void)hipEventDestroy(e0);
+        (void)hipEventDestroy(e1);
+        if (rc)
+            return rc;
+        {
+            std::lock_guard<std::mutex> lk(g_tune_mu);
+            g_tune_loaded = true;
+            g_tune[sig_of(groups, n_groups)] = best;
+            if (cache_path_host)
+                save_cache_file(cache_path_host);
+        }
+        if (best_host) {
+            best_host[0] = best.T;
+            best_host[1] = best.E_f;
+            best_host[2] = best.E_s;
+        }
+        return PSS_OK;
+    } catch (...) {
+        set_error("exception in pss_autotune");
+        return PSS_EINVAL;
+    }
+}
+
+} // extern "C"
