@@ -2,7 +2,7 @@
 
 Main workload: coordinated-turn bearings-only tracking, one long sequence of
 n = 10^6 steps (the long-sequence configuration), 10 cubature IPLS passes
-(SLR, filter elements, filter scan, smoother scan), then the
+(SLR, filter and smoother scan), then the
 pseudo-log-likelihood and its gradient at the final nominal (one gradient
 pass returns both), FP64.  One
 "step" is that whole hot path over the sequence, captured in a HIP graph and
@@ -28,9 +28,8 @@ Also in the line (same run):
                   re-run at every evaluation); ipls_next_pass_change: how far
                   the nominal still moves in one more pass after those
                   passes, per sequence (whether IPLS reached a fixed point)
-  kernels         every scan kernel of one filter and one smoother scan,
-                  timed per launch with HIP events on its stream, with the
-                  counted flops it executes
+  kernels         every kernel of the step, timed per launch with HIP events
+                  on its stream, with the counted flops it executes
   roofline        the kernel with the largest time among those: its counted
                   flops and algorithmic bytes per launch over its time, against
                   78.6 TFLOP/s (vector ALU) and 8 TB/s (HBM); bound = the larger
@@ -98,7 +97,7 @@ def parse():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extras", action="store_true", help="main line only (profiling)")
     ap.add_argument("--batched-only", action="store_true",
-                    help="the ragged 512-sequence batch alone (profiling its persistent pass)")
+                    help="the ragged 512-sequence batch alone (profiling)")
     return ap.parse_args()
 
 
@@ -127,88 +126,88 @@ def scan_plan(lengths, T0, E0, Tup, E1, Eup, flat0):
     return levels
 
 
-def scan_kernel_flops(op, lengths, T0, E0, Tup, E1, Eup, flat0):
-    """Counted flops of each kernel of one scan, keyed (kernel, level).
-
-    Up-sweep (and the first half of the top kernel): the fold and the tile
-    tree combine every element but the first of each tile, elems - tiles
-    combines.  Down-sweep: the tree applies threads - tiles times and every
-    element is applied once.  A flat level has no tree: elems - threads
-    combines up, elems applies down.  The smoother's level-0 up-sweep also
-    builds its elements (one per state)."""
-    comb, app = FLOPS[op + "_combine"], FLOPS[op + "_apply"]
-    if op == "adjoint":
-        comb, app = FLOPS["adjoint_combine"], FLOPS["adjoint_apply"]
-    # the filter's finest level folds and applies leaf elements (elements -
-    # threads fold combines, elements applies); its trees use the general form
-    lcomb = FLOPS.get(op + "_combine_leaf", comb)
-    lapp = FLOPS.get(op + "_apply_leaf", app)
-    plan = scan_plan(lengths, T0, E0, Tup, E1, Eup, flat0)
-    out = {}
-    for l, (T, E, elems, tiles, threads, flat) in enumerate(plan):
-        if flat:
-            up = (elems - threads) * lcomb
-            down = elems * lapp
-        elif l == 0:
-            up = (elems - threads) * lcomb + (threads - tiles) * comb
-            down = elems * lapp + (threads - tiles) * app
-        else:
-            up = (elems - tiles) * comb
-            down = (elems + threads - tiles) * app
-        if op == "smoother" and l == 0:
-            up += elems * FLOPS["smoother_element"]
-        if op == "adjoint" and l == 0:
-            # the map of every step is built in the up-sweep and again in the
-            # down-sweep, which also forms the step's cotangents
-            up += elems * FLOPS["adjoint_element"]
-            down += elems * (FLOPS["adjoint_element"] + FLOPS["adjoint_cotangents"])
-        if l == len(plan) - 1:
-            out[(op + "_top", l)] = up + down
-        else:
-            out[(op + "_up", l)] = up
-            out[(op + "_down", l)] = down
-    return out
-
-
 # numbers per object (CT, nx = 5, ny = 2): marginal (m, packed N), filter
-# element, smoother element / adjoint map, linearisation parts
-NUM = dict(marg=20, felem=65, selem=45, gam_trans=45, gam_obs=15, y=2)
+# element, smoother element / adjoint map, linearisation, measurement
+NUM = dict(marg=20, felem=65, selem=45, gam=60, y=2)
+GROUPS = 32  # 16-lane groups of a block of the levels above the finest
 
 
-def scan_kernel_bytes(op, lengths, T0, E0, Tup, E1, Eup, flat0, esz, B=1):
-    """Algorithmic HBM bytes of each kernel of one scan, keyed (kernel,
-    level): every input the kernel's contract needs read once and every
-    output written once, in the library's storage design (elements of the
-    level, the tile's saved LDS tree, tile aggregates, exclusive prefixes).
-    Level-0 inputs: filter elements (filter); the filtering marginal and the
-    transition part of Gamma per state, plus the element stash written in
-    the up-sweep and read in the down-sweep (smoother); the marginal, Gamma
-    and y per step, and 3 FP64 theta terms written per step (adjoint)."""
-    plan = scan_plan(lengths, T0, E0, Tup, E1, Eup, flat0)
-    ne = NUM["felem"] if op == "filter" else NUM["selem"]
-    npre = NUM["marg"]
-    out = {}
+def lq_flops(K, Z0, R, C):
+    """Flops of the first K reflections of a Tria of R rows and C columns whose
+    row i has nothing beyond column Z0 + i: the row's norm and reflector, then
+    a dot product and an update on each of the rows below."""
+    tot = 0
+    for i in range(K):
+        w = min(C, Z0 + i + 1) - i
+        tot += 2 * w + 30 + (R - 1 - i) * (4 * w + 2)
+    return tot
+
+
+def fold_flops():
+    """One step of step_fold: the conditional filter (predict, update of
+    Lemma 1), its transfer matrix and the information about its start."""
+    nx, ny = 5, 2
+    predict = 2 * nx * nx * (2 * nx + 1) + lq_flops(nx, nx, nx, 2 * nx)
+    update = 2 * ny * nx * (nx + nx) + lq_flops(ny, nx, nx + ny, nx + ny)
+    transfer = 2 * nx * nx * ny * 2 + 6 * nx * ny + lq_flops(nx, ny, nx, nx + ny)
+    return predict + update + transfer
+
+
+def upper_levels(op, plan, esz):
+    """(flops, bytes) of the levels above the finest, keyed (kernel, level).
+    Up: every element but the first of a tile is combined once; elements in,
+    the groups' prefixes and the tile's aggregate out.  Down: every element is
+    applied once; elements and saved prefixes in, marginals out."""
+    comb, app = FLOPS[op + "_combine"], FLOPS[op + "_apply"]
+    ne, nm = (NUM["felem"] if op == "filter" else NUM["selem"]), NUM["marg"]
+    fl, by = {}, {}
     for l, (T, E, elems, tiles, threads, flat) in enumerate(plan):
-        top = l == len(plan) - 1
-        tree = 0 if (flat or top) else tiles * T * ne
-        if l == 0 and op == "smoother":
-            src_up = elems * npre + (elems - B) * NUM["gam_trans"] + elems * NUM["selem"]
-            src_down = elems * NUM["selem"]
-        elif l == 0 and op == "adjoint":
-            src_up = src_down = elems * (npre + NUM["gam_trans"] + NUM["gam_obs"] + NUM["y"])
+        if l == 0:
+            continue
+        saved = min(elems, tiles * GROUPS)
+        if l == len(plan) - 1:
+            fl[(op + "_top", l)] = (elems - tiles) * comb + elems * app
+            by[(op + "_top", l)] = elems * (ne + nm) * esz
         else:
-            src_up = src_down = elems * ne
-        agg = threads * ne if flat else tiles * ne
-        pre_in = threads * npre if flat else tiles * npre
-        outs = elems * npre * esz
-        if l == 0 and op == "adjoint":
-            outs = elems * 3 * 8
-        if top:
-            out[(op + "_top", l)] = src_up * esz + outs
-        else:
-            out[(op + "_up", l)] = (src_up + tree + agg) * esz
-            out[(op + "_down", l)] = (src_down + tree + pre_in) * esz + outs
-    return out
+            fl[(op + "_up", l)] = (elems - tiles) * comb
+            by[(op + "_up", l)] = (elems + saved + tiles) * ne * esz
+            fl[(op + "_down", l)] = (elems + saved) * app
+            by[(op + "_down", l)] = ((elems + saved) * ne + (elems + tiles) * nm) * esz
+    return fl, by
+
+
+def step_costs(n, dtype, T_req=0, E_req=0):
+    """Counted flops and algorithmic HBM bytes of the kernels of one IPLS pass
+    and (FP64) of the gradient over one sequence of n steps: what a kernel's
+    contract needs read once and written once."""
+    esz = 8 if dtype == "f64" else 4
+    plan = scan_plan([n], *step_shapes(n, T_req, E_req))
+    agg = plan[1][2]
+    step = NUM["gam"] + NUM["y"]
+    fl, by = {}, {}
+    for op in ("filter", "smoother", "adjoint"):
+        f, b = upper_levels(op, plan, esz)
+        fl.update(f)
+        by.update(b)
+    F = FLOPS
+    update = 2 * 2 * 5 * 5 + lq_flops(2, 5, 7, 7)
+    fl[("slr", 0)] = n * (F["slr_transition"] + F["slr_bearings"])
+    by[("slr", 0)] = n * (NUM["marg"] + NUM["y"] + NUM["gam"]) * esz
+    fl[("step_fold", 0)] = n * fold_flops()
+    by[("step_fold", 0)] = (n * step + agg * NUM["felem"]) * esz
+    fl[("step_walk", 0)] = n * (F["smoother_element"] + F["smoother_combine"] + update)
+    by[("step_walk", 0)] = (n * (step + NUM["selem"]) + agg * (NUM["marg"] + NUM["selem"])) * esz
+    fl[("step_smooth", 0)] = n * F["smoother_apply"]
+    by[("step_smooth", 0)] = (n * (NUM["selem"] + NUM["marg"]) + agg * NUM["marg"]) * esz
+    by[("nominal_plain", 0)] = 2 * n * NUM["marg"] * esz
+    if dtype == "f64":
+        fl[("filter_walk", 0)] = n * (F["adjoint_element"] + F["adjoint_combine"])
+        by[("filter_walk", 0)] = (n * (step + NUM["marg"]) + agg *
+                                  (NUM["marg"] + NUM["selem"])) * esz + n * 8
+        fl[("adjoint_down", 0)] = n * (F["adjoint_element"] + F["adjoint_apply"] +
+                                       F["adjoint_cotangents"])
+        by[("adjoint_down", 0)] = (n * (step + NUM["marg"]) + agg * NUM["marg"]) * esz + 3 * n * 8
+    return fl, by
 
 
 def kernel_source_hash():
@@ -228,12 +227,12 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
-def counter_traffic(kernel, level, dtype, n, summary=None):
+def counter_traffic(kernel, level, dtype, n):
     """HBM bytes per launch of (kernel, level) from the committed rocprofv3
     FETCH_SIZE / WRITE_SIZE summary of this workload, each scaled by what the
     same counter reads for a copy of known size; None when there is no
     summary for the kernels built here."""
-    name = summary or "hbm_traffic_ct_n%d_%s.md" % (n, dtype)
+    name = "hbm_traffic_ct_n%d_%s.md" % (n, dtype)
     path = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(path):
         return None
@@ -249,21 +248,15 @@ def counter_traffic(kernel, level, dtype, n, summary=None):
     return int(float(kv["bytes"]))
 
 
+def is_pass_kernel(key):
+    """Kernels that every IPLS pass launches once."""
+    return key[0] in ("slr", "step_fold", "step_walk", "step_smooth") or (
+        key[1] >= 1 and key[0].startswith(("filter_", "smoother_")))
+
+
 def pass_alg_bytes(n, dtype, T_req=0, E_req=0):
-    """Algorithmic HBM bytes of one IPLS pass of one sequence of n steps
-    (the kernels of the multi-launch pass: linearisation, filter elements,
-    every filter and smoother scan kernel)."""
-    esz = 8 if dtype == "f64" else 4
-    by = scan_kernel_bytes("filter", [n], *shapes(dtype, T_req, E_req), esz)
-    by.update(scan_kernel_bytes("smoother", [n + 1], *shapes(dtype, T_req, E_req, True), esz))
-    gam = NUM["gam_trans"] + NUM["gam_obs"]
-    tot = sum(by.values())
-    if dtype == "f32":  # linearisation fused with the elements
-        tot += ((n + 1) * NUM["marg"] + n * (NUM["y"] + NUM["gam_trans"] + NUM["felem"])) * esz
-    else:
-        tot += ((n + 1) * NUM["marg"] + n * (NUM["y"] + gam)) * esz
-        tot += n * (gam + NUM["y"] + NUM["felem"]) * esz
-    return tot
+    """Algorithmic HBM bytes of one IPLS pass of one sequence of n steps."""
+    return sum(v for k, v in step_costs(n, dtype, T_req, E_req)[1].items() if is_pass_kernel(k))
 
 
 def copy_probe(stream, dev, reps=5):
@@ -284,6 +277,13 @@ def shapes(dtype, T_req, E_req, smoother=False):
     T0 = T_req or 64
     E0 = E_req or (2 if smoother else 4)
     return T0, E0, min(T0, 64), 2 if smoother else 4, 2, not smoother
+
+
+def step_shapes(n, T_req, E_req):
+    """The same for a smoothing pass: its finest level runs Kalman steps, 2 a
+    thread on sequences of up to 768 and 8 beyond."""
+    T0 = T_req or 64
+    return T0, E_req or (2 if n <= 768 else 8), min(T0, 64), 4, 2, True
 
 
 class Runner:
@@ -361,8 +361,9 @@ def timed(stream, fn, reps):
 
 def bench_batched(stream, dev, M, B=512, seed=3, graph=True):
     """Ragged batch: B sequences, lengths uniform in [100, 20000], half linear
-    constant-velocity, half coordinated-turn, FP32; each IPLS pass is one
-    persistent launch over both groups (autotuned shape, graph-captured)."""
+    constant-velocity, half coordinated-turn, FP32 (autotuned shape; eager
+    calls run the two groups side by side, a captured graph one after the
+    other)."""
     log("simulating ragged batch of %d sequences" % B)
     groups_w, lengths, kinds = wl.ragged_mixed(B, 100, 20000, seed, M=M)
     tdt = torch.float32
@@ -407,25 +408,21 @@ def bench_batched(stream, dev, M, B=512, seed=3, graph=True):
     ok = int(status.item()) == 0
     nan = int(torch.isnan(m_ct).any().item() or torch.isnan(m_cv).any().item())
     log("batched: %.3f ms for %d step-passes (status %s)" % (t_batched, steps * M, ok))
+    t_eager = timed(stream, step, 3)
     # HBM: the fused minimum of a pass (every nominal and measurement read
-    # once, every nominal written once) and, from the committed rocprofv3
-    # summary of this batch, the persistent kernel's counter bytes per launch
+    # once, every nominal written once)
     esz = 4
     n_ct, n_cv = len(wct.y), len(wcv.y)
     nseq_ct, nseq_cv = len(wct.y_off) - 1, len(wcv.y_off) - 1
     min_bytes = esz * (2 * NUM["marg"] * (n_ct + nseq_ct) + NUM["y"] * n_ct +
                        2 * 14 * (n_cv + nseq_cv) + NUM["y"] * n_cv)
-    min_gbps = min_bytes * M / (t_batched * 1e-3) / 1e9
-    ctr = counter_traffic("ipls_persistent", 0, "f32", B,
-                          summary="hbm_traffic_batched_ragged512_f32.md")
-    ctr_gbps = None if ctr is None else ctr * M / (t_batched * 1e-3) / 1e9
-    log("batched: fused-minimum bytes per pass %.3g (%.0f GB/s), counter bytes per pass %s" %
-        (min_bytes, min_gbps, ctr))
-    # comparators: the multi-launch path per group, and one call per sequence
+    min_gbps = min_bytes * M / (min(t_batched, t_eager) * 1e-3) / 1e9
+    log("batched: fused-minimum bytes per pass %.3g (%.0f GB/s)" % (min_bytes, min_gbps))
+    # comparators: one call per group, and one call per sequence
     wsi_cv, _ = b_cv.workspace("ipls")
     wsi_ct, _ = b_ct.workspace("ipls")
 
-    def multi_launch():
+    def per_group():
         m_cv.copy_(m_cv0)
         N_cv.copy_(N_cv0)
         m_ct.copy_(m_ct0)
@@ -433,7 +430,7 @@ def bench_batched(stream, dev, M, B=512, seed=3, graph=True):
         pss.ipls_iterate(b_cv, y_cv, M, m_cv, N_cv, gamma=g_cv, ws=wsi_cv)
         pss.ipls_iterate(b_ct, y_ct, M, m_ct, N_ct, ws=wsi_ct)
 
-    t_multi = timed(stream, multi_launch, 2)
+    t_multi = timed(stream, per_group, 2)
     singles = []
     for wgrp, bgrp, ygrp, gam in ((wcv, b_cv, y_cv, g_cv), (wct, b_ct, y_ct, None)):
         for s in range(len(wgrp.y_off) - 1):
@@ -451,21 +448,18 @@ def bench_batched(stream, dev, M, B=512, seed=3, graph=True):
             pss.ipls_iterate(bs, ys, M, mm, NN, gamma=gam, ws=wsi)
 
     t_loop = timed(stream, loop_singles, 1)
-    log("batched: multi-launch %.3f ms, %d single-sequence calls %.3f ms" % (t_multi, B, t_loop))
+    log("batched: per group %.3f ms, %d single-sequence calls %.3f ms" % (t_multi, B, t_loop))
     return {"B": B, "total_steps": steps, "passes": M, "dtype": "f32",
             "autotuned_shape": {"threads": best[0], "filter_elems": best[1],
                                 "smoother_elems": best[2]},
-            "persistent_graph_ms": round(t_batched, 4),
+            "graph_ms": round(t_batched, 4), "eager_ms": round(t_eager, 4),
             "fused_min_bytes_per_pass": int(min_bytes),
             "fused_min_GBps": round(min_gbps, 1),
-            "counter_bytes_per_pass": ctr,
-            "counter_GBps": None if ctr_gbps is None else round(ctr_gbps, 1),
-            "counter_hbm_frac": None if ctr_gbps is None else round(ctr_gbps / HBM_GBPS, 4),
-            "value": round(steps * M / (t_batched * 1e-3), 1),
+            "value": round(steps * M / (min(t_batched, t_eager) * 1e-3), 1),
             "unit": "smoothed time steps/s",
-            "multi_launch_ms": round(t_multi, 4),
+            "per_group_ms": round(t_multi, 4),
             "looped_single_sequence_ms": round(t_loop, 4),
-            "speedup_vs_looped": round(t_loop / t_batched, 2),
+            "speedup_vs_looped": round(t_loop / min(t_batched, t_eager), 2),
             "status_ok": ok, "nan": nan}
 
 
@@ -714,28 +708,10 @@ def main():
             "loglik_grad": timed(stream, lambda: pss.loglik_grad(b, m, N, yd, ws=R.ws_grad), reps),
         }
         log("stages (ms): " + ", ".join("%s %.3f" % kv for kv in stage.items()))
-        fshape = shapes(args.dtype, args.scan_threads, args.scan_elems)
-        sshape = shapes(args.dtype, args.scan_threads, args.scan_elems, True)
-        ashape = (fshape[0], 2, min(fshape[0], 64), 2, 2, False)  # adjoint scan
-        T0, E0 = fshape[0], fshape[1]
+        shp = step_shapes(n, args.scan_threads, args.scan_elems)
+        T0, E0 = shp[0], shp[1]
         esz = 8 if args.dtype == "f64" else 4
-        kflops = scan_kernel_flops("filter", [n], *fshape)
-        kflops.update(scan_kernel_flops("smoother", [n + 1], *sshape))
-        kflops.update(scan_kernel_flops("adjoint", [n], *ashape))
-        kbytes = scan_kernel_bytes("filter", [n], *fshape, esz)
-        kbytes.update(scan_kernel_bytes("smoother", [n + 1], *sshape, esz))
-        kbytes.update(scan_kernel_bytes("adjoint", [n], *ashape, esz))
-        E0s = sshape[1]
-        kflops[("slr", 0)] = n * (FLOPS["slr_transition"] + FLOPS["slr_bearings"])
-        kflops[("filter_elements", 0)] = n * FLOPS["filter_element"]
-        kflops[("slr_felem", 0)] = n * (FLOPS["slr_transition"] + FLOPS["slr_bearings"] +
-                                         FLOPS["filter_element"])
-        gam = NUM["gam_trans"] + NUM["gam_obs"]
-        kbytes[("slr", 0)] = ((n + 1) * NUM["marg"] + n * (NUM["y"] + gam)) * esz
-        kbytes[("filter_elements", 0)] = n * (gam + NUM["y"] + NUM["felem"]) * esz
-        kbytes[("slr_felem", 0)] = ((n + 1) * NUM["marg"] +
-                                    n * (NUM["y"] + NUM["gam_trans"] + NUM["felem"])) * esz
-        kbytes[("loglik_terms", 0)] = n * (NUM["marg"] + gam + NUM["y"]) * esz + n * 8
+        kflops, kbytes = step_costs(n, args.dtype, args.scan_threads, args.scan_elems)
         kernels = {}
         for key, (calls, tot) in sorted(ktimes.items()):
             avg = tot / calls
@@ -759,9 +735,7 @@ def main():
             "algorithmic (HBM %.3f) -> %s bound" % (dom[0], dom[1], dom_ms, fl / t_dom / 1e12,
                                                    alu_frac, by / t_dom / 1e9, hbm_frac, bound))
         # one IPLS pass as a whole: its kernels once each
-        pass_keys = [k for k in ktimes if k[0] in ("slr", "filter_elements", "slr_felem") or
-                     k[0].startswith(("filter_up", "filter_down", "filter_top", "smoother_up",
-                                      "smoother_down", "smoother_top"))]
+        pass_keys = [k for k in ktimes if is_pass_kernel(k)]
         pass_ms = sum(ktimes[k][1] / ktimes[k][0] for k in pass_keys)
         pass_fl = sum(kflops.get(k, 0) for k in pass_keys)
         pass_by = sum(kbytes.get(k, 0) for k in pass_keys)
@@ -990,7 +964,7 @@ def main():
         "data": "synthetic (seeded CT bearings-only simulation)",
         "config": {"workload": "ct_bearings_long_n%d_M%d_cubature" % (n, M), "B": 1, "n": n,
                    "passes": M, "nx": 5, "ny": 2, "graph": not args.no_graph,
-                   "scan_threads": T0, "filter_elems": E0, "smoother_elems": E0s},
+                   "scan_threads": T0, "steps_per_thread": E0},
         "loglik_grad_ms": extras.get("param_estimation_64x1e4", {}).get(args.dtype, {}).get(
             "loglik_plus_grad_ms"),
         "nan_loglik": nan,

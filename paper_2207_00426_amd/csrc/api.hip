@@ -273,6 +273,18 @@ size_t seq_sum_bytes(const Ctx &c, int nc)
 
 int launch_seq_sum(const Ctx &c, int nc, const double *terms, int64_t ld, double *out, void *ws)
 {
+    int64_t longest = 0;
+    for (int b = 0; b < c.B; ++b)
+        longest = std::max(longest, c.p->y_off_host[b + 1] - c.p->y_off_host[b]);
+    if (longest <= (int64_t)kSumDirect * kSumChunk) {
+        if (nc == 1)
+            hipLaunchKernelGGL(k_seq_sum<1>, dim3(c.B), dim3(256), 0, c.s, c.p->y_off, terms, ld,
+                               c.B, out);
+        else
+            hipLaunchKernelGGL(k_seq_sum<3>, dim3(c.B), dim3(256), 0, c.s, c.p->y_off, terms, ld,
+                               c.B, out);
+        return hip_check(hipGetLastError(), "sequence sum launch");
+    }
     Carver cv{static_cast<char *>(ws)};
     int64_t *chunk_off = cv.take<int64_t>(c.B + 1);
     const int64_t nch = seq_chunks(c);

@@ -1102,13 +1102,40 @@ __global__ __launch_bounds__(128) void k_loglik_terms(const int64_t *y_off, int 
     ell[t] = l;
 }
 
-// Deterministic per-sequence sums in two stages.  Stage 1: one block per
-// chunk of kSumChunk consecutive step slots of ONE sequence (chunk offsets
-// from the tile plan with tile size kSumChunk); fixed thread strides, then a
-// fixed LDS tree.  Stage 2: one block per sequence adds its chunk partials in
-// order.  The bracketing depends only on the sequence lengths.
+// Deterministic per-sequence sums.  A chunk is kSumChunk consecutive step slots
+// of ONE sequence; fixed thread strides, then a fixed LDS tree; a sequence's
+// chunks are added in order.  The bracketing depends only on its length.
 constexpr int kSumChunk = 8192;
 
+// slots [a, z) of every component: on return red[c][0] holds the sums (thread 0
+// may read them)
+template <int NC>
+PSS_INL void chunk_sum(const double *terms, int64_t ld, int64_t a, int64_t z,
+                       double (&red)[NC][256])
+{
+    double s[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        s[c] = 0.0;
+#pragma unroll 8
+    for (int64_t t = a + threadIdx.x; t < z; t += 256)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            s[c] += terms[c * ld + t];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        red[c][threadIdx.x] = s[c];
+    for (int w = 128; w >= 1; w >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < w)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                red[c][threadIdx.x] += red[c][threadIdx.x + w];
+    }
+}
+
+// Long sequences, in two stages: one block per chunk (chunk offsets from the
+// tile plan with tile size kSumChunk), then one thread per sequence.
 template <int NC>
 __global__ __launch_bounds__(256) void k_chunk_sum(const int64_t *y_off, const int64_t *chunk_off,
                                                    int B, const double *terms, int64_t ld,
@@ -1121,25 +1148,7 @@ __global__ __launch_bounds__(256) void k_chunk_sum(const int64_t *y_off, const i
     int64_t z = a + kSumChunk;
     if (z > y_off[b + 1])
         z = y_off[b + 1];
-    double s[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-        s[c] = 0.0;
-#pragma unroll 8
-    for (int64_t t = a + threadIdx.x; t < z; t += blockDim.x)
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            s[c] += terms[c * ld + t];
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-        red[c][threadIdx.x] = s[c];
-    for (int w = blockDim.x / 2; w >= 1; w >>= 1) {
-        __syncthreads();
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-                red[c][threadIdx.x] += red[c][threadIdx.x + w];
-    }
+    chunk_sum<NC>(terms, ld, a, z, red);
     if (threadIdx.x == 0)
 #pragma unroll
         for (int c = 0; c < NC; ++c)
@@ -1160,6 +1169,36 @@ __global__ __launch_bounds__(64) void k_seq_total(const int64_t *chunk_off, cons
             s += partial[c * nchunks + k];
         out[(int64_t)c * B + b] = s;
     }
+}
+
+// Sequences of kSumDirect chunks at most: one block per sequence runs through
+// its chunks, the same sums in the same order, without the plan's launch and the
+// second stage's (an FP32 gradient of 1 x 1024 steps: 125.6 us with them, 117.9
+// without; a further chunk costs a block about what a launch does).
+constexpr int kSumDirect = 2;
+template <int NC>
+__global__ __launch_bounds__(256) void k_seq_sum(const int64_t *y_off, const double *terms,
+                                                 int64_t ld, int B, double *out)
+{
+    __shared__ double red[NC][256];
+    const int b = blockIdx.x;
+    const int64_t end = y_off[b + 1];
+    double s[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+        s[c] = 0.0;
+    for (int64_t a = y_off[b]; a < end; a += kSumChunk) {
+        chunk_sum<NC>(terms, ld, a, a + kSumChunk < end ? a + kSumChunk : end, red);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                s[c] += red[c][0];
+        __syncthreads(); // red is written again
+    }
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            out[(int64_t)c * B + b] = s[c];
 }
 
 // theta_bar[c] = sum_b w[b] grad[c][b] in a fixed order (one block)

@@ -1,0 +1,226 @@
+"""The kernels that run Kalman steps at a scan's finest level, the scans in
+16-lane groups above them, and the rules that choose between their forms, at
+the sizes where each can go wrong.
+
+Tolerances are tests/parity.TOL, the bars of every parity test; where two
+routes run the same arithmetic the comparison is bitwise.
+"""
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+from paper_2207_00426_amd import pss
+from paper_2207_00426_amd import workloads as wl
+from tests import parity as par
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _dt(tag):
+    return torch.float64 if tag == "f64" else torch.float32
+
+
+def _offsets(lens):
+    return np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+
+
+def _linear(nx, ny, lens, seed, per_step, dt):
+    rng = np.random.default_rng(seed)
+    off = _offsets(lens)
+    G, m0, N0 = wl.random_linear_model(nx, ny, rng, int(off[-1]) if per_step else None)
+    if dt == torch.float32:  # both sides solve the rounded problem
+        G = {k: par.kernel_input(v, dt) for k, v in G.items()}
+        m0, N0 = par.kernel_input(m0, dt), par.kernel_input(N0, dt)
+    seq = [({k: v[off[b]:off[b + 1]] for k, v in G.items()} if per_step else G)
+           for b in range(len(lens))]
+    ys = [par.kernel_input(wl.simulate_linear(g, m0, N0, int(n), rng), dt)
+          for g, n in zip(seq, lens)]
+    return G, seq, m0, N0, ys, off
+
+
+def _ct(lens, seed, dt, **kw):
+    rng = np.random.default_rng(seed)
+    ys = [par.kernel_input(wl.simulate_ct(int(n), rng)[1], dt) for n in lens]
+    b = pss.Batch.ct(_offsets(lens), wl.CTModel(), dtype=dt, device=DEV, **kw)
+    return b, ys, pss.to_soa(np.concatenate(ys), dt, DEV)
+
+
+def _check(m, N, nx, off, ref, tol):
+    ma, Na = pss.marg_from_soa(m, N, nx)
+    for b, (rm, rN) in enumerate(ref):
+        a, z = off[b] + b, off[b + 1] + b + 1
+        em, eP = par.marg_errs(ma[a:z], Na[a:z], rm, rN)
+        assert em < tol["m"] and eP < tol["P"], (b, z - a - 1, em, eP)
+
+
+# one step; a tile of 128 (2 a thread, up to 768 steps) and of 512 (8 a thread
+# beyond), full, one short and one over; group tiles of 256 elements, full and
+# one over (2049 = 257 threads of 8)
+EDGES = [1, 2, 127, 128, 129, 512, 513, 768, 769, 1024, 1025, 2048, 2049]
+
+
+@pytest.mark.parametrize("tag", ["f64", "f32"])
+@pytest.mark.parametrize("nx,ny,per_step", [(1, 1, True), (2, 3, False), (4, 2, True),
+                                            (5, 2, False)])
+def test_smoothing_pass_at_tile_edges(nx, ny, per_step, tag):
+    dt = _dt(tag)
+    G, seq, m0, N0, ys, off = _linear(nx, ny, EDGES, 31 * nx + ny, per_step, dt)
+    b = pss.Batch(pss.MODEL_LINEAR, dt, nx, ny, off, m0, N0, device=DEV)
+    m, N, mf, Nf = pss.ipls_iterate(b, pss.to_soa(np.concatenate(ys), dt, DEV), 1,
+                                    gamma=b.gamma_from_numpy(G), want_filter=True)
+    torch.cuda.synchronize()
+    filt = [orc.sqrt_filter(m0, N0, g, y)[:2] for g, y in zip(seq, ys)]
+    _check(mf, Nf, nx, off, filt, par.TOL[tag])
+    smooth = [orc.sqrt_smoother(g, *f)[:2] for g, f in zip(seq, filt)]
+    _check(m, N, nx, off, smooth, par.TOL[tag])
+
+
+@pytest.mark.parametrize("tag,elems", [("f64", 0), ("f32", 0), ("f64", 3), ("f32", 16)])
+@pytest.mark.parametrize("lin", ["cubature", "taylor"])
+def test_bearings_passes_at_tile_edges(lin, tag, elems):
+    """Linearisation into tile order (blocks of 256 steps across sequences) and
+    the nominal between passes, at the default and at forced steps a thread."""
+    dt = _dt(tag)
+    lens = [1, 129, 254, 768, 769, 2]
+    b, ys, yd = _ct(lens, 5, dt, linearization=lin, scan_elems=elems)
+    m, N = pss.ipls_iterate(b, yd, 2)
+    torch.cuda.synchronize()
+    md = wl.CTModel()
+    ref = [orc.ct_ipls(orc.ct_params(), md.m0, np.eye(5), y, 2, method=lin) for y in ys]
+    _check(m, N, 5, _offsets(lens), [(r["ms"], r["Ns"]) for r in ref], par.TOL[tag])
+
+
+@pytest.mark.parametrize("turn", [0.0, 0.3, 0.46, 0.4999, 0.51, 3.0])
+def test_turn_angles_on_both_sides_of_the_shared_expansion(turn):
+    """One expansion serves every sigma point while all turn by less than 1/2
+    in a step; nominals around that line against the oracle."""
+    rng = np.random.default_rng(3)
+    n, md = 40, wl.CTModel()
+    y = wl.simulate_ct(n, rng)[1]
+    ms = rng.normal(size=(n + 1, 5))
+    ms[:, 4] = turn / 0.01 * np.where(np.arange(n + 1) % 2, 1.0, -1.0)
+    Ns = 0.3 * np.tril(rng.normal(size=(n + 1, 5, 5)))
+    Ns[:, range(5), range(5)] = rng.uniform(0.5, 1.0, size=(n + 1, 5))
+    b = pss.Batch.ct([0, n], md, dtype=torch.float64, device=DEV)
+    g = pss.slr_linearize(b, pss.to_soa(ms, torch.float64, DEV),
+                          pss.to_soa(pss.pack_lower(Ns), torch.float64, DEV),
+                          pss.to_soa(y, torch.float64, DEV))
+    torch.cuda.synchronize()
+    ref = orc.ct_linearize(orc.ct_params(), ms, Ns, y)
+    for key, shape in (("F", (5, 5)), ("c", (5,)), ("H", (2, 5)), ("d", (2,))):
+        got = pss.from_soa(g[key], shape)
+        err = np.abs(got - ref[key]).max() / max(1.0, np.abs(ref[key]).max())
+        assert err < par.TOL["f64"]["m"], (key, err)
+    for key, k in (("SL", 5), ("SO", 2)):
+        got = par.gram(pss.unpack_lower(pss.from_soa(g[key], (pss.tri(k),)), k))
+        assert par.cov_err(got, par.gram(ref[key])) < par.TOL["f64"]["P"], key
+
+
+@pytest.mark.parametrize("bad", ["y", "mean"])
+def test_not_a_number_reaches_every_part_of_the_linearisation(bad):
+    """Columns that need no angle of their own still take a NaN along."""
+    md, n = wl.CTModel(), 5
+    b = pss.Batch.ct([0, n], md, dtype=torch.float64, device=DEV)
+    y = pss.to_soa(np.zeros((n, 2)), torch.float64, DEV)
+    m, N = b.prior_nominal()
+    if bad == "y":
+        y[:, 2] = float("nan")  # of step 2
+    else:
+        m[0, 3] = float("nan")  # state 3, which step 2 measures
+    g = pss.slr_linearize(b, m, N, y)
+    torch.cuda.synchronize()
+    H = pss.from_soa(g["H"], (2, 5))
+    assert np.isnan(H[2]).all() and np.isfinite(np.delete(H, 2, axis=0)).all()
+
+
+@pytest.mark.parametrize("tag", ["f64", "f32"])
+def test_loglik_and_gradient_at_tile_edges(tag):
+    """4 steps a thread up to 8192, 8 beyond (FP32: 2); group tiles of 256
+    elements; per-sequence sums of one chunk and of two."""
+    dt = _dt(tag)
+    lens = [1, 3, 256, 257, 1024, 1025, 8192, 8193] if tag == "f64" else [1, 2, 3, 512, 513, 1000]
+    b, ys, yd = _ct(lens, 8, dt)
+    m, N = pss.ipls_iterate(b, yd, 1)
+    ll, grad, _ = pss.loglik_grad(b, m, N, yd)
+    torch.cuda.synchronize()
+    ma, Na = pss.marg_from_soa(m.double(), N.double(), 5)
+    off, md = _offsets(lens), wl.CTModel()
+    for s, y in enumerate(ys):
+        a, z = off[s] + s, off[s + 1] + s + 1
+        l_ref, g_ref = orc.ct_score(orc.ct_params(), md.m0, np.eye(5), y, ma[a:z], Na[a:z])
+        assert par.ll_err(ll[s].item(), l_ref) < par.TOL[tag]["ll"], lens[s]
+        assert par.grad_err(grad[:, s].cpu().numpy(), g_ref) < par.TOL[tag]["g"], lens[s]
+
+
+def test_sums_in_one_launch_have_the_bits_of_two_stages():
+    """A sequence of 16384 steps is summed by one block; next to one of 16385 in
+    chunks.  Its log-likelihood and cotangents do not show it."""
+    dt, lens = torch.float64, [16384, 16385, 5]
+    G, seq, m0, N0, ys, off = _linear(2, 1, lens, 12, False, dt)
+    out = []
+    for sel in ([0, 2], [0, 1, 2]):
+        b = pss.Batch(pss.MODEL_LINEAR, dt, 2, 1, _offsets([lens[i] for i in sel]), m0, N0,
+                      device=DEV)
+        yd = pss.to_soa(np.concatenate([ys[i] for i in sel]), dt, DEV)
+        out.append(pss.loglik(b, yd, gamma=b.gamma_from_numpy(G)).cpu())
+    ref = [orc.sqrt_filter(m0, N0, G, y)[2].sum() for y in ys]
+    assert par.ll_err(out[1].numpy(), ref) < par.TOL["f64"]["ll"]
+    assert torch.equal(out[0], out[1][[0, 2]])
+
+
+def test_result_does_not_depend_on_the_copy_to_the_plain_layout():
+    """The last pass of a small call stores its marginals in the caller's
+    layout, that of a large one (over 16 MiB of them) copies them there."""
+    lens = [900, 110000]
+    b, ys, yd = _ct(lens, 4, torch.float64)
+    m, N = pss.ipls_iterate(b, yd, 2)
+    b1, _, y1 = _ct(lens[:1], 4, torch.float64)
+    m1, N1 = pss.ipls_iterate(b1, y1, 2)
+    torch.cuda.synchronize()
+    assert torch.equal(m[:, :901], m1) and torch.equal(N[:, :901], N1)
+
+
+def test_groups_on_side_streams_from_two_threads():
+    """Calls of two threads borrow side streams from one pool; each gives the
+    bits of the same groups run one call after the other."""
+    dt = torch.float32
+    G, seq, m0, N0, ys, off = _linear(4, 2, [300, 40], 2, False, dt)
+
+    def groups():
+        bl = pss.Batch(pss.MODEL_LINEAR, dt, 4, 2, off, m0, N0, device=DEV)
+        bc, _, yc = _ct([500, 1, 900], 6, dt)
+        return [(bl, pss.to_soa(np.concatenate(ys), dt, DEV), *bl.prior_nominal(),
+                 bl.gamma_from_numpy(G)), (bc, yc, *bc.prior_nominal(), None)]
+
+    alone = groups()
+    for g in alone:
+        pss.ipls_batched([g], 2)
+    torch.cuda.synchronize()
+    sets = [groups() for _ in range(6)]
+    ws = [torch.empty(pss.batched_workspace_size(g), dtype=torch.uint8, device=DEV) for g in sets]
+    status = [torch.zeros(1, dtype=torch.int32, device=DEV) for _ in sets]
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(part):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for i in part:
+                    pss.ipls_batched(sets[i], 2, ws=ws[i], status=status[i])
+        except Exception as ex:  # noqa: BLE001
+            failed.append(ex)
+
+    threads = [threading.Thread(target=work, args=(range(k, 6, 2),)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not failed
+    for s in sets:
+        for g, r in zip(s, alone):
+            assert torch.equal(g[2], r[2]) and torch.equal(g[3], r[3])
