@@ -281,9 +281,9 @@ def shapes(dtype, T_req, E_req, smoother=False):
 
 def step_shapes(n, T_req, E_req):
     """The same for a smoothing pass: its finest level runs Kalman steps, 2 a
-    thread on sequences of up to 768 and 8 beyond."""
+    thread on sequences of up to 256, 4 up to 768 and 8 beyond."""
     T0 = T_req or 64
-    return T0, E_req or (2 if n <= 768 else 8), min(T0, 64), 4, 2, True
+    return T0, E_req or (2 if n <= 256 else 4 if n <= 768 else 8), min(T0, 64), 4, 2, True
 
 
 class Runner:

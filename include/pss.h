@@ -154,8 +154,12 @@ typedef struct pss_problem {
     double sensors[4];          /* CT: s1x, s1y, s2x, s2y                      */
     /* launch shape overrides (0 = library default / autotuned):
        block threads per scan tile (64, 128 or 256; default 64) and elements
-       folded sequentially per thread (>= 1) at the finest level of both
-       scans (default 4 for the filter scan, 2 for the smoother scan) */
+       folded sequentially per thread (>= 1) at the finest level.  Default
+       elements: 4 in pss_sqrt_filter_scan, 2 in pss_sqrt_smoother_scan; where
+       the finest level runs Kalman steps, by the sequence's length: 2, 4 or 8
+       in ipls_iterate and ipls_batched (up to 256 steps, up to 768, beyond),
+       4 or 8 in the FP64 log-likelihood calls (up to 8192, beyond), 2 for a
+       scalar state in ipls_iterate */
     int32_t scan_threads;
     int32_t scan_elems;
     /* pss_linearization used by every call that linearises the model
@@ -196,8 +200,9 @@ typedef struct pss_felem {
      0       every filtering marginal (nx + nx(nx+1)/2 numbers per state);
      l >= 1  the exclusive prefixes of the filter scan's level-l elements
              (the filtering marginal before each level-l element: one per
-             4 states at level 1, one per 1024 at level 2 with the default
-             shapes); the backward pass re-runs only the levels below l;
+             4 or 8 states at level 1, one per 256 times as many at level 2
+             with the default shapes); the backward pass re-runs only the
+             levels below l;
    a level at or above the scan's top keeps nothing but the per-sequence
    log-likelihoods, and the backward pass re-runs the whole filter scan.
    `tag` is written by pss_loglik and identifies the problem (sizes, model,
@@ -406,7 +411,7 @@ int pss_sequential_smoother(const pss_problem *p, const pss_gamma *g, const void
 int pss_nan_status(const pss_problem *p, const void *m, const void *N, int32_t marg_bit,
                    const double *ll, int32_t ll_bit, int32_t *status, hipStream_t stream);
 
-/* ---- ragged batches of several model groups in one persistent launch ---- */
+/* ---- ragged batches of several model groups in one call ---- */
 
 /* One model group of a batched call: a ragged batch of sequences of one
    model.  Supported groups: PSS_MODEL_CT_BEARINGS (nx 5, ny 2) with the
@@ -423,14 +428,13 @@ typedef struct pss_group {
 /* Workspace bytes of pss_ipls_batched for these groups (0 if invalid). */
 size_t pss_batched_workspace_size(const pss_group *groups, int32_t n_groups);
 
-/* Algorithm 3 for up to 4 groups of ragged sequences, each pass ONE
-   persistent kernel launch (plus a flag-clearing kernel): a work queue of
-   filter tiles then smoother tiles of every sequence of every group; a tile
-   fuses the SLR of Section 4.3 (CT), the elements of Lemma 1 / Table 4, the
-   sequential fold, the in-LDS tree and the down-sweep, and chains with its
-   neighbour tile (inclusive prefix of tile t = prefix of tile t-1 (x) tile
-   aggregate).  Waits only target earlier queue items, are bounded, and set
-   bit flags in `status` (device int, nullable; 0 = ok) if a bound is hit.
+/* Algorithm 3 for up to 4 groups of ragged sequences: the passes of
+   pss_ipls_iterate on each group, with the same results.  The groups run side
+   by side, each in its own part of the workspace: all but the first on streams
+   of the library, which start after the work that `stream` holds and which
+   `stream` waits for before anything enqueued later.  While `stream` is
+   captured they run one after the other on it.  `status` (device int,
+   nullable) is set to 0.
    Launch shape: the problem's overrides, else the autotuned shape for this
    batch signature (pss_autotune, or the file named by the environment
    variable PSS_TUNE_CACHE), else defaults.  Bitwise reproducible for a
@@ -442,7 +446,7 @@ int pss_ipls_batched(const pss_group *groups, int32_t n_groups, int32_t n_iter, 
 size_t pss_autotune_workspace_size(const pss_group *groups, int32_t n_groups);
 
 /* Autotuner: times one batched pass for each candidate launch shape (block
-   threads 64/128/256, filter and smoother elements per thread 1..8) on the
+   threads 64/128/256, elements per thread 1..8) on the
    caller's data (the nominal is copied, not modified), keeps the fastest for
    this batch signature (dtype, models, batch sizes, log2 of total steps) in a
    host cache used by pss_ipls_batched, and writes the cache to
@@ -470,7 +474,8 @@ int pss_kernel_timing(int32_t enable);
 /* Waits for the events recorded since the last call, then writes one text
    line per (kernel, scan level): "<kernel> <level> <launches> <total ms>\n"
    (kernel = filter_up, filter_top, filter_down, smoother_up, ..., slr,
-   filter_elements, loglik_terms, grad_terms, sequential, persistent_pass),
+   step_fold, step_walk, step_smooth, nominal_plain, filter_walk,
+   adjoint_down, ..., filter_elements, loglik_terms, grad_terms, sequential),
    NUL-terminated and truncated to cap bytes, into buf (host), and clears
    the records.  With buf NULL nothing is written or cleared.  Returns the
    bytes needed (text + NUL), or a negative status. */

@@ -110,18 +110,17 @@ KTime::~KTime()
 // scan planning (host side mirrors k_plan exactly)
 // ---------------------------------------------------------------------------
 ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, int Eup,
-                    bool flat0, int E_short, int64_t n_short)
+                    bool flat0, ShortRule few)
 {
     ScanShape sh;
-    sh.E_short = E_short;
-    sh.n_short = n_short;
+    sh.few = few;
     std::vector<int64_t> cnt(c.B);
     // the sequence's level-0 elements per thread, decided before cnt shrinks
-    std::vector<char> is_short(c.B);
+    std::vector<int> E_seq(c.B);
     int64_t total = 0;
     for (int b = 0; b < c.B; ++b) {
         cnt[b] = c.p->y_off_host[b + 1] - c.p->y_off_host[b] + extra;
-        is_short[b] = cnt[b] <= n_short;
+        E_seq[b] = few.elems(cnt[b], E0);
         total += cnt[b];
     }
     sh.nelem[0] = total;
@@ -131,7 +130,7 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
         const int64_t TS = (int64_t)sh.T[l] * sh.E[l];
         int64_t nt = 0, mx = 0;
         for (int b = 0; b < c.B; ++b) {
-            const int64_t ts = l == 0 && is_short[b] ? (int64_t)T0 * E_short : TS;
+            const int64_t ts = l == 0 ? (int64_t)T0 * E_seq[b] : TS;
             mx = std::max(mx, cnt[b]);
             nt += (cnt[b] + ts - 1) / ts;
         }
@@ -148,7 +147,7 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
         const int64_t D = sh.flat[l] ? sh.E[l] : TS;
         int64_t ne = 0;
         for (int b = 0; b < c.B; ++b) {
-            const int64_t d = l == 0 && is_short[b] ? E_short : D;
+            const int64_t d = sh.flat[l] ? E_seq[b] : D;
             cnt[b] = (cnt[b] + d - 1) / d;
             ne += cnt[b];
         }
@@ -212,13 +211,13 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a)
         const int b = base + threadIdx.x;
         const bool in = b < a.B;
         int64_t cn = in ? a.y_off[b + 1] - a.y_off[b] + a.extra : 0;
-        const bool sh = in && cn <= a.n_short;
+        const int E0 = a.few.elems(cn, a.E0);
 #pragma unroll
         for (int l = 0; l < kMaxLevels; ++l) {
             if (l >= a.L)
                 break;
-            const int64_t ts = l == 0 && sh ? a.TS_short : a.TS[l];
-            const int64_t d = l == 0 && sh ? a.D_short : a.D[l];
+            const int64_t ts = l == 0 ? (int64_t)a.T0 * E0 : a.TS[l];
+            const int64_t d = l == 0 && a.flat0 ? E0 : l == 0 ? ts : a.D[l];
             int64_t t = (cn + ts - 1) / ts, e = cn, tt, te;
             plan_sums(t, e, tt, te, w);
             if (in) {
@@ -248,9 +247,10 @@ int launch_plan(const Ctx &c, const ScanShape &sh, int extra, int64_t *const *ti
         a.tile_off[l] = in ? tile_off[l] : nullptr;
         a.elem_off[l] = in && elem_off ? elem_off[l] : nullptr;
     }
-    a.n_short = sh.n_short;
-    a.D_short = sh.E_short;
-    a.TS_short = (int64_t)sh.T[0] * sh.E_short;
+    a.few = sh.few;
+    a.T0 = sh.T[0];
+    a.E0 = sh.E[0];
+    a.flat0 = sh.flat[0];
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(c.B <= 64 ? 64 : 1024), 0, c.s, a);
     return hip_check(hipGetLastError(), "plan launch");
 }

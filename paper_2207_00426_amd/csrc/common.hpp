@@ -72,6 +72,17 @@ struct Ctx {
     const void *dev_m = nullptr;
 };
 
+// Elements per thread at the finest level by the sequence's own length: E, half
+// of it up to `half` elements, a quarter up to `quarter` (0: no such rule).
+struct ShortRule {
+    int64_t half = 0, quarter = 0;
+    __host__ __device__ int elems(int64_t n, int E) const
+    {
+        const int e = E >> ((n <= half ? 1 : 0) + (n <= quarter ? 1 : 0));
+        return e > 0 ? e : 1;
+    }
+};
+
 // shape of one scan (filter: n_b elements per sequence, smoother: n_b + 1).
 // Level l has tiles of T[l] * E[l] elements, one block of T[l] threads each.
 // A tree level hands one aggregate per tile to the level above; a flat level
@@ -82,17 +93,14 @@ struct ScanShape {
     int T[kMaxLevels] = {};
     int E[kMaxLevels] = {};
     int flat[kMaxLevels] = {};
-    // level 0 of a flat plan: sequences of at most n_short elements fold
-    // E_short per thread instead of E[0] (0: no such rule)
-    int E_short = 0;
-    int64_t n_short = 0;
+    ShortRule few; // level 0 of a flat plan
     int64_t ntiles[kMaxLevels] = {};
     int64_t nelem[kMaxLevels] = {};
 };
 
 // level 0 takes (T0, E0), level 1 (Tup, E1), the levels above (Tup, Eup)
 ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, int Eup,
-                    bool flat0, int E_short = 0, int64_t n_short = 0);
+                    bool flat0, ShortRule few = {});
 // device tile offsets of every level and, where elem_off is given, the
 // element offsets of every level >= 1 (both [B + 1] per level)
 int launch_plan(const Ctx &c, const ScanShape &sh, int extra, int64_t *const *tile_off,

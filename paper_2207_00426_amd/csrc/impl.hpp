@@ -35,16 +35,17 @@ struct Defaults {
     static constexpr int E0_smoother = 2;
     // Kalman steps per thread (steps.hpp): 8 balance the level above, which
     // costs most per element, against the thread's serial steps; a short
-    // sequence leaves the chip idle and only the serial steps count.  The rule
-    // looks at the sequence alone, so that its result does not depend on its
-    // batch.  us per call at 2 and 8 steps: 10 passes of 100 FP64 steps 830 and
-    // 1278, 2 passes of 300 243 and 282, 10 passes of 1003 1685 and 1658; 200
-    // FP32 sequences of ~1800 569 and 317, 2 passes of 10^6 3556 and 2124.
-    // A scalar state has cheap operators and folds 2 (2 passes of 10^4 Ricker
-    // steps: 112 us, with 8 129).
+    // sequence leaves the chip idle and only the serial steps and the rounds
+    // above them count.  The rule looks at the sequence alone, so that its
+    // result does not depend on its batch.  us per call at 2, 4 and 8 steps, 2
+    // FP64 passes: one sequence of 100 158, 181, 249; of 256 206, 198, 264; of 512
+    // 285, 241, 282; of 768 325, 281, 315; of 1003 327, 324, 327; of 10^6 3556,
+    // -, 2095; 60 of 768 398, 327, 375.  One FP32 pass of 300 of 600 steps 735,
+    // 525, 540, of 1000 1070, 788, 647.  A scalar state has cheap operators and
+    // folds 2 (2 passes of 10^4 Ricker steps: 112 us, with 8 129).
     static constexpr int E0_step = NX == 1 ? 2 : 8;
-    static constexpr int E0_step_short = 2;
-    static constexpr int64_t n_step_short = 768;
+    static constexpr int64_t n_half = NX == 1 ? 0 : 768;
+    static constexpr int64_t n_quarter = NX == 1 ? 0 : 256;
     static constexpr int Tup = 64;
     static constexpr int E1_filter = 4;
     static constexpr int E1_smoother = 2;
@@ -242,8 +243,7 @@ struct Core {
         g.B = c.B;
         g.E = sh.E[l];
         g.stage = scan_stage(Op::NE, Op::NP, sh.T[l], sh.E[l], sizeof(T));
-        g.E_short = sh.E_short;
-        g.n_short = l == 0 ? sh.n_short : 0;
+        g.few = l == 0 ? sh.few : ShortRule{};
         return g;
     }
 
@@ -652,8 +652,11 @@ struct Core {
         case PSS_OP_SMOOTHER_SCAN:
             return sscan_bytes(c);
         case PSS_OP_IPLS:
-            return gamma_bytes(c) + felem_bytes(c) + marg_bytes(c) +
-                   std::max(scans, scan_bytes(c, step_shape(c)));
+            // stored elements (covariance form), or the steps' stash, which
+            // is smaller by about a marginal per step
+            return gamma_bytes(c) + marg_bytes(c) +
+                   std::max(felem_bytes(c) + scans, align256(step_stash(c) * sizeof(T)) +
+                                                        scan_bytes(c, step_shape(c)));
         case PSS_OP_LOGLIK:
             return fwd + grad_scans(c, 1);
         case PSS_OP_LOGLIK_GRAD:
@@ -723,12 +726,16 @@ struct Core {
         if (c.p->scan_elems > 0)
             return plan_scan(c, 0, T0, E0, Tup, E1, Eup, true);
         using D = Defaults<T, NX>;
-        return plan_scan(c, 0, T0, D::E0_step, Tup, E1, Eup, true, D::E0_step_short,
-                         D::n_step_short);
+        return plan_scan(c, 0, T0, D::E0_step, Tup, E1, Eup, true,
+                         ShortRule{D::n_half, D::n_quarter});
+    }
+    static size_t step_stash(const Ctx &c)
+    {
+        return (size_t)Sizes<NX>::selem * c.T_y + (size_t)Sizes<NX>::marg * c.B;
     }
     static StepTiles step_tiles(const ScanShape &sh)
     {
-        return StepTiles{sh.T[0], sh.E[0], sh.E_short, sh.n_short};
+        return StepTiles{sh.T[0], sh.E[0], sh.few};
     }
 
     // the same for the log-likelihood calls: at least 4 steps a thread, so that
@@ -749,7 +756,7 @@ struct Core {
         if (!kStepsLL)
             return plan_scan(c, 0, T0, 2, Tup, E1, Eup, true);
         return plan_scan(c, 0, T0, std::max(4, D::E0_step), Tup, E1, Eup, true,
-                         std::max(4, D::E0_step_short), 8192);
+                         ShortRule{NX == 1 ? 0 : 8192, 0});
     }
     static size_t scan_bytes(const Ctx &c, const ScanShape &sh)
     {
@@ -823,9 +830,8 @@ struct Core {
         const ScanShape sh = step_shape(c);
         Carver cv{static_cast<char *>(ws)};
         pss_gamma gw = carve_gamma(cv, c.T_y);
-        // the space of the filter elements: smoother elements, then one
-        // marginal per sequence (felem - selem = marg numbers per step)
-        T *fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
+        // the smoother elements, then one marginal per sequence
+        T *fel = cv.template take<T>(step_stash(c));
         T *mid = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
         const auto w = carve_scan<FS>(cv, c, sh);
         const SElemRef<T, NX> stash = selem_ref(fel, c.T_y);

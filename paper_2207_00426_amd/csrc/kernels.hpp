@@ -15,6 +15,11 @@
 //   level has one tile per sequence; that top level runs fold, up, down and
 //   apply in one kernel; lower levels run an "up" kernel (fold + up-sweep,
 //   LDS tree saved to global) and later a "down" kernel.
+// The square-root scans run these kernels at the finest level only; above it
+// scan_group.hpp gives each element 16 lanes, and inside the smoothing and
+// FP64 gradient passes steps.hpp and adjoint.hpp replace the finest level too.
+// What is left here in full: the covariance form, FP32 log-likelihoods, a scalar
+// state.
 // LDS holds one object per thread, component-major ([c * T + slot]) so that
 // consecutive lanes touch consecutive words.
 #pragma once
@@ -481,9 +486,7 @@ struct LevelGeom {
     int E;
     int stage; // outputs staged in LDS and written by the whole block (needs
                // NP * T * E values of LDS)
-    // level 0: sequences of at most n_short elements take E_short
-    int E_short;
-    int64_t n_short;
+    ShortRule few; // level 0: E by the sequence's length
 };
 
 PSS_INL void seq_range(const LevelGeom &g, int b, int64_t &off, int64_t &cnt)
@@ -544,7 +547,7 @@ PSS_INL TileInfo tile_info(const LevelGeom &g)
     ti.b = find_seq(g.tile_off, g.B, tile, 0);
     const int64_t tin = tile - g.tile_off[ti.b];
     seq_range(g, ti.b, ti.off, ti.cnt);
-    ti.E = ti.cnt <= g.n_short ? g.E_short : g.E;
+    ti.E = g.few.elems(ti.cnt, g.E);
     const int64_t TS = (int64_t)blockDim.x * ti.E;
     ti.start = tin * TS;
     const int64_t rem = ti.cnt - ti.start;
@@ -986,7 +989,8 @@ struct PlanArgs {
     int L;
     int64_t TS[kMaxLevels]; // tile size of level l
     int64_t D[kMaxLevels];  // elements of level l per element of level l + 1
-    int64_t n_short, TS_short, D_short; // level 0 of short sequences (ScanShape)
+    ShortRule few; // level 0, from T0 threads of E0 elements
+    int T0, E0, flat0;
     int64_t *tile_off[kMaxLevels];
     int64_t *elem_off[kMaxLevels]; // may be null
 };

@@ -23,11 +23,13 @@
 // passes are tile-interleaved (ilv): a wave's accesses are whole lines.
 //
 // Measured at 10^6 FP64 coordinated-turn steps, per pass (bound by their
-// bytes; a large copy reaches 4.9 TB/s): fold 0.163 ms for 0.50 GB, walk 0.197
-// ms for 0.86 GB, smooth 0.12 ms for 0.52 GB; they replace element build
+// bytes; a large copy reaches 4.9 TB/s): fold 0.150 ms for 0.56 GB, walk 0.200
+// ms for 0.92 GB, smooth 0.12 ms for 0.54 GB; they replace element build
 // (0.224), filter up and down (0.202, 0.139) and smoother up and down (0.334,
 // 0.191 ms).  Holding fold and walk to 256 registers (two waves a SIMD) gained
-// nothing: 0.161 and 0.221 ms.
+// nothing: 0.161 and 0.221 ms.  Reading the next step's linearisation while
+// this one computes (448 and 466 registers) took the walk to 0.182 ms there, but
+// made short sequences slower: 8 steps of fold 34 -> 36 us, of walk 45 -> 48.
 #pragma once
 
 #include "kernels.hpp"
@@ -50,12 +52,12 @@ struct NomRef {
     }
 };
 
-// tiles of the finest level: T threads of E steps each, E_short for a sequence
-// of at most n_short steps
+// tiles of the finest level: T threads of E steps each, fewer for a short
+// sequence
 struct StepTiles {
-    int T, E, E_short;
-    int64_t n_short;
-    PSS_INL int elems(int64_t n) const { return n <= n_short ? E_short : E; }
+    int T, E;
+    ShortRule few;
+    PSS_INL int elems(int64_t n) const { return few.elems(n, E); }
 };
 
 // k / TS of a step index, in 32 bits wherever k fits (a 64-bit division takes
@@ -524,7 +526,8 @@ __global__ __launch_bounds__(256) void k_gamma_ilv(const int64_t *y_off, int B, 
 // after the other they made a chain of some 4000 instructions, all there is to a
 // short sequence's launch.  A block takes 256 steps that follow each other, so
 // that it reads a plain nominal's lines once, and its lanes follow the slots: a
-// run of 256 / E lanes stores whole lines.
+// run of 256 / E lanes stores whole lines.  FP64 cubature: 100 steps 8.7 us (in
+// one chain 12), 10^6 steps 182 us (one thread per slot 198, per step 255).
 // Lin: trans(marginal, F, c, S_L) and obs(marginal, y, H, d, S_O).
 template <class Lin>
 __global__ __launch_bounds__(256) void k_step_lin(const int64_t *y_off, int B, int64_t T_y,

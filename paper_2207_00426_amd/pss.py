@@ -677,7 +677,7 @@ def _with_theta(batch, theta):
 
 
 # ---------------------------------------------------------------------------
-# ragged multi-group batches (one persistent launch per pass)
+# ragged multi-group batches (the groups of a call run side by side)
 # ---------------------------------------------------------------------------
 class _Groups:
     """ctypes array of pss_group plus the objects it points into (kept alive)."""

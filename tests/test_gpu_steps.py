@@ -57,10 +57,10 @@ def _check(m, N, nx, off, ref, tol):
         assert em < tol["m"] and eP < tol["P"], (b, z - a - 1, em, eP)
 
 
-# one step; a tile of 128 (2 a thread, up to 768 steps) and of 512 (8 a thread
-# beyond), full, one short and one over; group tiles of 256 elements, full and
-# one over (2049 = 257 threads of 8)
-EDGES = [1, 2, 127, 128, 129, 512, 513, 768, 769, 1024, 1025, 2048, 2049]
+# one step; tiles of 128 (2 a thread, up to 256 steps), of 256 (4, up to 768)
+# and of 512 (8 beyond), full, one short and one over; group tiles of 256
+# elements, full and one over (2049 = 257 threads of 8)
+EDGES = [1, 2, 127, 128, 129, 256, 257, 511, 513, 768, 769, 1024, 1025, 2048, 2049]
 
 
 @pytest.mark.parametrize("tag", ["f64", "f32"])
@@ -85,7 +85,7 @@ def test_bearings_passes_at_tile_edges(lin, tag, elems):
     """Linearisation into tile order (blocks of 256 steps across sequences) and
     the nominal between passes, at the default and at forced steps a thread."""
     dt = _dt(tag)
-    lens = [1, 129, 254, 768, 769, 2]
+    lens = [1, 129, 254, 257, 768, 769, 2]
     b, ys, yd = _ct(lens, 5, dt, linearization=lin, scan_elems=elems)
     m, N = pss.ipls_iterate(b, yd, 2)
     torch.cuda.synchronize()
