@@ -209,9 +209,10 @@ struct Side {
     hipStream_t s = nullptr;
     hipEvent_t done = nullptr;
 };
-constexpr size_t kMaxIdle = 8;
+constexpr int kMaxIdle = 8;
 std::mutex g_side_mu;
-std::vector<Side> g_side;
+Side g_side[kMaxIdle]; // the first g_idle (no allocation: returned in a destructor)
+int g_idle = 0;
 
 void free_side(Side &x)
 {
@@ -225,10 +226,10 @@ bool take_side(int dev, Side &x)
 {
     {
         std::lock_guard<std::mutex> lk(g_side_mu);
-        for (size_t i = 0; i < g_side.size(); ++i)
+        for (int i = 0; i < g_idle; ++i)
             if (g_side[i].dev == dev) {
                 x = g_side[i];
-                g_side.erase(g_side.begin() + i);
+                g_side[i] = g_side[--g_idle];
                 return true;
             }
     }
@@ -245,8 +246,8 @@ void give_side(Side &x)
 {
     {
         std::lock_guard<std::mutex> lk(g_side_mu);
-        if (g_side.size() < kMaxIdle) {
-            g_side.push_back(x);
+        if (g_idle < kMaxIdle) {
+            g_side[g_idle++] = x;
             return;
         }
     }
@@ -307,7 +308,13 @@ struct Fork {
         }
         return rc;
     }
-    ~Fork() { (void)join(); }
+    ~Fork()
+    {
+        try {
+            (void)join();
+        } catch (...) { // an error's message could not be kept
+        }
+    }
     Fork(const Fork &) = delete;
     Fork &operator=(const Fork &) = delete;
 };
