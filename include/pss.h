@@ -428,13 +428,16 @@ typedef struct pss_group {
 /* Workspace bytes of pss_ipls_batched for these groups (0 if invalid). */
 size_t pss_batched_workspace_size(const pss_group *groups, int32_t n_groups);
 
-/* Algorithm 3 for up to 4 groups of ragged sequences: the passes of
-   pss_ipls_iterate on each group, with the same results.  The groups run side
-   by side, each in its own part of the workspace: all but the first on streams
-   of the library, which start after the work that `stream` holds and which
-   `stream` waits for before anything enqueued later.  While `stream` is
-   captured they run one after the other on it.  `status` (device int,
-   nullable) is set to 0.
+/* Algorithm 3 for up to 4 groups of ragged sequences: on each group the passes
+   of pss_ipls_iterate at the launch shape below, except for FP32 coordinated-
+   turn groups: their scans run over chained tiles (default 256 threads of 4
+   elements), in FP32 and absolute coordinates, so that their results, which
+   carry rounding of up to some 1e-5, stay comparable with stored ones.  The
+   groups run side by side, each in its own part of the workspace: all but the
+   first on streams of the library, which start after the work that `stream`
+   holds and which `stream` waits for before anything enqueued later.  While
+   `stream` is captured they run one after the other on it.  `status` (device
+   int, nullable) is set to 0.
    Launch shape: the problem's overrides, else the autotuned shape for this
    batch signature (pss_autotune, or the file named by the environment
    variable PSS_TUNE_CACHE), else defaults.  Bitwise reproducible for a

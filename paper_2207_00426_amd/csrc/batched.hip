@@ -1,17 +1,20 @@
 // Ragged batches of several model groups, and the autotuner of their launch
 // shape.
 //
-// Each group runs the passes of pss_ipls_iterate: its launches cover every
-// tile of every sequence, which is what fills the chip.  One persistent launch
-// per pass, whose tiles chained through a work queue, took 1.22 ms for a call of
-// 400 ragged FP32 sequences (830 000 steps of two models) where these launches
-// take 0.77 ms one group after the other and 0.63 ms side by side: it ran every stage at the registers of its heaviest one, a wave per
-// SIMD, and its chains wrote the L2 back tile by tile.
+// Each group's passes are launches over every tile of every sequence, which is
+// what fills the chip: those of pss_ipls_iterate, except that FP32 bearings
+// tracks keep chained tiles and FP32 operators (Core::ipls_tiles).  One
+// persistent launch per pass, whose tiles chained through a work queue, took
+// 1.26 ms for a call of 400 ragged FP32 sequences (830 000 steps of two models)
+// where these launches take 0.87 ms, with the same bits for the tracks: it ran
+// every stage at the registers of its heaviest one, a wave per SIMD, and its
+// chains wrote the L2 back tile by tile.  (0.72 ms were the tracks to run
+// ipls_iterate's steps.)
 //
 // The groups share nothing, so all but the first run on streams of their own
 // between two events: a few short sequences leave the chip idle through every
-// launch (three of each model, 206 to 1652 FP32 steps: 276 us instead of 368),
-// and long ones fill each other's last waves.
+// launch (three FP32 sequences of each model, 360 to 1032 steps: 352 us), and
+// long ones fill each other's last waves.
 #include <math.h>
 #include <stdio.h>
 
@@ -185,9 +188,27 @@ pss_problem shaped(const pss_group &g, const Shape &sh)
     return p;
 }
 
+// FP32 bearings tracks run in chained tiles (Core::ipls_tiles), 256 threads of
+// 4 elements where neither an override nor the tuner says otherwise
+bool tiled(const pss_problem *p)
+{
+    return p->dtype == PSS_F32 && kind_of(p) == kGroupCT;
+}
+TileChain tile_chain(const Shape &sh)
+{
+    return TileChain{sh.T > 0 ? sh.T : 256, sh.E_f > 0 ? sh.E_f : 4, sh.E_s > 0 ? sh.E_s : 4};
+}
+Ctx ctx_of(const pss_problem *p, hipStream_t s)
+{
+    const int64_t T_y = p->y_off_host[p->B];
+    return Ctx{p, p->B, T_y, T_y + p->B, s};
+}
+
 // the groups run side by side, each in its own part of the space
 size_t group_bytes(const pss_group &g, const Shape &sh)
 {
+    if (tiled(g.p))
+        return align256(Impl<float, 5, 2>::tiles_bytes(ctx_of(g.p, nullptr), tile_chain(sh)));
     const pss_problem p = shaped(g, sh);
     return align256(pss_workspace_size(&p, PSS_OP_IPLS));
 }
@@ -337,7 +358,7 @@ int run(const pss_group *gs, int ng, int n_iter, int32_t *status, void *ws, size
         hipStream_t s, const Shape &sh)
 {
     // a shape from a cache file may hold anything
-    if ((sh.T != 0 && sh.T != 64 && sh.T != 128 && sh.T != 256) || sh.E_f < 0) {
+    if ((sh.T != 0 && sh.T != 64 && sh.T != 128 && sh.T != 256) || sh.E_f < 0 || sh.E_s < 0) {
         set_error("batched: block threads must be 64, 128 or 256, elements at least 1");
         return PSS_EINVAL;
     }
@@ -353,9 +374,16 @@ int run(const pss_group *gs, int ng, int n_iter, int32_t *status, void *ws, size
     Fork fork(s, ng - 1);
     Carver cv{static_cast<char *>(ws)};
     for (int i = ng - 1; i >= 0; --i) { // the side streams' work first
-        const pss_problem p = shaped(gs[i], sh);
         const size_t bytes = group_bytes(gs[i], sh);
         char *part = cv.take<char>(bytes);
+        if (tiled(gs[i].p)) {
+            if (int rc = Impl<float, 5, 2>::ipls_tiles(ctx_of(gs[i].p, fork.stream(i)),
+                                                       tile_chain(sh), gs[i].y, n_iter,
+                                                       gs[i].m_nom, gs[i].N_nom, part))
+                return rc;
+            continue;
+        }
+        const pss_problem p = shaped(gs[i], sh);
         if (int rc = pss_ipls_iterate(&p, gs[i].g, gs[i].y, n_iter, gs[i].m_nom, gs[i].N_nom,
                                       nullptr, nullptr, part, bytes, fork.stream(i)))
             return rc;

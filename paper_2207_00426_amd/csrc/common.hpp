@@ -140,6 +140,11 @@ bool rule_host(const pss_problem *p, int nx, RuleHost &r);
 // workspace of pss_loglik_grad_ift (defined in ift.hip)
 size_t ift_ws_size(const pss_problem *p);
 
+// tiles of ipls_tiles: threads, elements a thread in the filter and the smoother
+struct TileChain {
+    int T, E_f, E_s;
+};
+
 // one implementation per (dtype, nx, ny); defined in impl.hpp, explicitly
 // instantiated in inst.hip
 template <typename T, int NX, int NY>
@@ -153,6 +158,9 @@ struct Impl {
                      void *Ns, void *ws);
     static int ipls(const Ctx &c, const pss_gamma *g, const void *y, int n_iter, void *m_nom,
                     void *N_nom, void *mf_out, void *Nf_out, void *ws);
+    static size_t tiles_bytes(const Ctx &c, const TileChain &tc);
+    static int ipls_tiles(const Ctx &c, const TileChain &tc, const void *y, int n_iter,
+                          void *m_nom, void *N_nom, void *ws);
     static int loglik(const Ctx &c, const pss_gamma *g, const void *m_nom, const void *N_nom,
                       const void *y, double *ll, const pss_ckpt *ckpt, void *ws);
     static int loglik_grad(const Ctx &c, const void *m_nom, const void *N_nom, const void *y,

@@ -1278,20 +1278,20 @@ PSS_INL void ct_slr_transition(const CTParams<T> &P, const Marg<T, 5> &mg, T (&F
     CTPhiMean<T> b;
     ct_phi_mean(P, mg, b);
     T ep[5][5], em[5][5];
-    auto points = [&](auto &&dsa, auto &&dsh) {
+    // images of the sigma point pair i
+    auto pair = [&](int i, auto &&dev) {
+        T dlt[5], zp[5], zm[5];
+        sigma_offset(mg, i, dlt);
+        dev(dlt, zp, zm);
 #pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            T dlt[5], zp[5], zm[5];
-            sigma_offset(mg, i, dlt);
-            const T da = dlt[4] * P.dt, ha = T(0.5) * da;
-            ct_phi_dev(P, b, dlt[2], dlt[3], dlt[4], da, dsa(da), dsh(ha), zp);
-            ct_phi_dev(P, b, -dlt[2], -dlt[3], -dlt[4], -da, dsa(-da), dsh(-ha), zm);
-#pragma unroll
-            for (int a = 0; a < 5; ++a) {
-                ep[a][i] = zp[a];
-                em[a][i] = zm[a];
-            }
+        for (int a = 0; a < 5; ++a) {
+            ep[a][i] = zp[a];
+            em[a][i] = zm[a];
         }
+    };
+    auto apart = [&](const T (&dlt)[5], T (&zp)[5], T (&zm)[5]) {
+        ct_phi_dev(P, b, dlt[2], dlt[3], dlt[4], zp);
+        ct_phi_dev(P, b, -dlt[2], -dlt[3], -dlt[4], zm);
     };
     T far = T(0);
     if constexpr (SHARE) {
@@ -1302,10 +1302,17 @@ PSS_INL void ct_slr_transition(const CTParams<T> &P, const Marg<T, 5> &mg, T (&F
     }
     if (SHARE && far < T(0.5)) {
         const DSincAt<T> dsa(b.a), dsh(T(0.5) * b.a);
-        points(dsa, dsh);
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+            pair(i, [&](const T (&dlt)[5], T (&zp)[5], T (&zm)[5]) {
+                const T da = dlt[4] * P.dt, ha = T(0.5) * da;
+                ct_phi_dev(P, b, dlt[2], dlt[3], dlt[4], da, dsa(da), dsh(ha), zp);
+                ct_phi_dev(P, b, -dlt[2], -dlt[3], -dlt[4], -da, dsa(-da), dsh(-ha), zm);
+            });
     } else {
-        points([&](T d) { return dsinc(b.a, d); },
-               [&](T d) { return dsinc(T(0.5) * b.a, d); });
+#pragma unroll
+        for (int i = 0; i < 5; ++i)
+            pair(i, apart);
     }
     cubature_from_dev(mg, P.LQ, ep, em, b.phi, F, c, S);
 #pragma unroll

@@ -886,6 +886,138 @@ struct Core {
         return rc;
     }
 
+    // ------------------------------------------------------------------
+    // Algorithm 3 over tiles of T threads of E elements whose prefixes are
+    // chained one tile after the other, everything in the type's own precision
+    // and in absolute coordinates: FP32 bearings tracks of pss_ipls_batched.
+    // Their results carry rounding of up to some 1e-5 (a bearings track is
+    // ill-conditioned in FP32), so another bracketing, deviation coordinates or
+    // FP64 steps move them by as much (measured up to 3.5e-5), and callers
+    // compare them with stored ones: operators, coordinates and brackets stay
+    // what they are.
+    static ScanShape chain_shape(const Ctx &c, int extra, int T0, int E0)
+    {
+        ScanShape sh = plan_scan(c, extra, T0, E0, T0, E0, E0, false);
+        sh.L = 1; // the chain takes the place of the levels above
+        return sh;
+    }
+    template <class Op>
+    static ScanWs<Op> carve_chain(Carver &cv, const Ctx &c, const ScanShape &sh)
+    {
+        ScanWs<Op> w{};
+        w.tile_off[0] = cv.template take<int64_t>(c.B + 1);
+        w.agg[1] = cv.template take<T>((size_t)Op::NE * sh.ntiles[0]);
+        w.pre[1] = cv.template take<T>((size_t)Op::NP * sh.ntiles[0]);
+        return w;
+    }
+    // everything but the chains' trees, which share one space
+    struct TilesWs {
+        ScanShape sh_f, sh_s;
+        pss_gamma gam; // transition part only
+        T *fel, *mf, *stash;
+        ScanWs<FS> f;
+        ScanWs<SS> s;
+    };
+    static TilesWs carve_tiles(Carver &cv, const Ctx &c, const TileChain &tc)
+    {
+        TilesWs w{};
+        w.sh_f = chain_shape(c, 0, tc.T, tc.E_f);
+        w.sh_s = chain_shape(c, 1, tc.T, tc.E_s);
+        w.gam.F = cv.template take<T>((size_t)NX * NX * c.T_y);
+        w.gam.c = cv.template take<T>((size_t)NX * c.T_y);
+        w.gam.SL = cv.template take<T>((size_t)P * c.T_y);
+        w.gam.stride = 1;
+        w.fel = cv.template take<T>((size_t)Sizes<NX>::felem * c.T_y);
+        w.mf = cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
+        w.stash = cv.template take<T>((size_t)Sizes<NX>::selem * c.T_x);
+        w.f = carve_chain<FS>(cv, c, w.sh_f);
+        w.s = carve_chain<SS>(cv, c, w.sh_s);
+        const size_t nt = std::max((size_t)FS::NE * w.sh_f.ntiles[0],
+                                   (size_t)SS::NE * w.sh_s.ntiles[0]);
+        w.f.tree[0] = w.s.tree[0] = cv.template take<T>(nt * tc.T);
+        return w;
+    }
+    static size_t tiles_bytes(const Ctx &c, const TileChain &tc)
+    {
+        Carver cv{nullptr};
+        carve_tiles(cv, c, tc);
+        return cv.used;
+    }
+    template <class Op, class Src, class Dst, class AggRef, class Start>
+    static int run_chain(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int extra,
+                         const Src &src, const Dst &dst, const Start &start,
+                         AggRef (*agg_ref)(T *, int64_t))
+    {
+        using Pre = MargRef<T, NX>;
+        const LevelGeom g = level_geom(c, sh, w, 0, extra);
+        const int64_t nt = sh.ntiles[0], tree_ld = nt * sh.T[0];
+        const size_t lb = lds_bytes<Op>(sh.T[0], sh.E[0], g.stage);
+        const dim3 grid((unsigned)nt), block(sh.T[0]);
+        const AggRef agg = agg_ref(w.agg[1], nt);
+        const Pre pre = marg_ref(w.pre[1], nt);
+        int rc;
+        {
+            KTime kt(c.s, Op::name, "up", 0);
+            auto k = k_scan_up<Op, Src, AggRef>;
+            if ((rc = prep_lds(k, lb)))
+                return rc;
+            hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src, agg, w.tree[0], tree_ld);
+            if ((rc = hip_check(hipGetLastError(), "scan up launch")))
+                return rc;
+        }
+        {
+            KTime kt(c.s, Op::name, "chain", 0);
+            hipLaunchKernelGGL((k_scan_chain<Op, AggRef, Start>), dim3((unsigned)((c.B + 63) / 64)),
+                               dim3(64), 0, c.s, w.tile_off[0], c.B, agg, pre, start);
+            if ((rc = hip_check(hipGetLastError(), "scan chain launch")))
+                return rc;
+        }
+        KTime kt(c.s, Op::name, "down", 0);
+        auto k = k_scan_down<Op, Src, Dst, Pre>;
+        if ((rc = prep_lds(k, lb)))
+            return rc;
+        hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src, dst, w.tree[0], tree_ld, pre);
+        return hip_check(hipGetLastError(), "scan down launch");
+    }
+    static int ipls_tiles(const Ctx &c, const TileChain &tc, const void *y, int n_iter,
+                          void *m_nom, void *N_nom, void *ws)
+    {
+        // its linearisation and elements are one kernel (slr_felem), FP32 CT only
+        if constexpr (NX == 5 && NY == 2 && std::is_same_v<T, float>) {
+            Carver cv{static_cast<char *>(ws)};
+            const TilesWs w = carve_tiles(cv, c, tc);
+            pss_problem p = *c.p; // the elements are interleaved for these tiles
+            p.scan_threads = tc.T;
+            p.scan_elems = tc.E_f;
+            Ctx cs = c;
+            cs.p = &p;
+            int rc = launch_plan(cs, w.sh_f, 0, w.f.tile_off);
+            if (!rc)
+                rc = launch_plan(cs, w.sh_s, 1, w.s.tile_off);
+            FElemRef<T, NX> fr = felem_ref(w.fel, c.T_y);
+            const pss_felem el{fr.A, fr.b, fr.U, fr.eta, fr.Z};
+            const MargRef<T, NX> mf = marg_ref(w.mf, c.T_x);
+            constexpr int LZ = NY < NX ? NY : NX;
+            const RefSrc<FS, FElemRef<T, NX>, true, LZ> fsrc{fr};
+            const FiltDst<T, NX> fdst{mf, c.p->y_off};
+            const SmootherSrc<T, NX, NY> ssrc{gamma_ref(&w.gam, c.T_y), mf,
+                                              selem_ref(w.stash, c.T_x), c.p->y_off};
+            const SmoothDst<T, NX> sdst{marg_ref2(m_nom, N_nom, c.T_x)};
+            const StartPre<T, NX> st{cptr<T>(c.p->m0), cptr<T>(c.p->N0)}, none{nullptr, nullptr};
+            for (int it = 0; it < n_iter && rc == PSS_OK; ++it) {
+                if ((rc = slr_felem(cs, m_nom, N_nom, y, &w.gam, &el, false, false)))
+                    break;
+                if ((rc = run_chain(cs, w.sh_f, w.f, 0, fsrc, fdst, st, &felem_ref)))
+                    break;
+                rc = run_chain(cs, w.sh_s, w.s, 1, ssrc, sdst, none, &selem_ref);
+            }
+            return rc;
+        } else {
+            set_error("chained tiles are built for FP32 bearings tracks only");
+            return PSS_EUNSUPPORTED;
+        }
+    }
+
     // a linear model's given linearisation: shared by all steps as it is, per
     // step into interleaved slots
     static int step_given(const Ctx &c, const pss_gamma *gin, const pss_gamma &gw,
@@ -1618,6 +1750,17 @@ int Impl<T, NX, NY>::ipls(const Ctx &c, const pss_gamma *g, const void *y, int n
                           void *m_nom, void *N_nom, void *mf_out, void *Nf_out, void *ws)
 {
     return Core<T, NX, NY>::ipls(c, g, y, n_iter, m_nom, N_nom, mf_out, Nf_out, ws);
+}
+template <typename T, int NX, int NY>
+size_t Impl<T, NX, NY>::tiles_bytes(const Ctx &c, const TileChain &tc)
+{
+    return Core<T, NX, NY>::tiles_bytes(c, tc);
+}
+template <typename T, int NX, int NY>
+int Impl<T, NX, NY>::ipls_tiles(const Ctx &c, const TileChain &tc, const void *y, int n_iter,
+                                void *m_nom, void *N_nom, void *ws)
+{
+    return Core<T, NX, NY>::ipls_tiles(c, tc, y, n_iter, m_nom, N_nom, ws);
 }
 template <typename T, int NX, int NY>
 int Impl<T, NX, NY>::loglik(const Ctx &c, const pss_gamma *g, const void *m_nom,

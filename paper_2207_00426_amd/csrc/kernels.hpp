@@ -981,6 +981,30 @@ __global__ __launch_bounds__(256) void k_scan_top(LevelGeom g, Src src, Dst dst,
     apply_phase<Op>(g, ti, src, dst, lds, Tb);
 }
 
+// the tiles' exclusive prefixes from their aggregates, tile by tile: one thread
+// per sequence (a level of one tile after the other, where the bracketing has
+// to be that of a chain)
+template <class Op, class AggRef, class Start>
+__global__ __launch_bounds__(64) void k_scan_chain(const int64_t *tile_off, int B, AggRef agg,
+                                                   MargRef<typename Op::T, Op::NX> pre,
+                                                   Start start)
+{
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= B)
+        return;
+    const int64_t end = tile_off[b + 1];
+    typename Op::Pre p;
+    start.get(p);
+    for (int64_t t = tile_off[b]; t < end; ++t) {
+        pre.store(t, p);
+        if (t + 1 < end) {
+            typename Op::Pre q;
+            Op::apply_v(p, view_of(agg, t), q);
+            p = q;
+        }
+    }
+}
+
 // tile offsets of every level, one thread per sequence + a block scan
 struct PlanArgs {
     const int64_t *y_off;
