@@ -73,10 +73,10 @@ from paper_2207_00426_amd import workloads as wl  # noqa: E402
 # the filter operator with a finest-level element on the right, whose Z has
 # only ny non-zero columns.  adjoint_element: the Kalman step and its map
 # T_k; adjoint_cotangents: the Gram cotangents and the theta contraction.
-FLOPS = dict(filter_combine=3310, filter_combine_leaf=2517, filter_apply=1940,
-             filter_apply_leaf=1432, smoother_combine=750, smoother_apply=525,
-             filter_element=1310, smoother_element=1545, slr_transition=1518, slr_bearings=323,
-             adjoint_element=1272, adjoint_combine=740, adjoint_apply=515,
+FLOPS = dict(filter_combine=3420, filter_combine_leaf=2627, filter_apply=2030,
+             filter_apply_leaf=1522, smoother_combine=770, smoother_apply=545,
+             filter_element=1372, smoother_element=1635, slr_transition=1538, slr_bearings=325,
+             adjoint_element=1314, adjoint_combine=740, adjoint_apply=515,
              adjoint_cotangents=966)
 PEAK = {"f64": 78.6, "f32": 78.6}  # TFLOP/s vector ALU (FP32 without packed instructions)
 HBM_GBPS = 8000.0  # MI355X HBM3E peak

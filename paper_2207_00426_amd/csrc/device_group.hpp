@@ -100,23 +100,12 @@ __device__ __forceinline__ void lq(T (&row)[C], int rho, T (&inv)[K])
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
             sig = pfma(x[j], x[j], sig);
-        T beta, tau, d;
-        bool neg;
-        reflector(x[i], sig, beta, tau, d, neg);
-        inv[i] = tau * beta;
+        const Reflector<T> h(x[i], sig);
+        inv[i] = h.q;
         // every row takes the reflection: on a row that is already reduced it
         // reaches only columns right of that row's diagonal, which are stale
-        const T ap = pflip(row[i], neg);
-        T w = -(beta * ap);
-#pragma unroll
-        for (int j = i + 1; j < jend; ++j)
-            w = pfma(row[j], x[j], w);
-        const T tw = tau * w;
-        const T nw = pfma(tw, beta, ap);
-        row[i] = rho == i ? d : nw;
-#pragma unroll
-        for (int j = i + 1; j < jend; ++j)
-            row[j] = pfma(-tw, x[j], row[j]);
+        h.row(row, x, i, jend);
+        row[i] = rho == i ? h.d : row[i];
     });
 }
 

@@ -67,26 +67,28 @@ PSS_INL float pldexp(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 // of Lemmas 1-3), the sweep never touches those columns.  Z0 = C disables
 // the shortcut.
 //
-// Reflector of row x = (a, t) (pivot a, tail t, s = |x|^2, r = |x|), FP64: the
-// pivot entry of v is a + sign(a) r, so nothing cancels and its size beta =
-// |a| + r serves both signs; v = (sign(a) beta, t), |v|^2 = 2 r beta, and the
-// reflection I - tau v v^T with tau = 1 / (r beta) maps x to (-sign(a) r, 0,
-// ...).  For a > 0 column i is then negated, which keeps the diagonal
-// non-negative; the negation is folded into the update as a sign flip of the
-// entry read.  One root and one reciprocal per row, each a hardware estimate
-// with Newton steps (the form with the pivot a - r needs a second reciprocal,
-// and a correctly rounded root costs twice the estimate's steps: a row's
-// scalar chain was ~45 instructions, now ~22; together with the reflections
-// that Table 3 no longer runs, one smoothing pass of 30 011 FP64 steps fell from
-// 456 to 404 us, of 10^6 steps from 1886 to 1778 us).
+// Reflector of row x = (a, t) (pivot a, tail t, s = |t|^2, r = |x|), FP64.  For
+// a row b below, taken with its pivot entry's sign flipped where a < 0 (a' =
+// |a|, b' likewise), the result is
+//   b0 <- b0' + w / r,   w = (a' - r) b0' + t . b_t
+//   b_t <- b_t - t (b0 + b0') / (a' + r)
+// : the new pivot entry (a' b0' + t . b_t) / r as a correction of the old one,
+// small where the tail is, with a' - r = -s / (a' + r); and the tail of the
+// reflection with the pivot a' + r, in which nothing cancels.  (The two belong
+// together: that reflection sends b0' to minus the new entry, and column i is
+// then negated, which also keeps the diagonal non-negative.)  One root, whose
+// estimate's Newton steps give 1 / r as well, and one reciprocal per row.
+// Error of the Gram of the 5 x 10 matrix [X, e Y], X and Y lower, rms in units
+// of 2^-53: 1.04 (e = 1), 0.65 (1e-2 to 1e-6); of the form with the pivot a - r
+// and two reciprocals 1.8 and 0.65, with the pivot a + r throughout 1.9 and 2.7.
+// The scalar chain is some 25 operations (two reciprocals and a correctly
+// rounded root: 45).
 //
-// FP32 keeps the pivot a - r, taken as -s_t / (a + r) for a > 0 (s_t = |t|^2),
-// the rounded root and a threshold under which a tail leaves a positive pivot
-// alone: where the tail is small the FP64 form rebuilds the rows below from
-// two parts of their size, which loses a few ulp that FP32 results show (their
-// error against 64 bits rose 1.7 times on a batch of short tracks).  Each FP32
-// row is first scaled by a power of two near its largest magnitude, so squares
-// neither overflow nor fall into the subnormal range.
+// FP32 keeps the pivot a - r, taken as -s / (a + r) for a > 0, the rounded root
+// and a threshold under which a tail leaves a positive pivot alone: results in
+// FP32 show a change of rounding.  Each FP32 row is first scaled by a power of
+// two near its largest magnitude, so squares neither overflow nor fall into the
+// subnormal range.
 //
 // A row of zeros (or whose squares vanish) is left alone; a NaN goes through
 // to the diagonal.
@@ -100,20 +102,26 @@ PSS_INL float pabs(float x) { return fabsf(x); }
 PSS_INL double pmax(double a, double b) { return fmax(a, b); }
 PSS_INL float pmax(float a, float b) { return fmaxf(a, b); }
 
-// sqrt(s) to ~1 ulp for normal s > 0: reciprocal-root estimate (~2^-23
-// relative error), one coupled Newton step for root and half reciprocal root,
-// one residual correction
+// r = sqrt(s) and q = 1 / r to ~1 ulp for normal s > 0: reciprocal-root
+// estimate (~2^-23 relative error), one coupled Newton step for root and half
+// reciprocal root, one correction of each from the root's residual
 template <typename T>
-PSS_INL T pnorm(T s) { return psqrt(s); }
-template <>
-PSS_INL double pnorm(double s)
+PSS_INL void pnorm(T s, T &r, T &q)
 {
-    const double r = __builtin_amdgcn_rsq(s);
-    double g = s * r, h = 0.5 * r;
+    r = psqrt(s);
+    q = prcp(r);
+}
+template <>
+PSS_INL void pnorm(double s, double &r, double &q)
+{
+    const double y = __builtin_amdgcn_rsq(s);
+    double g = s * y, h = 0.5 * y;
     const double e = fma(-h, g, 0.5);
     g = fma(g, e, g);
     h = fma(h, e, h);
-    return fma(fma(-g, g, s), h, g);
+    r = fma(fma(-g, g, s), h, g);
+    q = h + h;
+    q = fma(q, fma(-q, r, 1.0), q);
 }
 
 // x with its sign flipped where neg
@@ -130,37 +138,77 @@ PSS_INL double pflip(double x, bool neg)
     return v.d;
 }
 
-// beta, tau, the reduced diagonal d and the column's sign from a row's pivot
-// and the sum of squares of its tail.  A vanishing row is masked out by a
-// factor, not by a branch around the root and the reciprocal (the compiler
-// makes one of a select there): beta = d = tau = 0.
+// The reflector from a row's pivot and the sum of squares of its tail: d is the
+// reduced diagonal, q = 1 / d.  A vanishing row is masked out by a factor, not
+// by a branch around the root and the reciprocal (the compiler makes one of a
+// select there): d, q and the reflection are zero.
 template <typename T>
-PSS_INL void reflector(T al, T sig, T &beta, T &tau, T &d, bool &neg)
-{
-    constexpr double tiny = 1e-290;
-    const T s = pfma(al, al, sig);
-    const T on = s > T(tiny) ? T(1) : T(0);
-    const T nr = pnorm(pmax(s, T(tiny)));
-    const T aa = pabs(al);
-    tau = prcp(nr * (aa + nr)) * on;
-    // s - s: NaN where the row's norm is not finite
-    d = pfma(nr, on, s - s);
-    beta = pfma(aa, on, d);
-    neg = al > T(0);
-}
+struct Reflector {
+    T d, q, v0, k;
+    bool neg;
+    PSS_INL Reflector(T al, T sig)
+    {
+        constexpr double tiny = 1e-290;
+        const T s = pfma(al, al, sig);
+        const T on = s > T(tiny) ? T(1) : T(0);
+        T r;
+        pnorm(pmax(s, T(tiny)), r, q);
+        const T aa = pabs(al);
+        k = prcp(aa + r);
+        v0 = -(sig * k);
+        k = k * on;
+        q = q * on;
+        // s - s: NaN where the row's norm is not finite
+        d = pfma(r, on, s - s);
+        neg = al < T(0);
+    }
+    // row b below, x the reflecting one: columns i to jend
+    template <int C>
+    PSS_INL void row(T (&b)[C], const T (&x)[C], int i, int jend) const
+    {
+        const T bp = pflip(b[i], neg);
+        T w = v0 * bp;
+        if (i + 1 < jend) { // the tail first: it does not wait for the root
+            w = b[i + 1] * x[i + 1];
+#pragma unroll
+            for (int j = i + 2; j < jend; ++j)
+                w = pfma(b[j], x[j], w);
+            w = pfma(v0, bp, w);
+        }
+        b[i] = pfma(w, q, bp);
+        const T u = (b[i] + bp) * k;
+#pragma unroll
+        for (int j = i + 1; j < jend; ++j)
+            b[j] = pfma(-u, x[j], b[j]);
+    }
+};
 template <>
-PSS_INL void reflector(float al, float sig, float &beta, float &tau, float &d, bool &neg)
-{
-    const float nr = psqrt(pfma(al, al, sig));
-    const float v0 = (al > 0.0f) ? -sig * prcp(al + nr) : (al - nr);
-    const float p = nr * v0;
-    const bool skip =
-        !(p < 0.0f) || (al > 0.0f && sig <= Eps<float>::v * Eps<float>::v * al * al);
-    tau = skip ? 0.0f : -prcp(p);
-    beta = -v0;
-    d = (skip && al > 0.0f) ? al : nr;
-    neg = false;
-}
+struct Reflector<float> {
+    float d, v0, tau;
+    PSS_INL Reflector(float al, float sig)
+    {
+        const float r = psqrt(pfma(al, al, sig));
+        v0 = (al > 0.0f) ? -sig * prcp(al + r) : (al - r);
+        const float p = r * v0;
+        const bool skip =
+            !(p < 0.0f) || (al > 0.0f && sig <= Eps<float>::v * Eps<float>::v * al * al);
+        tau = skip ? 0.0f : -prcp(p);
+        d = (skip && al > 0.0f) ? al : r;
+    }
+    template <int C>
+    PSS_INL void row(float (&b)[C], const float (&x)[C], int i, int jend) const
+    {
+        float w = v0 * b[i];
+#pragma unroll
+        for (int j = i + 1; j < jend; ++j)
+            w = pfma(b[j], x[j], w);
+        const float tw = tau * w;
+        b[i] = pfma(-tw, v0, b[i]);
+#pragma unroll
+        for (int j = i + 1; j < jend; ++j)
+            b[j] = pfma(-tw, x[j], b[j]);
+    }
+};
 
 template <int K, int Z0, typename T, int R, int C>
 PSS_INL void lq_rows(T (&A)[R][C])
@@ -185,25 +233,11 @@ PSS_INL void lq_rows(T (&A)[R][C])
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
             sig = pfma(A[i][j], A[i][j], sig);
-        T beta, tau, d;
-        bool neg;
-        reflector(A[i][i], sig, beta, tau, d, neg);
+        const Reflector<T> h(A[i][i], sig);
 #pragma unroll
-        for (int r = i + 1; r < R; ++r) {
-            // the pivot column as it will be signed; the row's product with v
-            // is then -beta ap + sum of the tail's products
-            const T ap = pflip(A[r][i], neg);
-            T w = -(beta * ap);
-#pragma unroll
-            for (int j = i + 1; j < jend; ++j)
-                w = pfma(A[r][j], A[i][j], w);
-            const T tw = tau * w;
-            A[r][i] = pfma(tw, beta, ap);
-#pragma unroll
-            for (int j = i + 1; j < jend; ++j)
-                A[r][j] = pfma(-tw, A[i][j], A[r][j]);
-        }
-        A[i][i] = kScale ? pldexp(d, ex) : d;
+        for (int r = i + 1; r < R; ++r)
+            h.row(A[r], A[i], i, jend);
+        A[i][i] = kScale ? pldexp(h.d, ex) : h.d;
     }
 }
 

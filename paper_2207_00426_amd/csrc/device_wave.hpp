@@ -11,7 +11,7 @@
 // are simply absent; a lane outside the matrix carries rho = -1 and is never
 // updated.
 //
-// The reflector is pss::reflector, as in pss::lq_rows, so a wave sweep and a
+// The reflector is pss::Reflector, as in pss::lq_rows, so a wave sweep and a
 // one-thread sweep of the same matrix differ only in where each row's
 // arithmetic runs.
 #pragma once
@@ -74,23 +74,11 @@ __device__ __forceinline__ void lq_rows(T (&a)[C], int rho)
 #pragma unroll
         for (int j = i + 1; j < jend; ++j)
             sig = pfma(x[j], x[j], sig);
-        T beta, tau, d;
-        bool neg;
-        reflector(x[i], sig, beta, tau, d, neg);
-        if (rho > i) {
-            const T ap = pflip(a[i], neg);
-            T w = -(beta * ap);
-#pragma unroll
-            for (int j = i + 1; j < jend; ++j)
-                w = pfma(a[j], x[j], w);
-            const T tw = tau * w;
-            a[i] = pfma(tw, beta, ap);
-#pragma unroll
-            for (int j = i + 1; j < jend; ++j)
-                a[j] = pfma(-tw, x[j], a[j]);
-        }
+        const Reflector<T> h(x[i], sig);
+        if (rho > i)
+            h.row(a, x, i, jend);
         if (rho == i)
-            a[i] = kScale ? pldexp(d, ex) : d;
+            a[i] = kScale ? pldexp(h.d, ex) : h.d;
     }
 }
 
