@@ -90,8 +90,9 @@ PSS_INL float pldexp(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 // two near its largest magnitude, so squares neither overflow nor fall into the
 // subnormal range.
 //
-// A row of zeros (or whose squares vanish) is left alone; a NaN goes through
-// to the diagonal.
+// An FP64 row of norm below 3e-154, whose squares run out of the exponent's
+// range, is not reflected: its pivot is kept, and taken as positive.  A row of
+// zeros leaves the others alone; a NaN goes through to the diagonal.
 // --------------------------------------------------------------------------
 template <typename T> struct Eps;
 template <> struct Eps<double> { static constexpr double v = 2.220446049250313e-16; };
@@ -139,16 +140,16 @@ PSS_INL double pflip(double x, bool neg)
 }
 
 // The reflector from a row's pivot and the sum of squares of its tail: d is the
-// reduced diagonal, q = 1 / d.  A vanishing row is masked out by a factor, not
-// by a branch around the root and the reciprocal (the compiler makes one of a
-// select there): d, q and the reflection are zero.
+// reduced diagonal, q = 1 / d.  A row too small to be reflected is masked out by
+// factors, not by a branch around the root and the reciprocal (the compiler
+// makes one of a select there): q and the reflection are zero, d is |pivot|.
 template <typename T>
 struct Reflector {
     T d, q, v0, k;
     bool neg;
     PSS_INL Reflector(T al, T sig)
     {
-        constexpr double tiny = 1e-290;
+        constexpr double tiny = 1e-307;
         const T s = pfma(al, al, sig);
         const T on = s > T(tiny) ? T(1) : T(0);
         T r;
@@ -159,7 +160,7 @@ struct Reflector {
         k = k * on;
         q = q * on;
         // s - s: NaN where the row's norm is not finite
-        d = pfma(r, on, s - s);
+        d = pmax(r * on, aa) + (s - s);
         neg = al < T(0);
     }
     // row b below, x the reflecting one: columns i to jend

@@ -12,7 +12,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.fixture(scope="module")
-def printed():
+def check():
+    """check(*arguments): the program's lines."""
     if not os.path.exists(HIPCC):
         pytest.skip("hipcc not available")
     with tempfile.TemporaryDirectory() as tmp:
@@ -21,13 +22,23 @@ def printed():
                         "-Xarch_host", "-mfma", "-I" + os.path.join(ROOT, "include"),
                         os.path.join(ROOT, "tests", "tria_check.cpp"), "-o", exe],
                        check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
-        return subprocess.run([exe], check=True, stdout=subprocess.PIPE, text=True).stdout
+        yield lambda *a: subprocess.run([exe, *a], check=True, stdout=subprocess.PIPE,
+                                        text=True).stdout.splitlines()
 
 
-def test_gram_is_as_exact_as_the_textbook_sweep(printed):
+def test_gram_is_as_exact_as_the_textbook_sweep(check):
     """Also where one part is far smaller than the other, as process noise beside
     a factor.  0.05 units of 2^-53 are left to the draws (20 000 of them)."""
-    for line in printed.splitlines():
+    for line in check():
         e, lib, ref = (float(v) for v in line.split())
         print("e %g: library %.3f, textbook %.3f" % (e, lib, ref))
         assert lib < ref + 0.05, e
+
+
+def test_small_rows_are_kept(check):
+    """Rows of norm 1e-150 are reduced as any others: to 64 units, since squares
+    of their small entries are subnormal (of 1e-307, 1e-17 of the row's sum).  A
+    pivot without a tail is kept at any size."""
+    scaled, diag = check("small")
+    assert float(scaled) < 64
+    assert [float(v) for v in diag.split()] == [1e-200, 1e-200, 1e-3, 1e-200, 1e-200]

@@ -2,8 +2,10 @@
 // matrix [X, e Y] with X and Y lower (X of positive diagonal: a factor, and the
 // process noise beside it) and for several e, the rms error of the Gram of the
 // result in units of 2^-53: the library's, and that of the textbook sweep with
-// the pivot a - r, two divisions and a rounded root.  Test infrastructure:
-// compiled and run by tests/test_tria_cpu.py.
+// the pivot a - r, two divisions and a rounded root.  With the argument "small":
+// how far Tria(2^-500 A) is from 2^-500 Tria(A) (largest entry's difference, in
+// units of 2^-53 of the row's norm), and Tria of the diagonal +-1e-200, 1e-3.
+// Test infrastructure: compiled and run by tests/test_tria_cpu.py.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -110,8 +112,46 @@ static double gram_err(const double (&X)[N][N], const double (&Y)[N][N], const d
     return (double)(num / den);
 }
 
-int main()
+static void small()
 {
+    const double f = 0x1p-500;
+    double worst = 0.0;
+    for (int k = 0; k < 1000; ++k) {
+        double X[N][N], Y[N][N], L[N][N], l[N][N];
+        draw(1.0, X, Y);
+        pss::tria_dense_lower(X, Y, L);
+        for (int i = 0; i < N; ++i)
+            for (int j = 0; j < N; ++j) {
+                X[i][j] *= f;
+                Y[i][j] *= f;
+            }
+        pss::tria_dense_lower(X, Y, l);
+        for (int i = 0; i < N; ++i) {
+            double nr = 0.0;
+            for (int j = 0; j <= i; ++j)
+                nr += L[i][j] * L[i][j];
+            for (int j = 0; j <= i; ++j) {
+                const double d = std::fabs(l[i][j] / f - L[i][j]) / std::sqrt(nr) * 0x1p53;
+                worst = d <= worst ? worst : d; // keeps a NaN
+            }
+        }
+    }
+    std::printf("%g\n", worst);
+    double D[N][N] = {}, Z[N][N] = {}, L[N][N];
+    for (int i = 0; i < N; ++i)
+        D[i][i] = i == 2 ? 1e-3 : i == 1 ? -1e-200 : 1e-200;
+    pss::tria_dense_lower(D, Z, L);
+    for (int i = 0; i < N; ++i)
+        std::printf("%.17g ", L[i][i]);
+    std::printf("\n");
+}
+
+int main(int argc, char **)
+{
+    if (argc > 1) {
+        small();
+        return 0;
+    }
     const int reps = 20000;
     for (double e : {1.0, 1e-1, 1e-2, 1e-4, 1e-6, 1e-8, 0.0}) {
         double lib = 0.0, ref = 0.0;
