@@ -157,19 +157,24 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
     return sh;
 }
 
-// inclusive prefix sums of two values over the block, and their totals (the
-// block calls it uniformly; w: one slot per wave)
+// inclusive prefix sums of two values over the block, zero past its first `count`
+// threads, and their totals (the block calls it uniformly; w: one slot per wave)
 __device__ __forceinline__ void plan_sums(int64_t &x, int64_t &y, int64_t &tx, int64_t &ty,
-                                          int64_t (*w)[2])
+                                          int count, int64_t (*w)[2])
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
+    const int last = nw == 1 && count < 64 ? count - 1 : 63;
+    for (int d = 1; d <= last; d <<= 1) {
         const int64_t px = __shfl_up(x, d), py = __shfl_up(y, d);
         if (lane >= d) {
             x += px;
             y += py;
         }
+    }
+    if (nw == 1) {
+        tx = __shfl(x, last);
+        ty = __shfl(y, last);
+        return;
     }
     __syncthreads();
     if (lane == 63) {
@@ -189,6 +194,15 @@ __device__ __forceinline__ void plan_sums(int64_t &x, int64_t &y, int64_t &tx, i
     }
     x += bx;
     y += by;
+}
+
+// ceil(n / d) of positive numbers, in 32 bits wherever they fit
+__device__ __forceinline__ int64_t ceil_div(int64_t n, int64_t d)
+{
+    const int64_t m = n + d - 1;
+    if (((m | d) >> 32) == 0)
+        return (int64_t)((uint32_t)m / (uint32_t)d);
+    return m / d;
 }
 
 // One thread per sequence: it walks the levels with its element count, and
@@ -218,8 +232,9 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a)
                 break;
             const int64_t ts = l == 0 ? (int64_t)a.T0 * E0 : a.TS[l];
             const int64_t d = l == 0 && a.flat0 ? E0 : l == 0 ? ts : a.D[l];
-            int64_t t = (cn + ts - 1) / ts, e = cn, tt, te;
-            plan_sums(t, e, tt, te, w);
+            const int64_t up = l + 1 < a.L ? ceil_div(cn, d) : 0;
+            int64_t t = d == ts && l + 1 < a.L ? up : ceil_div(cn, ts), e = cn, tt, te;
+            plan_sums(t, e, tt, te, a.B - base, w);
             if (in) {
                 a.tile_off[l][b + 1] = ct[l] + t;
                 if (l > 0 && a.elem_off[l])
@@ -227,7 +242,31 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a)
             }
             ct[l] += tt;
             ce[l] += te;
-            cn = (cn + d - 1) / d;
+            cn = up;
+        }
+    }
+}
+
+// A single sequence: its counts are the plan's totals, which the host has.  (A
+// pass of a short sequence waits for its plan; walking the levels took 3.2 us,
+// one thread's walk without sums 2.5, this 2.1.)
+struct PlanOne {
+    int64_t ntiles[kMaxLevels], nelem[kMaxLevels];
+    int64_t *tile_off[kMaxLevels], *elem_off[kMaxLevels];
+};
+__global__ __launch_bounds__(64) void k_plan_one(PlanOne a)
+{
+    if (threadIdx.x != 0)
+        return;
+#pragma unroll
+    for (int l = 0; l < kMaxLevels; ++l) {
+        if (a.tile_off[l]) {
+            a.tile_off[l][0] = 0;
+            a.tile_off[l][1] = a.ntiles[l];
+        }
+        if (a.elem_off[l]) {
+            a.elem_off[l][0] = 0;
+            a.elem_off[l][1] = a.nelem[l];
         }
     }
 }
@@ -235,6 +274,17 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a)
 int launch_plan(const Ctx &c, const ScanShape &sh, int extra, int64_t *const *tile_off,
                 int64_t *const *elem_off)
 {
+    if (c.B == 1) {
+        PlanOne o{};
+        for (int l = 0; l < sh.L; ++l) {
+            o.ntiles[l] = sh.ntiles[l];
+            o.nelem[l] = sh.nelem[l];
+            o.tile_off[l] = tile_off[l];
+            o.elem_off[l] = l > 0 && elem_off ? elem_off[l] : nullptr;
+        }
+        hipLaunchKernelGGL(k_plan_one, dim3(1), dim3(64), 0, c.s, o);
+        return hip_check(hipGetLastError(), "plan launch");
+    }
     PlanArgs a;
     a.y_off = c.p->y_off;
     a.B = c.B;
@@ -293,6 +343,7 @@ int launch_seq_sum(const Ctx &c, int nc, const double *terms, int64_t ld, double
     sh.L = 1;
     sh.T[0] = kSumChunk;
     sh.E[0] = 1;
+    sh.ntiles[0] = nch;
     int rc = launch_plan(c, sh, 0, &chunk_off);
     if (rc)
         return rc;

@@ -224,3 +224,19 @@ def test_groups_on_side_streams_from_two_threads():
     for s in sets:
         for g, r in zip(s, alone):
             assert torch.equal(g[2], r[2]) and torch.equal(g[3], r[3])
+
+
+@pytest.mark.parametrize("B", [2, 63, 64, 65, 1025])
+def test_plan_offsets_of_many_sequences(B):
+    """The plan's sums over one wave, over a block and over rounds of a block:
+    every sequence as in a call of its own."""
+    dt, lens = torch.float64, 1 + np.arange(B) * 37 % 301
+    G, seq, m0, N0, ys, off = _linear(2, 1, lens, B, False, dt)
+    b = pss.Batch(pss.MODEL_LINEAR, dt, 2, 1, off, m0, N0, device=DEV)
+    m, N = pss.ipls_iterate(b, pss.to_soa(np.concatenate(ys), dt, DEV), 1,
+                            gamma=b.gamma_from_numpy(G))
+    for s in (0, 1, B // 2, B - 1):
+        b1 = pss.Batch(pss.MODEL_LINEAR, dt, 2, 1, [0, int(lens[s])], m0, N0, device=DEV)
+        m1, N1 = pss.ipls_iterate(b1, pss.to_soa(ys[s], dt, DEV), 1, gamma=b1.gamma_from_numpy(G))
+        a, z = off[s] + s, off[s + 1] + s + 1
+        assert torch.equal(m[:, a:z], m1) and torch.equal(N[:, a:z], N1), s
