@@ -2,13 +2,18 @@
 // likelihood: the VJP of the filter scan as a reverse associative scan of
 // affine cotangent maps (device_adj.hpp) and the per-step VJP with respect to
 // the linearisation Gamma_k (Section 5.2, eq. gradient, at a frozen nominal).
-// Its finest level works on the tiles of steps.hpp, a thread on E consecutive
-// steps:
+// In FP64 its finest level works on the tiles of steps.hpp, a thread on E
+// consecutive steps:
 //   k_filter_walk  filters from the marginal before the thread's first step;
 //                  writes the log-likelihood terms, the filtering marginals,
 //                  and the aggregate of its cotangent maps, each on request
 //   k_adj_down     from the cotangent of the state after its last step back to
 //                  its first: every step's cotangents and the prior's
+// In FP32, whose marginals and linearisation are in the plain layout, it is a
+// tile scan (AdjSrc): threads that read E numbers apart gain nothing from longer
+// runs of steps, and its in-tile tree leaves the levels above 64 times fewer
+// elements.  (Folding 2 steps a thread without the tree: backward pass of 64 x
+// 10^4 steps 449 us instead of 411, of 300 x 600 281 instead of 235.)
 #pragma once
 
 #include "device_adj.hpp"
@@ -432,52 +437,78 @@ __global__ __launch_bounds__(256) void k_filter_walk(LevelGeom g, GammaRef<T, NX
                           view_of(agg, agg_slot(next_off, ti.b, cnt1 - 1 - v, nT, nE)));
 }
 
-// the maps of a thread's steps folded from stored marginals, everything in the
-// plain layout (FP32)
-template <typename T, int NX, int NY, class AggRef>
-__global__ __launch_bounds__(256) void k_adj_fold(LevelGeom g, GammaRef<T, NX, NY> gam,
-                                                  const T *y, int64_t T_y, MargRef<T, NX> marg,
-                                                  AggRef agg, const int64_t *next_off, int nT,
-                                                  int nE)
-{
-    const TileInfo ti = tile_info(g);
-    if ((int)threadIdx.x >= ti.nvalid)
-        return;
-    const int64_t p0 = ti.start + (int64_t)threadIdx.x * ti.E;
-    int64_t pe = p0 + ti.E;
-    if (pe > ti.start + ti.tcnt)
-        pe = ti.start + ti.tcnt;
-    const int64_t v = ti.start / ti.E + threadIdx.x, cnt1 = next_off[ti.b + 1] - next_off[ti.b];
-    SElem<T, NX> a;
-    for (int64_t p = p0; p < pe; ++p) {
-        const int64_t t = ti.off + p;
-        T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
+// FP32: element p of sequence b at the finest level is the map of step k = n - p,
+// built from the filtering marginal of state k - 1 and Gamma at step slot y_off[b]
+// + k - 1; down_apply also emits the step's cotangents with the suffix lambda_k
+template <typename T, int NX, int NY, class Out>
+struct AdjSrc {
+    static constexpr bool lazy_up = false, lazy_down = false, fused_down = true;
+    static constexpr int leaf_nz = 0;
+    GammaRef<T, NX, NY> gam;
+    MargRef<T, NX> filt;
+    const T *y;
+    int64_t T_y;
+    Out out;
+
+    PSS_INL int64_t load(const TileInfo &ti, int64_t p, T (&F)[NX][NX], T (&c)[NX],
+                         T (&SL)[NX][NX], T (&H)[NY][NX], T (&d)[NY], T (&SO)[NY][NY],
+                         T (&yy)[NY], Marg<T, NX> &f) const
+    {
+        const int64_t t = ti.off + ti.cnt - 1 - p; // step slot of step n - p
         gam.load_trans(t, F, c, SL);
         gam.load_obs(t, H, d, SO);
 #pragma unroll
-        for (int q = 0; q < NY; ++q)
-            yy[q] = y[q * T_y + t];
+        for (int a = 0; a < NY; ++a)
+            yy[a] = y[a * T_y + t];
+        filt.load(t + ti.b, f);
+        return t;
+    }
+    PSS_INL void up(const TileInfo &ti, int64_t p, SElem<T, NX> &e) const
+    {
+        T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
         Marg<T, NX> f;
-        marg.load(t + ti.b, f);
+        load(ti, p, F, c, SL, H, d, SO, yy, f);
         StepQ<T, NX, NY> q;
         T Np[NX][NX], P22[NX][NX], mp[NX];
         adj_step(F, c, SL, H, d, SO, yy, f, q, Np, P22, mp);
-        SElem<T, NX> e;
         adj_element(F, q, e);
-        if (p == p0)
-            a = e;
-        else
-            adj_combine_v<T, NX>(SRegV<T, NX>{&a}, SRegV<T, NX>{&e}, SRegV<T, NX>{&a});
     }
-    selem_copy<T, NX>(SRegV<T, NX>{&a},
-                      view_of(agg, agg_slot(next_off, ti.b, cnt1 - 1 - v, nT, nE)));
-}
+    PSS_INL void down_apply(const TileInfo &ti, int64_t p, const Marg<T, NX> &lam,
+                            Marg<T, NX> &o) const
+    {
+        T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
+        Marg<T, NX> f;
+        const int64_t t = load(ti, p, F, c, SL, H, d, SO, yy, f);
+        StepQ<T, NX, NY> q;
+        T Np[NX][NX], P22[NX][NX], mp[NX];
+        adj_step(F, c, SL, H, d, SO, yy, f, q, Np, P22, mp);
+        {
+            SElem<T, NX> e;
+            adj_element(F, q, e);
+            adj_apply_v<T, NX>(SRegV<T, NX>{&e}, lam, o);
+        }
+        adj_emit(out, ti.b, t, F, SL, H, SO, f, q, Np, P22, mp, lam);
+    }
+};
+
+// its sink: the inclusive suffix at the last scan position is lambda_0
+template <typename T, int NX>
+struct AdjDst {
+    static constexpr bool stageable = false, stage_excl = false;
+    AdjPrior<T, NX> prior;
+    PSS_INL void put(const TileInfo &ti, int64_t p, const Marg<T, NX> &excl,
+                     const Marg<T, NX> &incl) const
+    {
+        if (p == ti.cnt - 1)
+            prior.put(ti.b, incl);
+    }
+};
 
 template <typename T, int NX, int NY, class Out, class PreRef>
 __global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, NY> gam,
                                                   const T *y, int64_t T_y, MargRef<T, NX> marg,
                                                   PreRef pre, Out out, AdjPrior<T, NX> prior,
-                                                  const int64_t *next_off, int plain)
+                                                  const int64_t *next_off)
 {
     const TileInfo ti = tile_info(g);
     if ((int)threadIdx.x >= ti.nvalid)
@@ -490,7 +521,7 @@ __global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, N
     Marg<T, NX> lam;
     pre.load(next_off[ti.b] + cnt1 - 1 - v, lam);
     for (int64_t p = pe - 1; p >= p0; --p) {
-        const int64_t u = plain ? ti.off + p : ilv_slot(ti, p), ug = gam.stride ? u : 0;
+        const int64_t u = ilv_slot(ti, p), ug = gam.stride ? u : 0;
         T F[NX][NX], c[NX], SL[NX][NX], H[NY][NX], d[NY], SO[NY][NY], yy[NY];
         gam.load_trans(ug, F, c, SL);
         gam.load_obs(ug, H, d, SO);
@@ -498,7 +529,7 @@ __global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, N
         for (int a = 0; a < NY; ++a)
             yy[a] = y[a * T_y + ti.off + p];
         Marg<T, NX> f, o;
-        marg.load(plain ? u + ti.b : u, f); // state p, before the step
+        marg.load(u, f); // state p, before the step
         StepQ<T, NX, NY> q;
         T Np[NX][NX], P22[NX][NX], mp[NX];
         adj_step(F, c, SL, H, d, SO, yy, f, q, Np, P22, mp);

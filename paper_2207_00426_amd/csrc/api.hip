@@ -110,7 +110,7 @@ KTime::~KTime()
 // scan planning (host side mirrors k_plan exactly)
 // ---------------------------------------------------------------------------
 ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, int Eup,
-                    bool flat0, ShortRule few)
+                    bool flat0, ShortRule few, bool never_top)
 {
     ScanShape sh;
     sh.few = few;
@@ -140,7 +140,7 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
         // lengths of the others in its batch (a level that holds a sequence
         // in one tile passes it through bitwise unchanged)
         sh.flat[l] = l == 0 && flat0;
-        if (mx <= TS && !sh.flat[l]) {
+        if (mx <= TS && !sh.flat[l] && !(l == 0 && never_top)) {
             sh.L = l + 1;
             break;
         }

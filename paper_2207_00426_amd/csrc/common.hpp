@@ -98,9 +98,10 @@ struct ScanShape {
     int64_t nelem[kMaxLevels] = {};
 };
 
-// level 0 takes (T0, E0), level 1 (Tup, E1), the levels above (Tup, Eup)
+// level 0 takes (T0, E0), level 1 (Tup, E1), the levels above (Tup, Eup);
+// never_top: there is a level above level 0 also where one tile would do
 ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, int Eup,
-                    bool flat0, ShortRule few = {});
+                    bool flat0, ShortRule few = {}, bool never_top = false);
 // device tile offsets of every level and, where elem_off is given, the
 // element offsets of every level >= 1 (both [B + 1] per level)
 int launch_plan(const Ctx &c, const ScanShape &sh, int extra, int64_t *const *tile_off,

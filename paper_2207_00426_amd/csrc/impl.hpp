@@ -377,8 +377,10 @@ struct Core {
         return PSS_OK;
     }
 
-    // a scan whose finest level folds and applies given elements (Src0, Dst0)
-    template <class Op, bool Flat, class Src0, class Dst0, class AggRef, class Start>
+    // a scan whose finest level folds and applies given elements (Src0, Dst0);
+    // Top0: it may be the top (a plan without never_top)
+    template <class Op, bool Flat, bool Top0 = true, class Src0, class Dst0, class AggRef,
+              class Start>
     static int run_scan(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w, int extra,
                         const Src0 &src0, const Dst0 &dst0, const Start &start,
                         AggRef (*agg_ref)(T *, int64_t), int stop = 0)
@@ -411,12 +413,15 @@ struct Core {
             return hip_check(hipGetLastError(), "scan up launch");
         };
         auto top0 = [&]() -> int {
-            KTime kt(c.s, Op::name, "top", 0);
-            auto k = k_scan_top<Op, Src0, Dst0, Start>;
-            if (int r = prep_lds(k, lb))
-                return r;
-            hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, dst0, start);
-            return hip_check(hipGetLastError(), "scan top launch");
+            if constexpr (Top0) {
+                KTime kt(c.s, Op::name, "top", 0);
+                auto k = k_scan_top<Op, Src0, Dst0, Start>;
+                if (int r = prep_lds(k, lb))
+                    return r;
+                hipLaunchKernelGGL(k, grid, block, lb, c.s, g, src0, dst0, start);
+                return hip_check(hipGetLastError(), "scan top launch");
+            }
+            return PSS_OK;
         };
         auto down0 = [&]() -> int {
             KTime kt(c.s, Op::name, "down", 0);
@@ -635,7 +640,15 @@ struct Core {
     // covariance form scans stored elements
     static size_t grad_scans(const Ctx &c, int nc)
     {
-        return std::max({fscan_bytes(c), scan_bytes(c, grad_shape(c)), seq_sum_bytes(c, nc)});
+        size_t adj;
+        if (kStepsLL) {
+            adj = scan_bytes(c, grad_shape(c));
+        } else {
+            Carver cv{nullptr};
+            carve_scan<AdjScan<T, NX>>(cv, c, adj_shape(c));
+            adj = cv.used;
+        }
+        return std::max({fscan_bytes(c), adj, seq_sum_bytes(c, nc)});
     }
 
     static size_t ws_size(const Ctx &c, int op)
@@ -738,14 +751,12 @@ struct Core {
         return StepTiles{sh.T[0], sh.E[0], sh.few};
     }
 
-    // the same for the log-likelihood calls: at least 4 steps a thread, so that
-    // a checkpoint of level 1 holds a prefix per 4 states at most.  Their
+    // the same for the FP64 log-likelihood calls: at least 4 steps a thread, so
+    // that a checkpoint of level 1 holds a prefix per 4 states at most.  Their
     // walks are longer per step and their scans above cheaper, so 8 steps pay
-    // only on long sequences (us per gradient at 4 and 8 steps, FP64: 1 x 1500
-    // 210 and 220, 8 x 6000 of a linear model 253 and 313, 1 x 10^4 227 and 274,
-    // 64 x 10^4 889 and 806).  FP32 folds 2: its marginals and linearisation are
-    // in the plain layout, read E numbers apart (64 x 10^4: at 4 steps the two
-    // passes over them take 300 us, at 2 192).
+    // only on long sequences (us per gradient at 4 and 8 steps: 1 x 1500 210 and
+    // 220, 8 x 6000 of a linear model 253 and 313, 1 x 10^4 227 and 274, 64 x
+    // 10^4 889 and 806).
     static ScanShape grad_shape(const Ctx &c)
     {
         int T0, E0, Tup, E1, Eup;
@@ -753,10 +764,16 @@ struct Core {
         if (c.p->scan_elems > 0)
             return plan_scan(c, 0, T0, E0, Tup, E1, Eup, true);
         using D = Defaults<T, NX>;
-        if (!kStepsLL)
-            return plan_scan(c, 0, T0, 2, Tup, E1, Eup, true);
         return plan_scan(c, 0, T0, std::max(4, D::E0_step), Tup, E1, Eup, true,
                          ShortRule{NX == 1 ? 0 : 8192, 0});
+    }
+    // FP32's adjoint scan, tiles of a wave with 2 steps a thread (their reads are
+    // 2 numbers apart; at 4 the passes take half as long again)
+    static ScanShape adj_shape(const Ctx &c)
+    {
+        const int T0 = c.p->scan_threads > 0 ? c.p->scan_threads : Defaults<T, NX>::T0;
+        const int Tup = std::min(T0, (int)Defaults<T, NX>::Tup);
+        return plan_scan(c, 0, T0, 2, Tup, 2, 2, false, {}, true);
     }
     static size_t scan_bytes(const Ctx &c, const ScanShape &sh)
     {
@@ -1169,7 +1186,6 @@ struct Core {
         MargRef<T, NX> marg; // filtering marginals, state k at the slot of step k + 1
         double *ell;
         void *sums;
-        int plain = 0; // FP32: linearisation and marginals in the plain layout
     };
     static int grad_state(const Ctx &c, const pss_gamma *gin, const void *m_nom,
                           const void *N_nom, const void *y, void *ws, GradState &s)
@@ -1265,9 +1281,9 @@ struct Core {
         return ckpt ? copy_ll(c, ck.ll, ll) : PSS_OK;
     }
 
-    // forward half of a gradient: the filtering marginals and the maps'
-    // level-1 aggregates from a checkpoint (re-running what it does not hold)
-    // or a full filter pass
+    // forward half of a gradient: the filtering marginals (FP64: and the maps'
+    // level-1 aggregates) from a checkpoint (re-running what it does not hold) or
+    // a full filter pass
     static int grad_forward(const Ctx &c, const pss_gamma *gin, const void *m_nom,
                             const void *N_nom, const void *y, const pss_ckpt *ckpt, double *ll,
                             void *ws, GradState &s)
@@ -1287,8 +1303,7 @@ struct Core {
             return grad_filter<true>(c, s, y, s.marg, ckpt ? nullptr : s.ell,
                                      ck.pre ? ck.level : 0);
         } else {
-            // over stored elements, as FP32's log-likelihood; then the maps
-            // from the marginals
+            // over stored elements, as FP32's log-likelihood
             Carver cv{static_cast<char *>(ws)};
             T *mf;
             if (!ckpt) {
@@ -1316,23 +1331,9 @@ struct Core {
             }
             if (rc)
                 return rc;
-            s.plain = 1;
             s.gam = gamma_ref(&s.gw, c.T_y);
             s.marg = marg_ref(mf, c.T_x);
-            s.sh = grad_shape(c);
-            Carver cs{static_cast<char *>(s.sums)};
-            s.w = carve_scan<FS>(cs, c, s.sh);
-            if ((rc = launch_plan(c, s.sh, 0, s.w.tile_off, s.w.elem_off)))
-                return rc;
-            KTime kt(c.s, "adjoint_fold", "", 0);
-            using AS = AdjScan<T, NX>;
-            const auto agg = agg_of(s.sh, share_ws<AS>(s.sh, s.w), 1, &selem_ref);
-            using Agg = std::decay_t<decltype(agg)>;
-            hipLaunchKernelGGL((k_adj_fold<T, NX, NY, Agg>), dim3((unsigned)s.sh.ntiles[0]),
-                               dim3(s.sh.T[0]), 0, c.s, level_geom(c, s.sh, s.w, 0, 0), s.gam,
-                               cptr<T>(y), c.T_y, s.marg, agg, s.w.elem_off[1], s.sh.T[1],
-                               agg_ilv<AS>(s.sh));
-            return hip_check(hipGetLastError(), "adjoint fold launch");
+            return PSS_OK;
         }
     }
 
@@ -1349,19 +1350,28 @@ struct Core {
         if (rc)
             return rc;
         Carver cv{static_cast<char *>(s.sums)};
-        const auto wa = share_ws<AS>(s.sh, carve_scan<FS>(cv, c, s.sh));
         const StartPre<T, NX> st{nullptr, nullptr};
-        auto nothing = []() -> int { return PSS_OK; };
-        rc = run_levels<AS, true>(c, s.sh, wa, 0, st, &selem_ref, 0, nothing, nothing, [&]() -> int {
-            KTime kt(c.s, "adjoint_down", "", 0);
-            const auto pre = pre_of(s.sh, wa, 1);
-            using Pre = std::decay_t<decltype(pre)>;
-            hipLaunchKernelGGL((k_adj_down<T, NX, NY, Out, Pre>), dim3((unsigned)s.sh.ntiles[0]),
-                               dim3(s.sh.T[0]), 0, c.s, level_geom(c, s.sh, wa, 0, 0), s.gam,
-                               cptr<T>(y), c.T_y, s.marg, pre, out, prior, wa.elem_off[1],
-                               s.plain);
-            return hip_check(hipGetLastError(), "adjoint down launch");
-        });
+        if constexpr (kStepsLL) {
+            const auto wa = share_ws<AS>(s.sh, carve_scan<FS>(cv, c, s.sh));
+            auto nothing = []() -> int { return PSS_OK; };
+            rc = run_levels<AS, true>(
+                c, s.sh, wa, 0, st, &selem_ref, 0, nothing, nothing, [&]() -> int {
+                    KTime kt(c.s, "adjoint_down", "", 0);
+                    const auto pre = pre_of(s.sh, wa, 1);
+                    using Pre = std::decay_t<decltype(pre)>;
+                    hipLaunchKernelGGL((k_adj_down<T, NX, NY, Out, Pre>),
+                                       dim3((unsigned)s.sh.ntiles[0]), dim3(s.sh.T[0]), 0, c.s,
+                                       level_geom(c, s.sh, wa, 0, 0), s.gam, cptr<T>(y), c.T_y,
+                                       s.marg, pre, out, prior, wa.elem_off[1]);
+                    return hip_check(hipGetLastError(), "adjoint down launch");
+                });
+        } else {
+            const ScanShape sh = adj_shape(c);
+            const auto wa = carve_scan<AS>(cv, c, sh);
+            const AdjSrc<T, NX, NY, Out> src{s.gam, s.marg, cptr<T>(y), c.T_y, out};
+            rc = run_scan<AS, false, false>(c, sh, wa, 0, src, AdjDst<T, NX>{prior}, st,
+                                            &selem_ref);
+        }
         if (rc)
             return rc;
         if (ckpt)

@@ -240,3 +240,39 @@ def test_plan_offsets_of_many_sequences(B):
         m1, N1 = pss.ipls_iterate(b1, pss.to_soa(ys[s], dt, DEV), 1, gamma=b1.gamma_from_numpy(G))
         a, z = off[s] + s, off[s + 1] + s + 1
         assert torch.equal(m[:, a:z], m1) and torch.equal(N[:, a:z], N1), s
+
+
+def test_fp32_gradient_at_the_edges_of_its_tiles():
+    """Tiles of 64 threads x 2 steps, groups of 128 tiles above them."""
+    lens = [1, 127, 128, 129, 16384, 16385]
+    b, ys, yd = _ct(lens, 9, torch.float32)
+    m, N = pss.ipls_iterate(b, yd, 1)
+    ll, grad, _ = pss.loglik_grad(b, m, N, yd)
+    ck = pss.Checkpoint(b, 0)
+    pss.loglik(b, yd, m, N, ckpt=ck)
+    l2, g2, _ = pss.loglik_grad(b, m, N, yd, ckpt=ck)
+    torch.cuda.synchronize()
+    assert torch.equal(ll, l2) and torch.equal(grad, g2)
+    ma, Na = pss.marg_from_soa(m.double(), N.double(), 5)
+    off, md = _offsets(lens), wl.CTModel()
+    for s, y in enumerate(ys):
+        a, z = off[s] + s, off[s + 1] + s + 1
+        l_ref, g_ref = orc.ct_score(orc.ct_params(), md.m0, np.eye(5), y, ma[a:z], Na[a:z])
+        assert par.ll_err(ll[s].item(), l_ref) < par.TOL["f32"]["ll"], lens[s]
+        assert par.grad_err(grad[:, s].cpu().numpy(), g_ref) < par.TOL["f32"]["g"], lens[s]
+
+
+@pytest.mark.parametrize("nx,ny,lens", [(1, 1, [1, 5, 128]), (3, 2, [128, 2]),
+                                        (2, 3, [129, 700, 1]), (5, 2, [300, 64])])
+def test_fp32_vjp_against_fp64(nx, ny, lens):
+    """Also where one tile holds every sequence."""
+    out = []
+    for dt in (torch.float32, torch.float64):
+        G, seq, m0, N0, ys, off = _linear(nx, ny, lens, 3 * nx + ny, True, torch.float32)
+        b = pss.Batch(pss.MODEL_LINEAR, dt, nx, ny, off, m0, N0, device=DEV)
+        ll, g, m0b, N0b = pss.loglik_vjp(b, pss.to_soa(np.concatenate(ys), dt, DEV),
+                                         gamma=b.gamma_from_numpy(G))
+        out.append([ll, m0b, N0b] + [g[k] for k in ("F", "c", "SL", "H", "d", "SO")])
+    for a, r in zip(*out):
+        a, r = a.double().cpu().numpy(), r.double().cpu().numpy()
+        assert np.abs(a - r).max() < par.TOL["f32"]["g"] * max(1.0, np.abs(r).max())
