@@ -185,7 +185,8 @@ def step_costs(n, dtype, T_req=0, E_req=0):
     agg = plan[1][2]
     step = NUM["gam"] + NUM["y"]
     fl, by = {}, {}
-    for op in ("filter", "smoother", "adjoint"):
+    # (FP32's adjoint scan has tiles of its own, not priced here)
+    for op in ("filter", "smoother") + (("adjoint",) if dtype == "f64" else ()):
         f, b = upper_levels(op, plan, esz)
         fl.update(f)
         by.update(b)
