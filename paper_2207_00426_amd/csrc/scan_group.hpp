@@ -11,7 +11,9 @@
 // -- no down-sweep -- and walks the group's elements.  32 groups are two waves
 // on each SIMD of a CU: one wave alone leaves half of its issue slots empty, and
 // more would share them.  The bracketing depends only on the sequence's own
-// length.
+// length, and so does the rounding: what a lower level stores between its halves
+// in FP32, the top level rounds likewise, so that a sequence's result does not
+// show whether a longer one in its batch made its top level a lower one.
 #pragma once
 
 #include "device_group.hpp"
@@ -279,9 +281,18 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_top(GroupGeom gm,
         start.get(s);
         visit(s, [&](int c, T &v) { p[c] = double(v); });
     }
+    const double *left = acc + (g - 1) * Op::NE;
+    if constexpr (sizeof(T) == 4) { // as k_group_down takes it: rounded
+        if (g > 0) {
+            GroupMove<T, Op::NE> mv;
+            mv.load(left);
+            mv.store(x);
+            left = x;
+        }
+    }
     grp::lds_order();
     if (g > 0)
-        GroupOp<Op>::apply(p, acc + (g - 1) * Op::NE, p, ln);
+        GroupOp<Op>::apply(p, left, p, ln);
     group_walk<Op>(ti, elems, pre_out, p, x, ln);
 }
 

@@ -276,3 +276,23 @@ def test_fp32_vjp_against_fp64(nx, ny, lens):
     for a, r in zip(*out):
         a, r = a.double().cpu().numpy(), r.double().cpu().numpy()
         assert np.abs(a - r).max() < par.TOL["f32"]["g"] * max(1.0, np.abs(r).max())
+
+
+@pytest.mark.parametrize("tag", ["f64", "f32"])
+def test_result_does_not_depend_on_the_batch(tag):
+    """Next to a longer sequence, whose scans have a level more."""
+    dt, lens = _dt(tag), [900, 129, 6000]
+
+    def run(k):
+        b, _, y = _ct(lens[:k], 4, dt)
+        m, N = pss.ipls_iterate(b, y, 1)
+        g = pss.slr_linearize(b, m, N, y)
+        mf, Nf = pss.sqrt_filter_scan(b, pss.sqrt_filter_elements(b, g, y))
+        ms, Ns = pss.sqrt_smoother_scan(b, g, mf, Nf)
+        ll, grad, _ = pss.loglik_grad(b, m, N, y)
+        torch.cuda.synchronize()
+        x = int(sum(lens[:2])) + 2
+        return [t[:, :x] for t in (m, N, mf, Nf, ms, Ns)] + [ll[:2], grad[:, :2]]
+
+    for i, (a, b) in enumerate(zip(run(2), run(3))):
+        assert torch.equal(a, b), i
