@@ -157,14 +157,14 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
     return sh;
 }
 
-// inclusive prefix sums of two values over the block, zero past its first `count`
-// threads, and their totals (the block calls it uniformly; w: one slot per wave)
+// inclusive prefix sums of two values over the block, and their totals (the
+// block calls it uniformly; w: one slot per wave)
 __device__ __forceinline__ void plan_sums(int64_t &x, int64_t &y, int64_t &tx, int64_t &ty,
-                                          int count, int64_t (*w)[2])
+                                          int64_t (*w)[2])
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
-    const int last = nw == 1 && count < 64 ? count - 1 : 63;
-    for (int d = 1; d <= last; d <<= 1) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
         const int64_t px = __shfl_up(x, d), py = __shfl_up(y, d);
         if (lane >= d) {
             x += px;
@@ -172,8 +172,8 @@ __device__ __forceinline__ void plan_sums(int64_t &x, int64_t &y, int64_t &tx, i
         }
     }
     if (nw == 1) {
-        tx = __shfl(x, last);
-        ty = __shfl(y, last);
+        tx = __shfl(x, 63);
+        ty = __shfl(y, 63);
         return;
     }
     __syncthreads();
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(1024) void k_plan(PlanArgs a)
             const int64_t d = l == 0 && a.flat0 ? E0 : l == 0 ? ts : a.D[l];
             const int64_t up = l + 1 < a.L ? ceil_div(cn, d) : 0;
             int64_t t = d == ts && l + 1 < a.L ? up : ceil_div(cn, ts), e = cn, tt, te;
-            plan_sums(t, e, tt, te, a.B - base, w);
+            plan_sums(t, e, tt, te, w);
             if (in) {
                 a.tile_off[l][b + 1] = ct[l] + t;
                 if (l > 0 && a.elem_off[l])
@@ -301,7 +301,8 @@ int launch_plan(const Ctx &c, const ScanShape &sh, int extra, int64_t *const *ti
     a.T0 = sh.T[0];
     a.E0 = sh.E[0];
     a.flat0 = sh.flat[0];
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(c.B <= 64 ? 64 : 1024), 0, c.s, a);
+    const int threads = std::min((c.B + 63) / 64 * 64, 1024);
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(threads), 0, c.s, a);
     return hip_check(hipGetLastError(), "plan launch");
 }
 
