@@ -448,13 +448,17 @@ int pss_ipls_batched(const pss_group *groups, int32_t n_groups, int32_t n_iter, 
 /* Workspace bytes of pss_autotune. */
 size_t pss_autotune_workspace_size(const pss_group *groups, int32_t n_groups);
 
-/* Autotuner: times one batched pass for each candidate launch shape (block
-   threads 64/128/256, elements per thread 1..8) on the
-   caller's data (the nominal is copied, not modified), keeps the fastest for
-   this batch signature (dtype, models, batch sizes, log2 of total steps) in a
-   host cache used by pss_ipls_batched, and writes the cache to
-   cache_path_host if not NULL.  best_host (nullable, 3 ints) receives
-   (threads, filter elements, smoother elements).  Synchronises the stream. */
+/* Autotuner: times a batched pass with the library's own rule and with each
+   forced launch shape (block threads 64/128/256, elements per thread 1..8) on
+   the caller's data (the nominal is copied, not modified), and keeps the
+   fastest for this batch signature (dtype, models, linearisations, batch
+   sizes, log2 of total steps and of the longest sequence) in a host cache
+   used by pss_ipls_batched; the cache is written to cache_path_host if not
+   NULL.  best_host (nullable, 3 ints) receives (threads, filter elements,
+   smoother elements); where the rule is kept, those of a long sequence
+   (64, 8, 8; FP32 coordinated-turn tracks 256, 4, 4), and the cache holds
+   zeros.  Entries of files written by library versions before this signature
+   are not applied.  Synchronises the stream. */
 int pss_autotune(const pss_group *groups, int32_t n_groups, void *ws, size_t ws_bytes,
                  const char *cache_path_host, int32_t *best_host, hipStream_t stream);
 
