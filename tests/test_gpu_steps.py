@@ -296,3 +296,42 @@ def test_result_does_not_depend_on_the_batch(tag):
 
     for i, (a, b) in enumerate(zip(run(2), run(3))):
         assert torch.equal(a, b), i
+
+
+def test_vjp_does_not_depend_on_the_copy_to_the_plain_layout():
+    """Cotangents of a small call are stored in the caller's layout, those of a
+    large one (over 16 MiB of them) in tile order and copied there."""
+    dt, lens = torch.float64, [9000, 26500, 7]
+    G, seq, m0, N0, ys, off = _linear(5, 2, lens, 3, True, dt)
+
+    def run(sel):
+        b = pss.Batch(pss.MODEL_LINEAR, dt, 5, 2, _offsets([lens[i] for i in sel]), m0, N0,
+                      device=DEV)
+        g = {k: np.concatenate([seq[i][k] for i in sel]) for k in G}
+        ll, gb, m0b, N0b = pss.loglik_vjp(
+            b, pss.to_soa(np.concatenate([ys[i] for i in sel]), dt, DEV),
+            gamma=b.gamma_from_numpy(g))
+        torch.cuda.synchronize()
+        return [gb[k] for k in ("F", "c", "SL", "H", "d", "SO")], (ll[None], m0b, N0b)
+
+    per_step, per_seq = run([0, 1, 2])
+    for i in (0, 1, 2):
+        s1, q1 = run([i])
+        for a, b in zip(per_step, s1):
+            assert torch.equal(a[:, off[i]:off[i + 1]], b), i
+        for a, b in zip(per_seq, q1):
+            assert torch.equal(a[:, i:i + 1], b), i
+
+
+def test_checkpoints_of_sequences_on_both_sides_of_8_steps_a_thread():
+    """4 steps a thread up to 8192, 8 beyond, in one batch: the gradient from a
+    checkpoint of every level has the bits of the one without."""
+    b, ys, yd = _ct([8193, 8192, 20000, 700], 13, torch.float64)
+    m, N = pss.ipls_iterate(b, yd, 1)
+    ll0, g0, _ = pss.loglik_grad(b, m, N, yd)
+    for level in (0, 1, 2, 3, 5):
+        ck = pss.Checkpoint(b, level)
+        llc = pss.loglik(b, yd, m, N, ckpt=ck)
+        ll, g, _ = pss.loglik_grad(b, m, N, yd, ckpt=ck)
+        torch.cuda.synchronize()
+        assert torch.equal(llc, ll0) and torch.equal(ll, ll0) and torch.equal(g, g0), level
