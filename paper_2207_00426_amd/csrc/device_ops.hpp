@@ -1326,7 +1326,10 @@ PSS_INL void ct_slr_transition(const CTParams<T> &P, const Marg<T, 5> &mg, T (&F
 // two absolute angles.  Images are read on the branch nearest to y: with
 // D0 = wrap(bearing(u0) - y), image - y = wrap(D0 + angle); the deviation
 // from D0 carries the 2 pi branch jumps explicitly.
-template <typename T>
+//
+// ALL: the angles of the columns that do not move the position are computed as
+// the others' instead of set to zero: the same values from fewer registers.
+template <typename T, bool ALL = false>
 PSS_INL void ct_slr_bearings(const CTParams<T> &P, const Marg<T, 5> &mg, const T (&y)[2],
                              T (&H)[2][5], T (&d)[2], T (&S)[2][2])
 {
@@ -1348,24 +1351,28 @@ PSS_INL void ct_slr_bearings(const CTParams<T> &P, const Marg<T, 5> &mg, const T
         // branch jumps of D0 + angle back into [-pi, pi): both lie within one
         // turn of it, so the jump is a comparison, not a division
         auto branch = [&](W ang) {
+            if constexpr (ALL)
+                return T(ang - tp * pfloor((D0 + ang + pi) / tp));
             const W t = D0 + ang;
             return T(ang - (pi <= t ? tp : (t < -pi ? -tp : zero)));
         };
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
+        for (int i = 0; i < (ALL ? 5 : 2); ++i) {
             // position part of column i of sqrt(nx) N (lower: rows >= i)
             const W d0 = (i == 0) ? sq * W(mg.N[0][0]) : W(0);
-            const W d1 = sq * W(mg.N[1][i]);
+            const W d1 = (i <= 1) ? sq * W(mg.N[1][i]) : W(0);
             const W cr = ux * d1 - uy * d0;
             const W dt = ux * d0 + uy * d1;
             ep[q][i] = branch(patan2(cr, r2 + dt));
             em[q][i] = branch(patan2(-cr, r2 - dt));
         }
         // the columns that do not move the position: their angle is zero
-        const T e0 = branch(zero);
+        if constexpr (!ALL) {
+            const T e0 = branch(zero);
 #pragma unroll
-        for (int i = 2; i < 5; ++i)
-            ep[q][i] = em[q][i] = e0;
+            for (int i = 2; i < 5; ++i)
+                ep[q][i] = em[q][i] = e0;
+        }
     }
     const T Sn[2][2] = {{P.sigma, T(0)}, {T(0), P.sigma}};
     cubature_from_dev(mg, Sn, ep, em, r, H, d, S);

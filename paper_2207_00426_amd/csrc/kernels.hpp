@@ -1787,7 +1787,7 @@ __global__ __launch_bounds__(256) void k_slr_felem_ct(const int64_t *y_off, int 
         if (taylor)
             ct_taylor_bearings(P, mg, yy, H, d, SO);
         else
-            ct_slr_bearings(P, mg, yy, H, d, SO);
+            ct_slr_bearings<T, COV>(P, mg, yy, H, d, SO);
 #pragma unroll
         for (int r = 0; r < 5; ++r)
             rk1[r] = mg.m[r];
