@@ -304,7 +304,7 @@ struct AdjPrior {
 // (nullable) the log-likelihood terms at the interleaved slots.  ADJ: the maps
 // T_k folded into an element of the adjoint scan's level 1 (scanned backwards).
 template <typename T, int NX, int NY, bool ADJ, class AggRef, class PreRef>
-__global__ __launch_bounds__(256) void k_filter_walk(LevelGeom g, GammaRef<T, NX, NY> gam,
+__global__ __launch_bounds__(256) void k_filter_walk(StepGeom g, GammaRef<T, NX, NY> gam,
                                                      const T *y, int64_t T_y,
                                                      StepPrior<T, NX> prior, PreRef pre,
                                                      MargRef<T, NX> have, MargRef<T, NX> marg,
@@ -505,7 +505,7 @@ struct AdjDst {
 };
 
 template <typename T, int NX, int NY, class Out, class PreRef>
-__global__ __launch_bounds__(256) void k_adj_down(LevelGeom g, GammaRef<T, NX, NY> gam,
+__global__ __launch_bounds__(256) void k_adj_down(StepGeom g, GammaRef<T, NX, NY> gam,
                                                   const T *y, int64_t T_y, MargRef<T, NX> marg,
                                                   PreRef pre, Out out, AdjPrior<T, NX> prior,
                                                   const int64_t *next_off)

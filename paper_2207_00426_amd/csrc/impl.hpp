@@ -243,7 +243,15 @@ struct Core {
         g.B = c.B;
         g.E = sh.E[l];
         g.stage = scan_stage(Op::NE, Op::NP, sh.T[l], sh.E[l], sizeof(T));
-        g.few = l == 0 ? sh.few : ShortRule{};
+        return g;
+    }
+    // the finest level's, where it runs Kalman steps
+    template <class Op>
+    static StepGeom step_geom(const Ctx &c, const ScanShape &sh, const ScanWs<Op> &w)
+    {
+        StepGeom g;
+        static_cast<LevelGeom &>(g) = level_geom(c, sh, w, 0, 0);
+        g.few = sh.few;
         return g;
     }
 
@@ -1059,7 +1067,7 @@ struct Core {
         const auto agg = agg_of(sh, w, 1, &felem_ref);
         using Agg = std::decay_t<decltype(agg)>;
         hipLaunchKernelGGL((k_step_fold<T, NX, NY, Agg>), dim3((unsigned)sh.ntiles[0]),
-                           dim3(sh.T[0]), 0, c.s, level_geom(c, sh, w, 0, 0), gam, cptr<T>(y),
+                           dim3(sh.T[0]), 0, c.s, step_geom(c, sh, w), gam, cptr<T>(y),
                            c.T_y, prior, nom, agg, w.elem_off[1], sh.T[1], agg_ilv<FS>(sh));
         return hip_check(hipGetLastError(), "step fold launch");
     }
@@ -1071,7 +1079,7 @@ struct Core {
                          const NomRef<T, NX> &out, const SElemRef<T, NX> &stash,
                          const MargAos<T, NX> &last, const MargRef<T, NX> &filt)
     {
-        const LevelGeom g = level_geom(c, sh, w, 0, 0);
+        const StepGeom g = step_geom(c, sh, w);
         const dim3 grid((unsigned)sh.ntiles[0]), block(sh.T[0]);
         const StepPrior<T, NX> prior{cptr<T>(c.p->m0), cptr<T>(c.p->N0), cptr<T>(c.dev_m),
                                      nom.r.ld};
@@ -1224,7 +1232,7 @@ struct Core {
         const StepPrior<T, NX> prior{cptr<T>(c.p->m0), cptr<T>(c.p->N0), nullptr, 0};
         hipLaunchKernelGGL((k_filter_walk<T, NX, NY, ADJ, Agg, Pre>),
                            dim3((unsigned)s.sh.ntiles[0]), dim3(s.sh.T[0]), 0, c.s,
-                           level_geom(c, s.sh, s.w, 0, 0), s.gam, cptr<T>(y), c.T_y, prior, pre,
+                           step_geom(c, s.sh, s.w), s.gam, cptr<T>(y), c.T_y, prior, pre,
                            have, out, ell, agg, s.w.elem_off[1], s.sh.T[1], agg_ilv<AS>(s.sh));
         return hip_check(hipGetLastError(), "filter walk launch");
     }
@@ -1361,7 +1369,7 @@ struct Core {
                     using Pre = std::decay_t<decltype(pre)>;
                     hipLaunchKernelGGL((k_adj_down<T, NX, NY, Out, Pre>),
                                        dim3((unsigned)s.sh.ntiles[0]), dim3(s.sh.T[0]), 0, c.s,
-                                       level_geom(c, s.sh, wa, 0, 0), s.gam, cptr<T>(y), c.T_y,
+                                       step_geom(c, s.sh, wa), s.gam, cptr<T>(y), c.T_y,
                                        s.marg, pre, out, prior, wa.elem_off[1]);
                     return hip_check(hipGetLastError(), "adjoint down launch");
                 });

@@ -486,7 +486,11 @@ struct LevelGeom {
     int E;
     int stage; // outputs staged in LDS and written by the whole block (needs
                // NP * T * E values of LDS)
-    ShortRule few; // level 0: E by the sequence's length
+};
+
+// level 0 where it runs steps: E by the sequence's length
+struct StepGeom : LevelGeom {
+    ShortRule few;
 };
 
 PSS_INL void seq_range(const LevelGeom &g, int b, int64_t &off, int64_t &cnt)
@@ -540,20 +544,29 @@ PSS_INL int64_t ilv_slot(const TileInfo &ti, int64_t p)
     return ti.off + ti.start + ilv((int)(p - ti.start), ti.tcnt, ti.E);
 }
 
-PSS_INL TileInfo tile_info(const LevelGeom &g)
+template <class Elems>
+PSS_INL TileInfo tile_info(const LevelGeom &g, Elems &&elems)
 {
     TileInfo ti;
     const int64_t tile = blockIdx.x;
     ti.b = find_seq(g.tile_off, g.B, tile, 0);
     const int64_t tin = tile - g.tile_off[ti.b];
     seq_range(g, ti.b, ti.off, ti.cnt);
-    ti.E = g.few.elems(ti.cnt, g.E);
+    ti.E = elems(ti.cnt);
     const int64_t TS = (int64_t)blockDim.x * ti.E;
     ti.start = tin * TS;
     const int64_t rem = ti.cnt - ti.start;
     ti.tcnt = (int)(rem < TS ? rem : TS);
     ti.nvalid = (ti.tcnt + ti.E - 1) / ti.E;
     return ti;
+}
+PSS_INL TileInfo tile_info(const LevelGeom &g)
+{
+    return tile_info(g, [&](int64_t) { return g.E; });
+}
+PSS_INL TileInfo tile_info(const StepGeom &g)
+{
+    return tile_info(g, [&](int64_t cnt) { return g.few.elems(cnt, g.E); });
 }
 
 // --- element sources --------------------------------------------------------

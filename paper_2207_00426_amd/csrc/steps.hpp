@@ -145,7 +145,7 @@ struct StepPrior {
 };
 
 template <typename T, int NX, int NY, class AggRef>
-__global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, NY> gam,
+__global__ __launch_bounds__(256) void k_step_fold(StepGeom g, GammaRef<T, NX, NY> gam,
                                                    const T *y, int64_t T_y,
                                                    StepPrior<T, NX> prior, NomRef<T, NX> nom,
                                                    AggRef agg, const int64_t *next_off, int nT,
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void k_step_fold(LevelGeom g, GammaRef<T, NX, 
 // filtering marginals on request: state k of sequence b at plain slot
 // y_off[b] + b + k of (m, N); m null: not taken
 template <typename T, int NX, int NY, class AggRef, class PreRef>
-__global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, NY> gam,
+__global__ __launch_bounds__(256) void k_step_walk(StepGeom g, GammaRef<T, NX, NY> gam,
                                                    const T *y, int64_t T_y,
                                                    StepPrior<T, NX> prior, NomRef<T, NX> nom,
                                                    PreRef pre, SElemRef<T, NX> stash,
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(256) void k_step_walk(LevelGeom g, GammaRef<T, NX, 
 }
 
 template <typename T, int NX, class PreRef>
-__global__ __launch_bounds__(256) void k_step_smooth(LevelGeom g, SElemRef<T, NX> stash,
+__global__ __launch_bounds__(256) void k_step_smooth(StepGeom g, SElemRef<T, NX> stash,
                                                      PreRef pre, MargAos<T, NX> last,
                                                      NomRef<T, NX> dev, NomRef<T, NX> out,
                                                      const int64_t *next_off)
