@@ -115,12 +115,15 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
     ScanShape sh;
     sh.few = few;
     std::vector<int64_t> cnt(c.B);
-    // the sequence's level-0 elements per thread, decided before cnt shrinks
-    std::vector<int> E_seq(c.B);
+    // with a rule, the sequence's level-0 elements per thread, decided before
+    // cnt shrinks
+    const bool ruled = few.half > 0 || few.quarter > 0;
+    std::vector<int> E_seq(ruled ? c.B : 0);
     int64_t total = 0;
     for (int b = 0; b < c.B; ++b) {
         cnt[b] = c.p->y_off_host[b + 1] - c.p->y_off_host[b] + extra;
-        E_seq[b] = few.elems(cnt[b], E0);
+        if (ruled)
+            E_seq[b] = few.elems(cnt[b], E0);
         total += cnt[b];
     }
     sh.nelem[0] = total;
@@ -130,7 +133,7 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
         const int64_t TS = (int64_t)sh.T[l] * sh.E[l];
         int64_t nt = 0, mx = 0;
         for (int b = 0; b < c.B; ++b) {
-            const int64_t ts = l == 0 ? (int64_t)T0 * E_seq[b] : TS;
+            const int64_t ts = l == 0 && ruled ? (int64_t)T0 * E_seq[b] : TS;
             mx = std::max(mx, cnt[b]);
             nt += (cnt[b] + ts - 1) / ts;
         }
@@ -147,7 +150,7 @@ ScanShape plan_scan(const Ctx &c, int extra, int T0, int E0, int Tup, int E1, in
         const int64_t D = sh.flat[l] ? sh.E[l] : TS;
         int64_t ne = 0;
         for (int b = 0; b < c.B; ++b) {
-            const int64_t d = sh.flat[l] ? E_seq[b] : D;
+            const int64_t d = sh.flat[l] && ruled ? E_seq[b] : D;
             cnt[b] = (cnt[b] + d - 1) / d;
             ne += cnt[b];
         }

@@ -659,11 +659,14 @@ struct Core {
         return std::max({fscan_bytes(c), adj, seq_sum_bytes(c, nc)});
     }
 
+    // (each part walks the sequences: only what the operation needs)
     static size_t ws_size(const Ctx &c, int op)
     {
-        const size_t scans = fscan_bytes(c) > sscan_bytes(c) ? fscan_bytes(c) : sscan_bytes(c);
-        const size_t fwd = gamma_bytes(c) + felem_bytes(c) + marg_bytes(c) +
-                           align256(c.T_y * sizeof(double));
+        auto scans = [&]() { return std::max(fscan_bytes(c), sscan_bytes(c)); };
+        auto fwd = [&]() {
+            return gamma_bytes(c) + felem_bytes(c) + marg_bytes(c) +
+                   align256(c.T_y * sizeof(double));
+        };
         switch (op) {
         case PSS_OP_SLR:
         case PSS_OP_FILTER_ELEMENTS:
@@ -672,22 +675,27 @@ struct Core {
             return fscan_bytes(c);
         case PSS_OP_SMOOTHER_SCAN:
             return sscan_bytes(c);
-        case PSS_OP_IPLS:
-            // stored elements (covariance form), or the steps' stash, which
-            // is smaller by about a marginal per step
+        case PSS_OP_IPLS: {
+            // stored elements, which the covariance form uses; the steps' stash
+            // is smaller by about a marginal per step, and the size a caller
+            // asks for stays one for both
+            const size_t el = felem_bytes(c) + scans();
             return gamma_bytes(c) + marg_bytes(c) +
-                   std::max(felem_bytes(c) + scans, align256(step_stash(c) * sizeof(T)) +
-                                                        scan_bytes(c, step_shape(c)));
+                   (c.p->form == PSS_FORM_COV
+                        ? el
+                        : std::max(el, align256(step_stash(c) * sizeof(T)) +
+                                           scan_bytes(c, step_shape(c))));
+        }
         case PSS_OP_LOGLIK:
-            return fwd + grad_scans(c, 1);
+            return fwd() + grad_scans(c, 1);
         case PSS_OP_LOGLIK_GRAD:
-            return fwd + grad_scans(c, 3) + align256(3 * c.T_y * sizeof(double)) +
+            return fwd() + grad_scans(c, 3) + align256(3 * c.T_y * sizeof(double)) +
                    align256(3 * c.B * sizeof(double));
         case PSS_OP_LOGLIK_VJP:
-            return fwd + grad_scans(c, 1);
+            return fwd() + grad_scans(c, 1);
         case PSS_OP_SCORE_FISHER:
             return gamma_bytes(c) + felem_bytes(c) + marg_bytes(c) +
-                   align256(c.T_y * sizeof(double)) + std::max(scans, seq_sum_bytes(c, 3)) +
+                   align256(c.T_y * sizeof(double)) + std::max(scans(), seq_sum_bytes(c, 3)) +
                    marg_bytes(c) + align256(3 * c.T_y * sizeof(double)) +
                    align256(3 * c.B * sizeof(double));
         case PSS_OP_SEQUENTIAL:
