@@ -724,8 +724,13 @@ struct Core {
             cv.template take<T>((size_t)Sizes<NX>::marg * c.T_x);
         } else {
             const ScanShape sh = filter_shape(c);
-            if (level < sh.L)
-                cv.template take<T>((size_t)Sizes<NX>::marg * sh.nelem[level]);
+            int64_t n = level < sh.L ? sh.nelem[level] : 0;
+            if constexpr (kStepsLL) { // what fills it (no more, by its longer runs)
+                const ScanShape gs = grad_shape(c);
+                n = std::max(n, level < gs.L ? gs.nelem[level] : 0);
+            }
+            if (n > 0)
+                cv.template take<T>((size_t)Sizes<NX>::marg * n);
         }
         return cv.used;
     }
@@ -1167,10 +1172,12 @@ struct Core {
         if ((rc = lin_elements(c, gin, m_nom, N_nom, y, gw, &el)))
             return rc;
         T *Nfb = mfb + (size_t)NX * c.T_x;
-        if (!kStepsLL && !cov)
-            rc = fscan_lane(c, &el, mfb, Nfb, scan_ws, ck.level, ck.pre, false);
-        else
+        if constexpr (kStepsLL)
             rc = fscan(c, &el, mfb, Nfb, scan_ws, true, cov);
+        else if (cov)
+            rc = fscan(c, &el, mfb, Nfb, scan_ws, true, true);
+        else
+            rc = fscan_lane(c, &el, mfb, Nfb, scan_ws, ck.level, ck.pre, false);
         if (rc)
             return rc;
         const int tb = 128;
