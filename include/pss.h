@@ -21,7 +21,9 @@
  * Conventions shared by every entry point
  *   - Every buffer pointer is a DEVICE pointer unless its name ends in
  *     "_host".  The caller allocates and owns every buffer; the library never
- *     allocates device memory and keeps no device state between calls.
+ *     allocates device memory and keeps no device state between calls, but
+ *     for up to 8 streams, with an event each, that pss_ipls_batched lends to
+ *     its groups.
  *   - Every call is asynchronous on the caller's HIP stream `stream` and
  *     returns PSS_OK or a negative status.  Arguments are validated on the
  *     host before anything is enqueued; a failed validation enqueues nothing.

@@ -18,16 +18,18 @@ inline const T *cptr(const void *p) { return static_cast<const T *>(p); }
 template <typename T>
 inline T *mptr(void *p) { return static_cast<T *>(p); }
 
-// default launch shapes (overridable through pss_problem).  One 64-lane
-// wave per tile; the filter folds 4 elements per thread, the smoother 2 (its
-// operator is cheaper, and with 2 its level-0 reads and stash writes stay
-// closer to whole cache lines).  The filter's finest level is flat: its
-// per-thread aggregates are the next level's elements, so no in-tile tree
-// runs there (a tree step keeps the whole wave busy for one operator while
-// half of its lanes or fewer have work); its next level, n/4 elements, folds
-// 4 per thread, the levels above it 2.  The smoother's operator is cheap
-// next to its element construction, so its finest level keeps the tree and
-// saves a level; its upper levels fold 2.
+// default launch shapes (overridable through pss_problem).  One 64-lane wave per
+// tile at the finest level; where it scans stored elements, the filter folds 4 of
+// them per thread, the smoother 2 (its operator is cheaper, and with 2 its level-0
+// reads and stash writes stay closer to whole cache lines).  The filter's finest
+// level is flat: its per-thread aggregates are the next level's elements, so no
+// in-tile tree runs there (a tree step keeps the whole wave busy for one operator
+// while half of its lanes or fewer have work).  The smoother's operator is cheap
+// next to its element construction, so its finest level keeps the tree and saves a
+// level.  Above it, Tup x E1 and Tup x Eup only set how many elements a tile has:
+// its block splits them over 32 groups of 16 lanes (scan_group.hpp), 8 elements a
+// group in a full tile of 256.  One element per lane, T threads of E, is left for a
+// scalar state, the covariance form and FP32 log-likelihoods.
 template <typename T, int NX>
 struct Defaults {
     static constexpr int T0 = 64;
