@@ -22,8 +22,8 @@
 // The linearisation, the stash of smoother elements and the nominal between
 // passes are tile-interleaved (ilv): a wave's accesses are whole lines.
 //
-// Measured at 10^6 FP64 coordinated-turn steps, per pass: fold 0.150 ms for 0.56
-// GB (3.7 TB/s, one wave a SIMD), walk 0.200 ms for 0.92 GB, smooth 0.12 ms for
+// Measured at 10^6 FP64 coordinated-turn steps, per pass: fold 0.137 ms for 0.56
+// GB (4.1 TB/s, one wave a SIMD), walk 0.193 ms for 0.92 GB, smooth 0.12 ms for
 // 0.54 GB (both bound by their bytes; a large copy reaches 4.9 TB/s); they replace
 // element build (0.224), filter up and down (0.202, 0.139) and smoother up and down
 // (0.334, 0.191 ms).  Holding fold and walk to 256 registers (two waves a SIMD)
